@@ -260,6 +260,16 @@ int isdf_zc_ab(const isdf_grid* grid /* host */, int32_t dt,
 int isdf_apply_minv(int32_t n_mu, int32_t aliased, const double* minv, const double* G, int64_t ldg,
                     int64_t nrows, int32_t dt, void* theta, int64_t ld_theta, void* stream);
 
+/* isdf_apply_minv_ws: the same product with a workspace
+ * (isdf_apply_minv_workspace bytes, 0 where it would not be used), which lets
+ * it run on the 8-bit matrix cores by residues where that is faster; FP64
+ * results either way.  ws null: isdf_apply_minv.
+ */
+size_t isdf_apply_minv_workspace(int32_t n_mu, int32_t aliased, int64_t nrows);
+int isdf_apply_minv_ws(int32_t n_mu, int32_t aliased, const double* minv, const double* G, int64_t ldg,
+                       int64_t nrows, int32_t dtype, void* theta, int64_t ld_theta, void* ws, size_t ws_bytes,
+                       void* stream);
+
 /*
  * Adjoint of isdf_fit with the interpolation points fixed (the paper gives
  * no adjoint; this is reverse-mode differentiation of eq. theta).  With

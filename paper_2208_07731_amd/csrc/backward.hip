@@ -190,6 +190,98 @@ struct EpiSAdj {
   }
 };
 
+// EpiSAdj for the residue form of the product: the same arithmetic on the 4
+// consecutive outputs of a thread (two whole columns nu in the complex case),
+// loss and maxima summed per workgroup.
+struct ModSAdj {
+  static constexpr int REP = 8;
+  struct Sum {
+    double loss, ma, mb;
+  };
+  const double* G;
+  int64_t ldg;
+  double* A;
+  double* B;
+  int64_t ldab;
+  const double* g;
+  int N;
+  int aliased;
+  int vec;  // pairs of a row of G aligned
+  double* partial;
+  double* amax;
+  __device__ __forceinline__ void operator()(int m, int n, const double (&c)[4], Sum& t) const {
+    const double gm = g[m];
+    const double* gr = G + (int64_t)m * ldg + n;
+    double gv[4];
+    if (vec && n + 4 <= N) {
+      load_pair<double>(gr, gv[0], gv[1]);
+      load_pair<double>(gr + 2, gv[2], gv[3]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) gv[e] = n + e < N ? gr[e] : 0.0;
+    }
+    if (aliased) {
+      double2* a = reinterpret_cast<double2*>(A + (int64_t)m * ldab) + n;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (n + e < N) {
+          const double s = 2.0 * gm * c[e];
+          t.loss += gm * c[e] * gv[e];
+          const double2 x = a[e];
+          const double2 o = make_double2(s * x.x, s * x.y);
+          a[e] = o;
+          t.ma = fmax(t.ma, fmax(fabs(o.x), fabs(o.y)));
+        }
+    } else {  // N even: (c[2 u], c[2 u + 1]) = S of column n / 2 + u over 2 g
+      double2* a = reinterpret_cast<double2*>(A + (int64_t)m * ldab) + n / 2;
+      double2* b = reinterpret_cast<double2*>(B + (int64_t)m * ldab) + n / 2;
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        if (n + 2 * u < N) {
+          const double sr = 2.0 * gm * c[2 * u], si = 2.0 * gm * c[2 * u + 1];
+          t.loss += gm * c[2 * u] * gv[2 * u];
+          t.loss += gm * c[2 * u + 1] * gv[2 * u + 1];
+          const double2 av = a[u], bv = b[u];
+          const double2 ob = make_double2(sr * bv.x - si * bv.y, sr * bv.y + si * bv.x);
+          const double2 oa = make_double2(sr * av.x + si * av.y, sr * av.y - si * av.x);
+          b[u] = ob;
+          a[u] = oa;
+          t.ma = fmax(t.ma, fmax(fabs(ob.x), fabs(ob.y)));
+          t.mb = fmax(t.mb, fmax(fabs(oa.x), fabs(oa.y)));
+        }
+    }
+  }
+  __device__ __forceinline__ void off() const {
+    if (threadIdx.x == 0) partial[blockIdx.x] = 0.0;
+  }
+  __device__ __forceinline__ void finish(const Sum& t) const {
+    __shared__ double red[3][256 / ISDF_WAVE];
+    const int w = threadIdx.x >> 6;
+    double l = wave_sum(t.loss), ma = t.ma, mb = t.mb;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      ma = fmax(ma, __shfl_xor(ma, o, ISDF_WAVE));
+      mb = fmax(mb, __shfl_xor(mb, o, ISDF_WAVE));
+    }
+    if ((threadIdx.x & 63) == 0) {
+      red[0][w] = l;
+      red[1][w] = ma;
+      red[2][w] = mb;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int i = 1; i < 256 / ISDF_WAVE; ++i) {
+        l += red[0][i];
+        ma = fmax(ma, red[1][i]);
+        mb = fmax(mb, red[2][i]);
+      }
+      partial[blockIdx.x] = l;
+      if (amax && ma > 0.0) atomic_max_pos(amax, ma);
+      if (amax && mb > 0.0) atomic_max_pos(amax + 1, mb);
+    }
+  }
+};
+
 // Largest |x| and |x rowscale[k]| over the rows of a real r-major block
 // (binary16 scales of the two split operands of H), folded into out[0] and
 // out[1] (positive doubles order like their bit patterns).
@@ -436,6 +528,7 @@ struct BwdPlan {
   double* tpart; // split-K partials of those products (null: never split)
   SplitWork sw;  // orbital-row and Gram right-hand-side planes (split precisions)
   AdjPlanes ap;  // Abar / Bbar and F planes (split precisions)
+  ModWork mod;   // residues of the products with (C C^H)^-1 and (C C^H)^-2
   int slots;     // workgroup slots the split factors were chosen for
   size_t bytes;
 };
@@ -489,7 +582,10 @@ static BwdPlan plan_bwd(void* ws, size_t cap, int64_t nr, int n_mu, int n_phi, i
   P.dA = c.take<double>((size_t)n_mu * 2 * n_mu);
   if (!aliased) P.dB = c.take<double>((size_t)n_mu * 2 * n_mu);
   P.T1 = c.take<double>((size_t)n_mu * 2 * nmax);
-  P.lpart = c.take<double>((size_t)ceil_div(rblock, 128) * ceil_div(n1, 128));
+  P.mod = carve_mod(c, rblock, n1, n1);
+  size_t lp = (size_t)ceil_div(rblock, 128) * ceil_div(n1, 128);
+  if (P.mod.mp) lp += (size_t)ceil_div(rblock, P.mod.mp) * (mod_crt_blocks<ModSAdj>(P.mod.mp, n1) + ceil_div(n1, 128));
+  P.lpart = c.take<double>(lp);
   P.sw = carve_split(c, prec, n_phi, n_psi, aliased, n_mu, rblock > n_mu ? rblock : n_mu);
   P.ap = carve_adj(c, prec, n_phi, n_psi, aliased, n_mu, rblock);
   if (prec == ISDF_P_BF16X6 || prec == ISDF_P_FP16X3) {
@@ -741,7 +837,7 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
                                                  P.ap.f_psi, P.ap.ldp, 2 * n_psi, sc ? sc + 3 : nullptr, s))
         return ISDF_E_HIP;
     }
-    if (!tbar && !dgemm<KC, KC, double>(n1, n1, n1, minv, n1, minv, n1, P.W2, n1, 1.0, 0.0, 0, ab, s))
+    if (!tbar && !nt_product<double>(n1, n1, n1, minv, n1, minv, n1, MOD_DIAG_B, P.W2, n1, 1.0, P.mod, false, ab, s))
       return ISDF_E_HIP;  // (C C^H)^-2
   }  // BWD_BEGIN
   for (int64_t r = row_lo; r < row_hi; r += rblock) {
@@ -795,18 +891,44 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
       EpiSAdj epi{Gb,  n1, Ab, Bb, 2 * (int64_t)n_mu, g + r, rows, n1, aliased ? 1 : 0, P.lpart,
                   SPLIT == SPLIT_FP16X3 ? P.amax + 4 : nullptr};
       Operand<double> a{Gb, n1, nullptr, nullptr}, b{P.W2, n1, nullptr, nullptr};
-      if (!launch_gemm<double, 128, 128, 16, 2, 2, double, KC, double, KC, 1>(rows, n1, n1, a, b, a, b, 0, epi, 0, ab,
-                                                                             s))
-        return ISDF_E_HIP;
-      const int ltiles = (int)(ceil_div(rows, 128) * ceil_div(n1, 128));
-      hipLaunchKernelGGL(add_loss, dim3(1), dim3(LOSS_THREADS), 0, s, P.st, (const double*)P.lpart, ltiles);
+      int64_t ltiles = 0;
+      if (P.mod.mp && mod_pays(rows, n1, n1)) {
+        // by residues, panel by panel; the FP64 kernel behind each panel runs
+        // (and writes its loss partials, zero otherwise) only on a flag
+        const ModWork& w = P.mod;
+        const int64_t mp = w.mp, fp64 = ceil_div(rows, mp) * ceil_div(mp, 128) * ceil_div(n1, 128);
+        if (!fill<double>(P.lpart, fp64, 0.0, s)) return ISDF_E_HIP;
+        ltiles = fp64;
+        if (!mod_prepare(P.W2, n1, n1, n1, MOD_DIAG_B, P.W2, n1, w, ab, s)) return ISDF_E_HIP;
+        for (int64_t q = 0, p = 0; q < rows; q += mp, ++p) {
+          const int pr = (int)(rows - q < mp ? rows - q : mp);
+          double *Aq = Ab + q * 2 * n_mu, *Bq = aliased ? nullptr : Bb + q * 2 * n_mu, *Gq = Gb + q * n1;
+          ModSAdj me{Gq, n1, Aq, Bq, 2 * (int64_t)n_mu, g + r + q, n1, aliased ? 1 : 0,
+                     n1 % 2 == 0 && (uintptr_t)Gq % 16 == 0, P.lpart + ltiles, epi.amax};
+          if (!mod_panel<double>(Gq, n1, pr, n1, n1, MOD_DIAG_B, (int)p, w, me, ab, s)) return ISDF_E_HIP;
+          ltiles += mod_crt_blocks<ModSAdj>(pr, n1);
+          EpiSAdj eq{Gq, n1, Aq, Bq, 2 * (int64_t)n_mu, g + r + q, pr, n1, aliased ? 1 : 0,
+                     P.lpart + p * ceil_div(mp, 128) * ceil_div(n1, 128), epi.amax};
+          Operand<double> aq{Gq, n1, nullptr, nullptr};
+          if (!launch_gemm<double, 128, 128, 16, 2, 2, double, KC, double, KC, 1>(
+                  pr, n1, n1, aq, b, aq, b, 0, eq, 0, ab, s, 1, 1, 0, 0, w.flags, w.flags + 1 + p))
+            return ISDF_E_HIP;
+        }
+      } else {
+        if (!launch_gemm<double, 128, 128, 16, 2, 2, double, KC, double, KC, 1>(rows, n1, n1, a, b, a, b, 0, epi, 0, ab,
+                                                                               s))
+          return ISDF_E_HIP;
+        ltiles = ceil_div(rows, 128) * ceil_div(n1, 128);
+      }
+      hipLaunchKernelGGL(add_loss, dim3(1), dim3(LOSS_THREADS), 0, s, P.st, (const double*)P.lpart, (int)ltiles);
       if (!launch_ok()) return ISDF_E_HIP;
     } else {
       // Theta = G M^-1, S = Thetabar M^-1 (over G), P += Theta^T S, Abar / Bbar in place
-      if (!dgemm<KC, KC, double>(rows, n1, n1, Gb, n1, minv, n1, P.Th, n1, 1.0, 0.0, 0, ab, s)) return ISDF_E_HIP;
+      if (!nt_product<double>(rows, n1, n1, Gb, n1, minv, n1, MOD_DIAG_B, P.Th, n1, 1.0, P.mod, false, ab, s))
+        return ISDF_E_HIP;
       const int64_t ldt = aliased ? ld_tbar : 2 * ld_tbar;
-      if (!dgemm<KC, KC, double, TT>(rows, n1, n1, tbar + (r - gbase) * ldt, ldt, minv, n1, Gb, n1, 1.0, 0.0, 0, ab,
-                                     s))
+      if (!nt_product<double, TT>(rows, n1, n1, tbar + (r - gbase) * ldt, ldt, minv, n1, MOD_DIAG_B, Gb, n1, 1.0, P.mod,
+                                  mod_pays(rows, n1, n1), ab, s))
         return ISDF_E_HIP;
       const int sp = sp_phi.h;
       const int64_t pn = (int64_t)n1 * n1;
@@ -842,8 +964,11 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
     // Theta^T S = 2 M^-1 H M^-2 with H = G^T diag(g) G
     const int64_t pn = (int64_t)n1 * n1;
     hipLaunchKernelGGL(mirror_lower, dim3(blocks_for(pn)), dim3(256), 0, s, P.P, n1, ab);
-    if (!dgemm<KC, KC, double>(n1, n1, n1, P.P, n1, P.W2, n1, P.Ppart, n1, 1.0, 0.0, 0, ab, s)) return ISDF_E_HIP;
-    if (!dgemm<KC, XC, double>(n1, n1, n1, minv, n1, P.Ppart, n1, P.P, n1, 2.0, 0.0, 0, ab, s)) return ISDF_E_HIP;
+    // (all symmetric: (C C^H)^-2 H = (H (C C^H)^-2)^T is the second product's K-contiguous operand)
+    if (!nt_product<double>(n1, n1, n1, P.W2, n1, P.P, n1, MOD_DIAG_B, P.Ppart, n1, 1.0, P.mod, false, ab, s))
+      return ISDF_E_HIP;
+    if (!nt_product<double>(n1, n1, n1, minv, n1, P.Ppart, n1, MOD_DIAG_A, P.P, n1, 2.0, P.mod, false, ab, s))
+      return ISDF_E_HIP;
   }
   // Mbar terms at the interpolation rows
   if (!gram<PREC, TS>(phi, ld_phi, n_phi, psi, ld_psi, n_psi, aliased, Ephi, Epsi, nmu16, n_mu, idx, nr, 0, n_mu,

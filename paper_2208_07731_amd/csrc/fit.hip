@@ -33,6 +33,7 @@ struct FitPlan {
   InvWork inv;
   double* G;
   SplitWork sw;
+  ModWork mod;   // residues of the solve Theta = G M^-1
   double* Th;    // residual mode: Theta of one r-block (FP64)
   double* part;  // residual mode: per-workgroup (||Z||^2 - Re G.Theta, ||Z||^2) pairs
   size_t bytes;
@@ -57,6 +58,7 @@ static FitPlan plan_fit(void* ws, size_t cap, int64_t nr, int n_mu, int n_phi, i
   P.inv.R = c.take<double>((size_t)n1 * n1);
   P.G = c.take<double>((size_t)rblock * n1);
   P.sw = carve_split(c, prec, n_phi, n_psi, aliased, n_mu, rblock > n_mu ? rblock : n_mu);
+  P.mod = carve_mod(c, rblock < nr ? rblock : nr, n1, n1);
   if (resid) {
     P.Th = c.take<double>((size_t)rblock * n1);
     P.part = c.take<double>((size_t)2 * RESID_BLOCKS * ceil_div(nr, rblock));
@@ -137,7 +139,7 @@ static int fit_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
                         row0 + r, rows, P.G, n1, aliased ? G_REAL : G_CPLX, ab, s, P.sc, &P.sw))
       return ISDF_E_HIP;
     const int64_t ldt = aliased ? ld_theta : 2 * ld_theta;
-    if (!dgemm<KC, KC, TT>(rows, n1, n1, P.G, n1, minv, n1, theta + r * ldt, ldt, 1.0, 0.0, 0, ab, s))
+    if (!nt_product<TT>(rows, n1, n1, P.G, n1, minv, n1, MOD_DIAG_B, theta + r * ldt, ldt, 1.0, P.mod, r > 0, ab, s))
       return ISDF_E_HIP;
   }
   hipLaunchKernelGGL(fit_finish, dim3(1), dim3(1), 0, s, P.st, info, (double*)nullptr, 0);
@@ -170,7 +172,8 @@ static int resid_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const
     if (!gram<PREC, TS>(phi, ld_phi, n_phi, psi, ld_psi, n_psi, aliased, Ephi, Epsi, nmu16, n_mu, nullptr, nr, r, rows,
                         P.G, n1, aliased ? G_REAL : G_CPLX, ab, s, P.sc, &P.sw))
       return ISDF_E_HIP;
-    if (!dgemm<KC, KC, double>(rows, n1, n1, P.G, n1, minv, n1, P.Th, n1, 1.0, 0.0, 0, ab, s)) return ISDF_E_HIP;
+    if (!nt_product<double>(rows, n1, n1, P.G, n1, minv, n1, MOD_DIAG_B, P.Th, n1, 1.0, P.mod, r > 0, ab, s))
+      return ISDF_E_HIP;
     hipLaunchKernelGGL((fit_resid_rows<TS>), dim3(RESID_BLOCKS), dim3(PAIR_THREADS), 0, s, (const double*)P.G,
                        (const double*)P.Th, rows, n1, phi, ld_phi, n_phi, psi, ld_psi, n_psi, aliased ? 1 : 0, r,
                        P.part + 2 * RESID_BLOCKS * blk);
@@ -404,20 +407,44 @@ extern "C" int isdf_zc_ab(const isdf_grid* grid, int32_t dt_in, const void* phi,
                      true, ws, ws_bytes, stream);
 }
 
-extern "C" int isdf_apply_minv(int32_t n_mu, int32_t aliased, const double* minv, const double* G, int64_t ldg,
-                               int64_t nrows, int32_t dt_in, void* theta, int64_t ld_theta, void* stream) {
+static int apply_minv(int32_t n_mu, int32_t aliased, const double* minv, const double* G, int64_t ldg, int64_t nrows,
+                      int32_t dt_in, void* theta, int64_t ld_theta, void* ws, size_t ws_bytes, void* stream) {
   if (!dtype_valid(dt_in)) return ISDF_E_ARG;
   const isdf_dtype dt = (isdf_dtype)dt_in;
   const int64_t n1 = aliased ? n_mu : 2 * (int64_t)n_mu;
   if (n_mu <= 0 || !minv || nrows < 0 || nrows > INT32_MAX || (nrows > 0 && (!G || !theta))) return ISDF_E_ARG;
   if (ldg < n1 || ld_theta < n_mu || (dt != ISDF_C128 && dt != ISDF_C64)) return ISDF_E_ARG;
   if (nrows == 0) return ISDF_OK;
+  ModWork w{};
+  if (ws) {
+    Carver c(ws, ws_bytes);
+    w = carve_mod(c, nrows, n1, n1);
+    if (!c.fits()) return ISDF_E_WORKSPACE;
+  }
   hipStream_t s = (hipStream_t)stream;
   const int64_t ldt = aliased ? ld_theta : 2 * ld_theta;
-  bool ok = dt == ISDF_C128
-                ? dgemm<KC, KC, double>((int)nrows, (int)n1, n1, G, ldg, minv, n1, (double*)theta, ldt, 1.0, 0.0, 0,
-                                        nullptr, s)
-                : dgemm<KC, KC, float>((int)nrows, (int)n1, n1, G, ldg, minv, n1, (float*)theta, ldt, 1.0, 0.0, 0,
-                                       nullptr, s);
+  bool ok = dt == ISDF_C128 ? nt_product<double>(nrows, (int)n1, (int)n1, G, ldg, minv, n1, MOD_DIAG_B, (double*)theta, ldt,
+                                                 1.0, w, false, nullptr, s)
+                            : nt_product<float>(nrows, (int)n1, (int)n1, G, ldg, minv, n1, MOD_DIAG_B, (float*)theta, ldt, 1.0,
+                                                w, false, nullptr, s);
   return ok ? ISDF_OK : ISDF_E_HIP;
+}
+
+extern "C" int isdf_apply_minv(int32_t n_mu, int32_t aliased, const double* minv, const double* G, int64_t ldg,
+                               int64_t nrows, int32_t dt_in, void* theta, int64_t ld_theta, void* stream) {
+  return apply_minv(n_mu, aliased, minv, G, ldg, nrows, dt_in, theta, ld_theta, nullptr, 0, stream);
+}
+
+extern "C" size_t isdf_apply_minv_workspace(int32_t n_mu, int32_t aliased, int64_t nrows) {
+  if (n_mu <= 0 || nrows <= 0) return 0;
+  const int64_t n1 = aliased ? n_mu : 2 * (int64_t)n_mu;
+  Carver c(nullptr, 0);
+  carve_mod(c, nrows, n1, n1);
+  return c.used;
+}
+
+extern "C" int isdf_apply_minv_ws(int32_t n_mu, int32_t aliased, const double* minv, const double* G, int64_t ldg,
+                                  int64_t nrows, int32_t dt_in, void* theta, int64_t ld_theta, void* ws,
+                                  size_t ws_bytes, void* stream) {
+  return apply_minv(n_mu, aliased, minv, G, ldg, nrows, dt_in, theta, ld_theta, ws, ws_bytes, stream);
 }

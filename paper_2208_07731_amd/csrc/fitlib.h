@@ -6,6 +6,7 @@
 #include <float.h>
 #include <limits.h>
 
+#include "gemm_mod.h"
 #include "gemm_split.h"
 
 namespace isdf {
@@ -225,7 +226,8 @@ template <class T, int BM, int BN, int BK, int WM, int WN, class TA, int LA, cla
           int FOLD = 0, class Epi>
 static bool launch_gemm(int M, int N, int64_t K, Operand<TA> A0, Operand<TB> B0, Operand<TA> A1,
                         Operand<TB> B1, int64_t K1, const Epi& epi, int lower_only, const int* abort,
-                        hipStream_t st, int splits = 1, int batch = 1, int64_t sa = 0, int64_t sb = 0) {
+                        hipStream_t st, int splits = 1, int batch = 1, int64_t sa = 0, int64_t sb = 0,
+                        const int* only = nullptr, const int* only2 = nullptr) {
   if (M <= 0 || N <= 0) return true;
   GemmShape sh;
   sh.M = M;
@@ -235,6 +237,8 @@ static bool launch_gemm(int M, int N, int64_t K, Operand<TA> A0, Operand<TB> B0,
   sh.splits = splits;
   sh.lower_only = lower_only && M == N && BM == BN;
   sh.abort = abort;
+  sh.only = only;
+  sh.only2 = only2;
   sh.sa = sa;
   sh.sb = sb;
   const int64_t tiles = gemm_tiles((int)ceil_div(M, BM), (int)ceil_div(N, BN), sh.lower_only);
@@ -248,12 +252,36 @@ static bool launch_gemm(int M, int N, int64_t K, Operand<TA> A0, Operand<TB> B0,
 template <int LA, int LB, class TC, class TA = double>
 static bool dgemm(int M, int N, int64_t K, const TA* A, int64_t lda, const double* B, int64_t ldb, TC* C,
                   int64_t ldc, double alpha, double beta, int lower_only, const int* abort, hipStream_t st,
-                  const double* rowscale = nullptr) {
-  EpiStore<TC> epi{C, ldc, M, N, alpha, beta, rowscale, 0, 0};
+                  const int* only = nullptr, const int* only2 = nullptr) {
+  EpiStore<TC> epi{C, ldc, M, N, alpha, beta, nullptr, 0, 0};
   Operand<TA> a{A, lda, nullptr};
   Operand<double> b{B, ldb, nullptr};
   return launch_gemm<double, 128, 128, 16, 2, 2, TA, LA, double, LB, 1>(M, N, K, a, b, a, b, 0, epi, lower_only,
-                                                                       abort, st);
+                                                                       abort, st, 1, 1, 0, 0, only, only2);
+}
+
+// C = alpha A B^T in FP64, by residues where that is faster (mod_pays) and the
+// work buffers are there, else on the FP64 matrix cores.  bal: the symmetric
+// operand (of order K) whose diagonal balances the two.  `prepared`: B's
+// residues are in the buffers from an earlier call.
+template <class TC, class TA = double>
+static bool nt_product(int64_t M, int N, int K, const TA* A, int64_t lda, const double* B, int64_t ldb, int bal, TC* C,
+                       int64_t ldc, double alpha, const ModWork& w, bool prepared, const int* abort, hipStream_t st) {
+  if (!w.mp || !mod_pays(M, N, K))
+    return dgemm<KC, KC, TC, TA>((int)M, N, K, A, lda, B, ldb, C, ldc, alpha, 0.0, 0, abort, st);
+  if (!prepared && !mod_prepare(B, ldb, N, K, bal, bal == MOD_DIAG_A ? (const double*)A : B,
+                                bal == MOD_DIAG_A ? lda : ldb, w, abort, st))
+    return false;
+  const int vec = ldc % 2 == 0 && (uintptr_t)C % (2 * sizeof(TC)) == 0;
+  for (int64_t r = 0, p = 0; r < M; r += w.mp, ++p) {
+    const int rows = (int)(M - r < w.mp ? M - r : w.mp);
+    ModStore<TC> epi{C + r * ldc, ldc, N, alpha, vec};
+    if (!mod_panel<TA>(A + r * lda, lda, rows, N, K, bal, (int)p, w, epi, abort, st)) return false;
+    if (!dgemm<KC, KC, TC, TA>(rows, N, K, A + r * lda, lda, B, ldb, C + r * ldc, ldc, alpha, 0.0, 0, abort, st,
+                               w.flags, w.flags + 1 + p))
+      return false;
+  }
+  return true;
 }
 
 // Batched FP64 GEMM: batch b uses A + b sa, B + b sb, C + b sc.

@@ -77,6 +77,7 @@ struct GemmShape {
   int splits;        // number of K slices (grid = tiles x splits, one dimension)
   int lower_only;    // only tiles on or below the diagonal (M == N)
   const int* abort;  // nonzero *abort turns the launch into a no-op
+  const int *only, *only2;  // when given, *only and *only2 both zero do so too
   int64_t sa, sb;    // batch strides of A and B (elements); batch index = blockIdx.y
 };
 
@@ -516,6 +517,7 @@ __global__ __launch_bounds__(WM* WN* ISDF_WAVE, 2) void gemm_kernel(GemmShape sh
   static_assert(FOLD == 0 || sizeof(T) == 4, "folding is for FP32 accumulators");
   typedef TileCfg<T, BM, BN, BK, WM, WN> Cfg;
   if (sh.abort && *sh.abort) return;
+  if (sh.only && !(*sh.only | *sh.only2)) return;
   constexpr int STAGE = Lds<T, LA, BM, BK>::SIZE + Lds<T, LB, BN, BK>::SIZE;
   __shared__ __attribute__((aligned(16))) T smem[2 * STAGE];
   const int tiles_n = (sh.N + BN - 1) / BN;

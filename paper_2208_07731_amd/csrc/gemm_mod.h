@@ -1,0 +1,540 @@
+// FP64 products C = A B^T on the 8-bit matrix cores of gfx950, by residues.
+//
+//   C(m, n) = sum_k A(m, k) B(n, k), A and B K-contiguous, FP64 results.
+//
+// Each row of A and of B is scaled by a power of two to a 2-norm below 2^58
+// and rounded to integers (mod_split), so that every entry of the integer
+// product is below 2^116 (Cauchy-Schwarz) whatever K is.  The integer product
+// is computed exactly modulo 15 pairwise coprime moduli of at most 8 bits
+// (their product P is 2^117.8) with one int8 matrix product per modulus
+// (mod_gemm), and put together by the Chinese remainder theorem (mod_crt):
+// with w_i = ((P / p_i)^-1 mod p_i) / p_i, C / P = sum_i r_i w_i modulo 1.
+// The only errors are the rounding of the operands (absolute, 2^-59 of the
+// row's 2-norm per entry: 2^-53 relative for an entry 2^-6 of the norm, and
+// below the rounding that an FP64 sum of K products accumulates) and the last
+// rounding of C.  Residue products are the idea of Ozaki's scheme for matrix
+// multiplication through integer arithmetic; this form is derived from the
+// remainder theorem above.
+//
+// Why: the FP64 matrix cores do 78.6 TFLOP/s, the int8 ones 64 times as much,
+// so 15 int8 products have 4 times the rate to spend; splitting and putting
+// together move 23 bytes per operand and per result element, which K N / (K +
+// N) has to pay for (mod_pays).  Measured: 32768 x 8192 x 8192 65.6 ms FP64
+// (67 TFLOP/s), 33 ms by residues; 65536 x 2048 x 2048 8.5 and 6.3 ms; the
+// 2-norm error against extended precision is 1.1e-16 to 2.0e-16 where the
+// FP64 kernel's is 1.4e-15 to 3.0e-15.
+//
+// A common power of two per k may be moved from one operand to the other
+// (A(m, k) d_k, B(n, k) / d_k, exact): with B = (C C^H)^-1 and d_k =
+// sqrt(B(k, k)) (mod_diag) both operands lose the range that the density at
+// the interpolation points gives their columns (six orders of magnitude and
+// more), which a row's scale alone cannot.
+//
+// A row that is not finite, or whose norm is outside 2^+-460, raises a flag;
+// the residue kernels then do nothing and the FP64 kernel launched behind them
+// (GemmShape::only) computes the panel as it always did.
+#pragma once
+
+#include "gemm.h"
+
+namespace isdf {
+namespace {
+
+constexpr int MOD_N = 15;
+constexpr int MOD_BITS = 58;      // a scaled row's 2-norm is at most 2^58
+constexpr int MOD_KMAX = 16384;   // |sum| < K 2^14 <= 2^28, the bound of mod_reduce
+constexpr int MOD_T = 256;        // output tile edge
+constexpr int MOD_BK = 128;       // K bytes per LDS stage
+constexpr int MOD_THREADS = 512;  // 8 wavefronts, 2 (m) x 4 (n), 128 x 64 outputs each
+
+struct ModTab {
+  int p[MOD_N];
+  int c14[MOD_N];    // 2^14 mod p, in (-p/2, p/2]
+  float fip[MOD_N];  // 1 / p
+  double ip[MOD_N];
+  // w = w1 + w2, w1 a multiple of 2^-42: sums of r_i w1_i are exact
+  double w1[MOD_N], w2[MOD_N];
+  double P, Plo;     // product of the moduli, P + Plo to 106 bits
+};
+
+constexpr ModTab make_mod_tab() {
+  ModTab t{};
+  const int p[MOD_N] = {256, 255, 253, 251, 247, 241, 239, 233, 229, 227, 223, 217, 211, 199, 197};
+  unsigned __int128 P = 1;
+  for (int i = 0; i < MOD_N; ++i) P *= (unsigned)p[i];
+  for (int i = 0; i < MOD_N; ++i) {
+    const int m = (int)((P / (unsigned)p[i]) % (unsigned)p[i]);
+    int q = 1;
+    while (q * m % p[i] != 1) ++q;
+    if (2 * q > p[i]) q -= p[i];
+    const long long num = (long long)q * (1ll << 42);
+    t.p[i] = p[i];
+    t.c14[i] = 16384 % p[i] > p[i] / 2 ? 16384 % p[i] - p[i] : 16384 % p[i];
+    t.fip[i] = 1.0f / (float)p[i];
+    t.ip[i] = 1.0 / p[i];
+    t.w1[i] = (double)(num / p[i]) / (double)(1ll << 42);
+    t.w2[i] = ((double)(num % p[i]) / p[i]) / (double)(1ll << 42);
+  }
+  t.P = (double)P;
+  t.Plo = (double)((__int128)P - (__int128)t.P);
+  return t;
+}
+constexpr ModTab MOD_TAB = make_mod_tab();
+static __device__ __constant__ ModTab mod_tab = make_mod_tab();
+
+typedef int i4v __attribute__((ext_vector_type(4)));
+typedef int i16v __attribute__((ext_vector_type(16)));
+
+// A panel is left to the FP64 kernel when either operand raised its flag.
+__device__ __forceinline__ bool mod_off(const int* abort, const int* bflag, const int* aflag) {
+  return (abort && *abort) || *bflag || *aflag;
+}
+
+// ------------------------------------------------------------------ scales
+// d[k] = 2^round(log2 sqrt(B(k, k))) and its reciprocal (1 where the diagonal
+// is not a normal positive number).
+__global__ void mod_diag(const double* __restrict__ B, int64_t ldb, int K, double* __restrict__ d,
+                         double* __restrict__ di) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= K) return;
+  const double v = B[(int64_t)k * ldb + k];
+  int e = 0;
+  if (v > 1e-280 && v < 1e280) {
+    frexp(v, &e);
+    e >>= 1;
+  }
+  d[k] = ldexp(1.0, e);
+  di[k] = ldexp(1.0, -e);
+}
+
+__global__ void mod_clear(int* flags, int n) {
+  for (int i = threadIdx.x; i < n; i += blockDim.x) flags[i] = 0;
+}
+
+// ------------------------------------------------------------------- split
+// Row blockIdx.x of X (K entries, times ks[k] when given): its scale and the
+// residues of its scaled integers, planes [MOD_N][rows][kpad] (zero past K).
+// One workgroup per row, the row held in registers between the norm and the
+// residues (4 IT per thread).  Bound by HBM: 8 bytes read and 15 written per
+// entry; a residue costs 7 FP64 operations.
+// r mod p of an integer |x| < 2^60 held in a double: the quotient's rounding
+// can leave the first remainder one p off, the second step is exact.
+__device__ __forceinline__ unsigned mod_byte(double x, double p, double ip) {
+  const double r = fma(-__builtin_rint(x * ip), p, x);
+  const double y = fma(-__builtin_rint(r * ip), p, r + 6755399441055744.0);  // + 1.5 2^52: integer in the low word
+  return (unsigned)__double2loint(y) & 0xffu;
+}
+
+template <class TS, int IT>
+__global__ __launch_bounds__(256) void mod_split(const TS* __restrict__ X, int64_t ld, int rows, int K, int kpad,
+                                                 const double* __restrict__ ks, int vec, int8_t* __restrict__ out,
+                                                 int64_t pstride, double* __restrict__ rscale, int* flag,
+                                                 const int* abort) {
+  if (abort && *abort) return;
+  __shared__ double red[256 / ISDF_WAVE];
+  const int tid = threadIdx.x;
+  const int64_t row = blockIdx.x;
+  const TS* x = X + row * ld;
+  double v[IT][4];
+  double n2 = 0.0;
+  bool any = false;
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int k = 4 * (tid + 256 * it);
+    if (vec && k + 4 <= K) {
+      load_pair<TS>(x + k, v[it][0], v[it][1]);
+      load_pair<TS>(x + k + 2, v[it][2], v[it][3]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[it][e] = k + e < K ? (double)x[k + e] : 0.0;
+    }
+    if (ks) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[it][e] *= k + e < K ? ks[k + e] : 0.0;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      n2 = fma(v[it][e], v[it][e], n2);
+      any |= v[it][e] != 0.0;  // true for NaN
+    }
+  }
+  n2 = wave_sum(n2);
+  if ((tid & 63) == 0) red[tid >> 6] = n2;
+  const int some = __syncthreads_or(any);
+  n2 = (red[0] + red[1]) + (red[2] + red[3]);
+  int e2 = 0;
+  double up = 0.0, down = 0.0;
+  if (n2 > 1e-280 && n2 < 1e280) {
+    frexp(n2, &e2);  // n2 < 2^e2
+    const int e = MOD_BITS - ((e2 + 1) >> 1);
+    up = ldexp(1.0, e);
+    down = ldexp(1.0, -e);
+  } else if (some) {
+    if (tid == 0) atomicOr(flag, 1);
+  }
+  if (tid == 0) rscale[row] = down;
+  int8_t* o = out + row * kpad;
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int k = 4 * (tid + 256 * it);
+    if (k >= kpad) continue;
+    double s[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[e] = __builtin_rint(v[it][e] * up);
+#pragma unroll
+    for (int i = 0; i < MOD_N; ++i) {
+      unsigned w = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w |= mod_byte(s[e], MOD_TAB.p[i], MOD_TAB.ip[i]) << (8 * e);
+      *reinterpret_cast<unsigned*>(o + i * pstride + k) = w;
+    }
+  }
+}
+
+// -------------------------------------------------------------------- GEMM
+// A word whose low byte is acc mod p in [-p/2, p/2] (the byte wraps for p =
+// 256): 14 low bits and the rest times 2^14 mod p give |t| <= 2^21 + 2^14,
+// whose quotient by p one FP32 multiply-add rounds to the nearest integer
+// (its error, 2^-25 t / p, is below the 1 / (2 p) between t / p and a half
+// integer); the 1.5 2^23 that puts the integer into the low bits is a
+// multiple of 256 and drops out of the byte.
+__device__ __forceinline__ unsigned mod_reduce(int acc, int p, int c14, float fip) {
+  const int t = __mul24(acc >> 14, c14 - 16384) + acc;
+  const int q = __float_as_int(fmaf((float)t, fip, 12582912.0f));
+  return (unsigned)(t - __mul24(q, p));
+}
+// Low bytes of four words.
+__device__ __forceinline__ unsigned mod_pack(unsigned a, unsigned b, unsigned c, unsigned d) {
+  return __builtin_amdgcn_perm(__builtin_amdgcn_perm(d, c, 0x0c0c0400u), __builtin_amdgcn_perm(b, a, 0x0c0c0400u),
+                               0x05040100u);
+}
+
+// Residue planes of A B^T: R [MOD_N][M][ldr] from A [MOD_N][M][ld] and B
+// [MOD_N][N][ld] (ld a multiple of 128 bytes, ldr of 256).  256 x 256 tiles of
+// eight wavefronts (128 x 64 each: 128 accumulator registers), 128-byte K
+// stages in two LDS buffers (128 KB, one workgroup per CU), the next stage
+// but one in flight in registers.  v_mfma_i32_32x32x32_i8 takes B's rows as
+// its row operand, so that a lane's four consecutive accumulators are four
+// consecutive n of one m and leave as one word.  An LDS row is its 8 chunks of
+// 16 bytes at chunk ^ (row / 4 % 8): the 32 lanes of a fragment read (32
+// rows, one chunk) hit 32 different 16-byte slots of the 512-byte bank row.
+__global__ __launch_bounds__(MOD_THREADS, 2) void mod_gemm(const int8_t* __restrict__ A, int64_t astride,
+                                                           const int8_t* __restrict__ B, int64_t bstride, int ld, int M,
+                                                           int N, int8_t* __restrict__ R, int64_t rstride, int ldr,
+                                                           const int* abort, const int* bflag, const int* aflag) {
+  if (mod_off(abort, bflag, aflag)) return;
+  constexpr int STAGE = 2 * MOD_T * MOD_BK;
+  __shared__ __attribute__((aligned(16))) int8_t smem[2 * STAGE];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int wm = wv >> 2, wn = wv & 3;
+  const int tiles_m = (M + MOD_T - 1) / MOD_T, tiles_n = (N + MOD_T - 1) / MOD_T;
+  const int ntiles = tiles_m * tiles_n;
+  const int logical = xcd_remap(blockIdx.x, gridDim.x);
+  const int mod = logical / ntiles, tile = logical % ntiles;
+  // column by column within groups of 4 row blocks: the 32 tiles of an XCD
+  // then need 4 row and 8 column panels of A and B
+  constexpr int GR = 4;
+  const int first = (tile / (GR * tiles_n)) * GR;
+  const int rows_in = tiles_m - first < GR ? tiles_m - first : GR;
+  const int local = tile % (GR * tiles_n);
+  const int m0 = (first + local % rows_in) * MOD_T, n0 = (local / rows_in) * MOD_T;
+  A += mod * astride;
+  B += mod * bstride;
+
+  // staging: chunk `id` of a stage is 16 bytes of row id / 8
+  constexpr int PER = MOD_T * MOD_BK / 16 / MOD_THREADS;
+  int64_t offa[PER], offb[PER];
+  int dst[PER];
+#pragma unroll
+  for (int c = 0; c < PER; ++c) {
+    const int id = tid + c * MOD_THREADS, r = id >> 3, ch = id & 7;
+    const int ra = m0 + r < M ? m0 + r : M - 1, rb = n0 + r < N ? n0 + r : N - 1;  // past the edge: any valid row
+    offa[c] = (int64_t)ra * ld + 16 * ch;
+    offb[c] = (int64_t)rb * ld + 16 * ch;
+    dst[c] = r * MOD_BK + 16 * (ch ^ ((r >> 1) & 7));
+  }
+  i4v sa[PER], sb[PER];
+  auto load_a = [&](int c, int k) { sa[c] = *reinterpret_cast<const i4v*>(A + offa[c] + k); };
+  auto load_b = [&](int c, int k) { sb[c] = *reinterpret_cast<const i4v*>(B + offb[c] + k); };
+  auto store_a = [&](int c, int8_t* buf) { *reinterpret_cast<i4v*>(buf + dst[c]) = sa[c]; };
+  auto store_b = [&](int c, int8_t* buf) { *reinterpret_cast<i4v*>(buf + MOD_T * MOD_BK + dst[c]) = sb[c]; };
+  const int half = lane >> 5, sw = ((lane & 31) >> 1) & 7;
+  const int arow = (wm * 128 + (lane & 31)) * MOD_BK;
+  const int brow = MOD_T * MOD_BK + (wn * 64 + (lane & 31)) * MOD_BK;
+  i4v fa[2][4], fb[2][2];
+  // fragment t of sub-step s (32 of the stage's K bytes): B 0, A 0..3, B 1 in
+  // the order the products want them
+  auto frag = [&](int t, const int8_t* buf, int s, int to) {
+    const int ch = 16 * ((2 * s + half) ^ sw);
+    if (t == 0) fb[to][0] = *reinterpret_cast<const i4v*>(buf + brow + ch);
+    else if (t == 5) fb[to][1] = *reinterpret_cast<const i4v*>(buf + brow + 32 * MOD_BK + ch);
+    else fa[to][t - 1] = *reinterpret_cast<const i4v*>(buf + arow + (t - 1) * 32 * MOD_BK + ch);
+  };
+  i16v acc[2][4];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[j][i] = i16v{0};
+
+  const int klast = ld - MOD_BK;
+  const int k1 = MOD_BK < klast ? MOD_BK : klast;
+#pragma unroll
+  for (int c = 0; c < PER; ++c) {
+    load_a(c, 0);
+    load_b(c, 0);
+  }
+#pragma unroll
+  for (int c = 0; c < PER; ++c) {
+    store_a(c, smem);
+    store_b(c, smem);
+  }
+#pragma unroll
+  for (int c = 0; c < PER; ++c) load_a(c, k1);
+#pragma unroll
+  for (int c = 0; c < PER; ++c) load_b(c, k1);
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < 6; ++t) frag(t, smem, 0, 0);
+  int cur = 0;
+  for (int k = 0; k < ld; k += MOD_BK) {
+    // the last steps load, store and read a stage that nothing uses (the last
+    // one again), which keeps the loop free of branches
+    const int8_t* cbuf = smem + cur * STAGE;
+    int8_t* nbuf = smem + (cur ^ 1) * STAGE;
+    const int k2 = k + 2 * MOD_BK < klast ? k + 2 * MOD_BK : klast;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int now = s & 1;
+      if (s == 3) __syncthreads();  // the next stage is stored by every wave; this buffer's reads are done
+      __builtin_amdgcn_s_setprio(1);
+      // one product, then at most one LDS read, LDS write and load: a wave's
+      // instructions issue in order, and a run of LDS accesses would hold
+      // back the products behind it while the LDS serves the other waves
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int j = t >> 2, i = t & 3;
+        acc[j][i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[now][j], fa[now][i], acc[j][i], 0, 0, 0);
+        if (t < 6) frag(t, s < 3 ? cbuf : nbuf, (s + 1) & 3, now ^ 1);
+        // the next stage goes into the other buffer (its last reads ended
+        // before the previous barrier), A's half under sub-step 0, B's under 1
+        if (t & 1) {
+          if (s == 0) {
+            store_a(t >> 1, nbuf);
+            load_a(t >> 1, k2);
+          }
+          if (s == 1) {
+            store_b(t >> 1, nbuf);
+            load_b(t >> 1, k2);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      __builtin_amdgcn_s_setprio(0);
+    }
+    cur ^= 1;
+  }
+
+  // residues to memory: a wave's 128 x 64 bytes through its own LDS rows (80
+  // bytes apart), 16-byte stores of 64-byte row segments
+  __syncthreads();
+  const int p = mod_tab.p[mod], c14 = mod_tab.c14[mod];
+  const float fip = mod_tab.fip[mod];
+  int8_t* mine = smem + wv * 128 * 80;
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        unsigned w[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = mod_reduce(acc[j][i][4 * q + e], p, c14, fip);
+        *reinterpret_cast<unsigned*>(mine + (i * 32 + (lane & 31)) * 80 + j * 32 + 8 * q + 4 * half) =
+            mod_pack(w[0], w[1], w[2], w[3]);
+      }
+  __builtin_amdgcn_wave_barrier();
+  int8_t* r = R + mod * rstride;
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    const int row = 16 * t + (lane >> 2), m = m0 + wm * 128 + row;
+    const i4v v = *reinterpret_cast<const i4v*>(mine + row * 80 + 16 * (lane & 3));
+    if (m < M) *reinterpret_cast<i4v*>(r + (int64_t)m * ldr + n0 + wn * 64 + 16 * (lane & 3)) = v;
+  }
+}
+
+// --------------------------------------------------------------------- CRT
+// C(m, n .. n + 3) from the residues of one row m, in FP64: f = sum_i r_i w_i
+// modulo 1 is C / P (|C| < P / 3, so the fraction nearest zero), exact in its
+// first part (r_i w1_i are multiples of 2^-42 below 2^10).
+__device__ __forceinline__ void mod_combine(const int8_t* __restrict__ R, int64_t rstride, double scale,
+                                            const double* __restrict__ cs, int n, int N, double (&c)[4]) {
+  int w[MOD_N];
+#pragma unroll
+  for (int i = 0; i < MOD_N; ++i) w[i] = *reinterpret_cast<const int*>(R + i * rstride);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    double h = 0.0, l = 0.0;
+#pragma unroll
+    for (int i = 0; i < MOD_N; ++i) {
+      const double r = (double)(int8_t)(w[i] >> (8 * e));
+      h = fma(r, MOD_TAB.w1[i], h);
+      l = fma(r, MOD_TAB.w2[i], l);
+    }
+    const double f = (h - __builtin_rint(h)) + l;
+    c[e] = fma(f, MOD_TAB.P, f * MOD_TAB.Plo) * scale * cs[n + e < N ? n + e : N - 1];
+  }
+}
+
+// One thread per Epi::REP runs of 4 consecutive outputs of a row; workgroups
+// of 256 threads over the panel's rows x ceil(N / 4).  HBM-bound: 15 residue
+// bytes read per output beside what the epilogue moves.
+template <class Epi>
+__global__ __launch_bounds__(256) void mod_crt(const int8_t* __restrict__ R, int64_t rstride, int ldr, int M, int N,
+                                               const double* __restrict__ rs, const double* __restrict__ cs,
+                                               const int* abort, const int* bflag, const int* aflag, Epi epi) {
+  if (mod_off(abort, bflag, aflag)) {
+    epi.off();
+    return;
+  }
+  const int n4 = (N + 3) / 4;
+  const int64_t total = (int64_t)M * n4;
+  typename Epi::Sum sum{};
+#pragma unroll 1
+  for (int u = 0; u < Epi::REP; ++u) {
+    const int64_t e = ((int64_t)blockIdx.x * Epi::REP + u) * 256 + threadIdx.x;
+    if (e < total) {
+      const int m = (int)(e / n4), n = 4 * (int)(e % n4);
+      double c[4];
+      mod_combine(R + (int64_t)m * ldr + n, rstride, rs[m], cs, n, N, c);
+      epi(m, n, c, sum);
+    }
+  }
+  epi.finish(sum);
+}
+
+// C(m, n) = alpha c
+template <class TC>
+struct ModStore {
+  static constexpr int REP = 1;
+  struct Sum {};
+  TC* C;
+  int64_t ldc;
+  int N;
+  double alpha;
+  int vec;  // pairs of a row aligned
+  __device__ __forceinline__ void operator()(int m, int n, const double (&c)[4], Sum&) const {
+    TC* p = C + (int64_t)m * ldc + n;
+    if (vec && n + 4 <= N) {
+      typedef TC v2 __attribute__((ext_vector_type(2)));
+      reinterpret_cast<v2*>(p)[0] = v2{(TC)(alpha * c[0]), (TC)(alpha * c[1])};
+      reinterpret_cast<v2*>(p)[1] = v2{(TC)(alpha * c[2]), (TC)(alpha * c[3])};
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (n + e < N) p[e] = (TC)(alpha * c[e]);
+    }
+  }
+  __device__ __forceinline__ void off() const {}
+  __device__ __forceinline__ void finish(const Sum&) const {}
+};
+
+// -------------------------------------------------------------------- host
+// Buffers of a product with up to `rows` rows of A per call, processed in
+// panels of `mp` rows (planes of a panel: 15 bytes per entry of A and of C).
+struct ModWork {
+  int8_t *a, *b, *r;
+  double *ra, *rb, *d, *di;
+  int* flags;  // [nflags]: [0] B, [1 + i] panel i
+  int nflags;
+  int64_t mp;  // 0: no buffers
+  int kpad, ldr;
+};
+
+constexpr int64_t MOD_PANEL = 16384;
+
+// Whether residues beat the FP64 kernel: measured per M row and column, the
+// FP64 product takes 2 K N / 66 TFLOP/s and the residues 30 K N / 2.4 POP/s
+// plus 23 (K + N) bytes at 4.4 TB/s; a margin for short panels and tiles that
+// stick out.
+static bool mod_pays(int64_t M, int64_t N, int64_t K) {
+  return M >= 2048 && K <= MOD_KMAX && K * N >= 512 * (K + N);
+}
+
+static ModWork carve_mod(Carver& c, int64_t rows, int64_t N, int64_t K) {
+  ModWork w{};
+  if (!mod_pays(rows, N, K)) return w;
+  w.mp = rows < MOD_PANEL ? rows : MOD_PANEL;
+  w.kpad = (int)ceil_div(K, MOD_BK) * MOD_BK;
+  w.ldr = (int)ceil_div(N, MOD_T) * MOD_T;
+  w.nflags = (int)(1 + ceil_div(rows > N ? rows : N, w.mp));
+  w.flags = c.take<int>(w.nflags);
+  w.d = c.take<double>(K);
+  w.di = c.take<double>(K);
+  w.ra = c.take<double>(w.mp);
+  w.rb = c.take<double>(N);
+  w.b = c.take<int8_t>((size_t)MOD_N * N * w.kpad);
+  w.a = c.take<int8_t>((size_t)MOD_N * w.mp * w.kpad);
+  w.r = c.take<int8_t>((size_t)MOD_N * w.mp * w.ldr);
+  return w;
+}
+
+template <class TS>
+static bool mod_rows(const TS* X, int64_t ld, int rows, int K, int kpad, const double* ks, int8_t* out, double* rscale,
+                     int* flag, const int* abort, hipStream_t s) {
+  const int vec = ld % 2 == 0 && (uintptr_t)X % (2 * sizeof(TS)) == 0;
+  const int64_t ps = (int64_t)rows * kpad;
+  const dim3 grid((unsigned)rows), block(256);
+  if (kpad <= 1024)
+    hipLaunchKernelGGL((mod_split<TS, 1>), grid, block, 0, s, X, ld, rows, K, kpad, ks, vec, out, ps, rscale, flag, abort);
+  else if (kpad <= 2048)
+    hipLaunchKernelGGL((mod_split<TS, 2>), grid, block, 0, s, X, ld, rows, K, kpad, ks, vec, out, ps, rscale, flag, abort);
+  else if (kpad <= 4096)
+    hipLaunchKernelGGL((mod_split<TS, 4>), grid, block, 0, s, X, ld, rows, K, kpad, ks, vec, out, ps, rscale, flag, abort);
+  else if (kpad <= 8192)
+    hipLaunchKernelGGL((mod_split<TS, 8>), grid, block, 0, s, X, ld, rows, K, kpad, ks, vec, out, ps, rscale, flag, abort);
+  else
+    hipLaunchKernelGGL((mod_split<TS, 16>), grid, block, 0, s, X, ld, rows, K, kpad, ks, vec, out, ps, rscale, flag,
+                       abort);
+  return launch_ok();
+}
+
+// Which operand's diagonal (that operand symmetric of order K) gives the
+// powers of two that are moved from it to the other.
+enum { MOD_PLAIN = 0, MOD_DIAG_A = 1, MOD_DIAG_B = 2 };
+
+// Residues of B (N x K), once per call; dmat, ldd: the operand of `bal`.
+static bool mod_prepare(const double* B, int64_t ldb, int N, int K, int bal, const double* dmat, int64_t ldd,
+                        const ModWork& w, const int* abort, hipStream_t s) {
+  hipLaunchKernelGGL(mod_clear, dim3(1), dim3(256), 0, s, w.flags, w.nflags);
+  if (bal != MOD_PLAIN)
+    hipLaunchKernelGGL(mod_diag, dim3((unsigned)ceil_div(K, 256)), dim3(256), 0, s, dmat, ldd, K, w.d, w.di);
+  return mod_rows<double>(B, ldb, N, K, w.kpad, bal == MOD_PLAIN ? nullptr : bal == MOD_DIAG_B ? w.di : w.d, w.b, w.rb,
+                          w.flags, abort, s);
+}
+
+template <class Epi>
+static int64_t mod_crt_blocks(int64_t rows, int64_t N) {
+  return ceil_div(rows * ceil_div(N, 4), 256 * Epi::REP);
+}
+
+// One panel (at most w.mp rows): residues of its rows of A, the residue
+// products, and the results through `epi`.
+template <class TA, class Epi>
+static bool mod_panel(const TA* A, int64_t lda, int rows, int N, int K, int bal, int panel, const ModWork& w,
+                      const Epi& epi, const int* abort, hipStream_t s) {
+  int* aflag = w.flags + 1 + panel;
+  if (!mod_rows<TA>(A, lda, rows, K, w.kpad, bal == MOD_PLAIN ? nullptr : bal == MOD_DIAG_B ? w.d : w.di, w.a, w.ra,
+                    aflag, abort, s))
+    return false;
+  const int64_t tiles = ceil_div(rows, MOD_T) * ceil_div(N, MOD_T);
+  hipLaunchKernelGGL(mod_gemm, dim3((unsigned)(tiles * MOD_N)), dim3(MOD_THREADS), 0, s, (const int8_t*)w.a,
+                     (int64_t)rows * w.kpad, (const int8_t*)w.b, (int64_t)N * w.kpad, w.kpad, rows, N, w.r,
+                     (int64_t)rows * w.ldr, w.ldr, abort, (const int*)w.flags, (const int*)aflag);
+  hipLaunchKernelGGL((mod_crt<Epi>), dim3((unsigned)mod_crt_blocks<Epi>(rows, N)), dim3(256), 0, s,
+                     (const int8_t*)w.r, (int64_t)rows * w.ldr, w.ldr, rows, N, (const double*)w.ra,
+                     (const double*)w.rb, abort, (const int*)w.flags, (const int*)aflag, epi);
+  return launch_ok();
+}
+
+}  // namespace
+}  // namespace isdf

@@ -78,6 +78,8 @@ class ISDFStep:
         self.keep_theta = keep_theta or len(self.blocks) == 1
         self.zc_ws = torch.empty(self.lib.isdf_zc_workspace(n_mu, self.npf, self.nps, int(self.aliased), self.prec,
                                                             self.block_rows), dtype=u8, device=dev)
+        self.mv_ws = torch.empty(self.lib.isdf_apply_minv_workspace(n_mu, int(self.aliased), self.block_rows), dtype=u8,
+                                 device=dev)
         self.G = torch.empty(self.block_rows, self.n1, dtype=f64, device=dev)
         real_t = f64 if self.dt == L.C128 else torch.float32
         cplx_t = torch.complex128 if self.dt == L.C128 else torch.complex64
@@ -175,8 +177,9 @@ class ISDFStep:
             if b == 0:
                 main.wait_event(self.ev_factor)
             th = self.theta.data_ptr() + (r0 * self.n_mu * esz if self.keep_theta else 0)
-            self._call(lib.isdf_apply_minv(self.n_mu, int(self.aliased), self.minv.data_ptr(), self.G.data_ptr(),
-                                           self.n1, nrows, self.dt, th, self.n_mu, s), "isdf_apply_minv")
+            self._call(lib.isdf_apply_minv_ws(self.n_mu, int(self.aliased), self.minv.data_ptr(), self.G.data_ptr(),
+                                              self.n1, nrows, self.dt, th, self.n_mu, self.mv_ws.data_ptr(),
+                                              self.mv_ws.numel(), s), "isdf_apply_minv_ws")
             if be:
                 be[2].record()
             if self.backward and self.save_gram:

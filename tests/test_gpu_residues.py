@@ -1,0 +1,111 @@
+"""FP64 products by int8 residues (isdf_apply_minv_ws) against the FP64 kernel
+(isdf_apply_minv) and extended-precision sums.
+
+Tolerance: the FP64 kernel's K-term sum is within K eps (|G| |W|) of the exact
+one; the residue form rounds the scaled operands, within sqrt(K) 2^-58 of the
+product of the row norms, plus the rounding of the result.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2208_07731_amd import _lib as L
+
+pytestmark = pytest.mark.gpu
+EPS = np.finfo(np.float64).eps
+
+
+def _inputs(rows, n1, seed, spread):
+    rng = np.random.Generator(np.random.PCG64(seed))
+    d = 2.0 ** rng.uniform(-spread, spread, n1)  # density at the interpolation points
+    G = np.abs(rng.standard_normal((rows, n1))) / d
+    W = rng.standard_normal((n1, n1)) / np.sqrt(n1)
+    W = (W + W.T) / 2 + np.diag(rng.uniform(1, 3, n1))
+    return G, (d[:, None] * W) * d[None, :]
+
+
+def _apply(lib, G, W, n_mu, aliased, rows, dt, ld_theta, ws):
+    real = {(L.C128, 1): torch.float64, (L.C64, 1): torch.float32, (L.C128, 0): torch.complex128,
+            (L.C64, 0): torch.complex64}[(dt, aliased)]
+    out = torch.full((rows, ld_theta), 7.0, dtype=real, device="cuda")
+    if ws is None:
+        code = lib.isdf_apply_minv(n_mu, aliased, W.data_ptr(), G.data_ptr(), G.stride(0), rows, dt, out.data_ptr(),
+                                   ld_theta, None)
+    else:
+        code = lib.isdf_apply_minv_ws(n_mu, aliased, W.data_ptr(), G.data_ptr(), G.stride(0), rows, dt, out.data_ptr(),
+                                      ld_theta, ws.data_ptr(), ws.numel(), None)
+    assert code == L.OK
+    torch.cuda.synchronize()
+    return out
+
+
+# n_mu 1024 is the smallest order the residues take; odd ones leave ragged K,
+# N and row tiles; 16384 rows are one panel
+@pytest.mark.parametrize("n_mu,aliased,rows,dt,pad,ldpad", [
+    (1024, 1, 2048, L.C128, 0, 0),
+    (1025, 1, 2049, L.C128, 1, 3),
+    (1290, 1, 16384 + 257, L.C64, 0, 1),
+    (600, 0, 2305, L.C128, 2, 0),
+    (601, 0, 2048, L.C64, 0, 5),
+    (2177, 1, 2100, L.C128, 0, 0),
+])
+def test_residue_product(n_mu, aliased, rows, dt, pad, ldpad):
+    lib = L.load()
+    n1 = n_mu if aliased else 2 * n_mu
+    Gh, Wh = _inputs(rows, n1, 11 * n_mu + rows, 12.0)
+    G = torch.zeros(rows, n1 + pad, dtype=torch.float64, device="cuda")
+    G[:, :n1] = torch.from_numpy(Gh).cuda()
+    W = torch.from_numpy(np.ascontiguousarray(Wh)).cuda()
+    size = lib.isdf_apply_minv_workspace(n_mu, aliased, rows)
+    assert size > 0
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    got = _apply(lib, G, W, n_mu, aliased, rows, dt, n_mu + ldpad, ws)
+    ref = _apply(lib, G, W, n_mu, aliased, rows, dt, n_mu + ldpad, None)
+    assert torch.equal(got[:, n_mu:], ref[:, n_mu:])  # nothing written past a row
+    sel = np.unique(np.concatenate([np.arange(0, rows, max(1, rows // 24)), [rows - 1]]))
+    col = np.unique(np.concatenate([np.arange(0, n1, max(1, n1 // 50)), [n1 - 2, n1 - 1]]))
+    exact = Gh[sel].astype(np.longdouble) @ Wh[col].astype(np.longdouble).T
+    terms = np.abs(Gh[sel]) @ np.abs(Wh[col]).T
+    g = got[:, :n_mu].contiguous()
+    g = (torch.view_as_real(g).reshape(rows, n1) if not aliased else g).cpu().numpy()[sel][:, col]
+    store = np.finfo(np.float64 if dt == L.C128 else np.float32).eps * np.abs(exact.astype(np.float64))
+    bound = n1 * EPS * terms + 2 * EPS * np.abs(exact.astype(np.float64)) + store
+    assert np.all(np.abs((g - exact).astype(np.float64)) <= bound)
+    if dt == L.C128:  # and no further off than the FP64 kernel overall
+        f = ref[:, :n_mu].contiguous()
+        f = (torch.view_as_real(f).reshape(rows, n1) if not aliased else f).cpu().numpy()[sel][:, col]
+        assert np.linalg.norm((g - exact).astype(np.float64)) <= np.linalg.norm((f - exact).astype(np.float64))
+
+
+@pytest.mark.parametrize("what", ["nan", "inf", "huge", "tiny"])
+def test_rows_out_of_range_take_the_fp64_kernel(what):
+    """A row that is not finite or whose squared norm leaves the FP64 range
+    sends its panel to the FP64 kernel: the results are its bits."""
+    lib = L.load()
+    n_mu, rows = 1100, 2304
+    Gh, Wh = _inputs(rows, n_mu, 5, 3.0)
+    Gh[77, 13] = {"nan": np.nan, "inf": np.inf, "huge": 1e200, "tiny": 1.0}[what]
+    if what == "tiny":
+        Gh[77] = 1e-200
+    G, W = torch.from_numpy(Gh).cuda(), torch.from_numpy(np.ascontiguousarray(Wh)).cuda()
+    ws = torch.empty(lib.isdf_apply_minv_workspace(n_mu, 1, rows), dtype=torch.uint8, device="cuda")
+    got = _apply(lib, G, W, n_mu, 1, rows, L.C128, n_mu, ws)
+    ref = _apply(lib, G, W, n_mu, 1, rows, L.C128, n_mu, None)
+    assert torch.equal(got.view(torch.int64), ref.view(torch.int64))
+
+
+def test_zero_rows_and_workspace_limits():
+    lib = L.load()
+    n_mu, rows = 1100, 2304
+    Gh, Wh = _inputs(rows, n_mu, 6, 3.0)
+    Gh[5] = 0.0
+    Gh[rows - 1] = 0.0
+    G, W = torch.from_numpy(Gh).cuda(), torch.from_numpy(np.ascontiguousarray(Wh)).cuda()
+    size = lib.isdf_apply_minv_workspace(n_mu, 1, rows)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    got = _apply(lib, G, W, n_mu, 1, rows, L.C128, n_mu, ws)
+    assert not got[5].any() and not got[rows - 1].any() and bool(torch.isfinite(got).all())
+    out = torch.empty(rows, n_mu, dtype=torch.float64, device="cuda")
+    assert lib.isdf_apply_minv_ws(n_mu, 1, W.data_ptr(), G.data_ptr(), n_mu, rows, L.C128, out.data_ptr(), n_mu,
+                                  ws.data_ptr(), size - 1, None) == L.E_WORKSPACE
+    assert lib.isdf_apply_minv_workspace(n_mu, 1, 2047) == 0  # too few rows: the FP64 kernel, no workspace

@@ -307,17 +307,6 @@ __global__ void absmax_real2(const double* __restrict__ x, int64_t ld, int n, in
   }
 }
 
-// Upper triangle of an n x n matrix from its lower triangle.
-__global__ void mirror_lower(double* __restrict__ H, int n, const int* abort) {
-  if (*abort) return;
-  const int64_t total = (int64_t)n * n;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int i = (int)(e / n), j = (int)(e % n);
-    if (j > i) H[e] = H[(int64_t)j * n + i];
-  }
-}
-
 // loss += sum of the per-tile partials, in a fixed order (one workgroup of
 // 256 threads, four independent loads in flight per thread).
 constexpr int LOSS_THREADS = 256;
@@ -450,40 +439,47 @@ static int device_slots() {
   return 2 * cu;
 }
 
-// Split-K factor of a 128 x 128-tiled product with `tiles` output tiles of
-// mn elements in total and K-deep sums: 1 or a multiple of 8 (one K slice per
-// XCD at a time), slices of at least 512 rows, chosen to minimise
-// the modelled time ceil(tiles s / slots) (K / s) t_row + s mn 16 B / bw,
-// i.e. whole waves of workgroups against the partial sums' write and read.
-static int splits_for(int64_t tiles, int64_t K, int64_t mn, int slots) {
-  const double t_row = 2.0 * 128 * 128 / (60e12 / slots);  // s per k-row and tile
-  const double bw = 4e12;                                   // B/s for the partials
-  int best = 1;
+// Tile and split-K factor of an M x N product of K-deep sums (its lower tiles
+// only when `lower`): 1 or a multiple of 8 (one K slice per XCD at a time),
+// slices of at least 4 tile edges of rows, chosen to minimise the modelled time
+// ceil(tiles s / CUs) (K / s) t_row + s M N 16 B / bw, i.e. whole rounds of
+// workgroups against the partial sums' write and read.  A round of one
+// workgroup per CU runs at about the rate of two (the matrix cores bound
+// both), hence CUs and not resident workgroups.  Small outputs get 64-tiles:
+// 256 x 256 lower tiles over 13824 rows 96 us on 128-tiles, 39 on these; 512 x
+// 64 over 13824 rows 98 and 29.
+static TilePlan splits_for(int64_t M, int64_t N, int lower, int64_t K, int slots) {
+  const int64_t cus = slots / 2 > 0 ? slots / 2 : 1;
+  const double bw = 4e12;  // B/s for the partials
+  TilePlan best{128, 1};
   double best_t = 0.0;
-  for (int s = 1; s <= MAX_SPLITS; s = s < 8 ? 8 : s + 8) {
-    if (s > 1 && ceil_div(K, s) < 512) break;
-    const double waves = (double)ceil_div(tiles * s, (int64_t)slots);
-    const double t = waves * ((double)K / s) * t_row + (s > 1 ? s * (double)mn * 16.0 / bw : 0.0);
-    if (s == 1 || t < best_t * (1.0 - 1e-9)) {
-      best = s;
-      best_t = t;
+  for (int tile = 128; tile >= 64; tile /= 2) {
+    const int64_t tiles = gemm_tiles((int)ceil_div(M, tile), (int)ceil_div(N, tile), lower);
+    const double t_row = 2.0 * tile * tile / (60e12 / (double)cus);  // s per k-row and tile
+    for (int s = 1; s <= MAX_SPLITS; s = s < 8 ? 8 : s + 8) {
+      if (s > 1 && ceil_div(K, s) < 4 * tile) break;
+      const double rounds = (double)ceil_div(tiles * s, cus);
+      double t = rounds * ((double)K / s) * t_row + (s > 1 ? s * (double)M * (double)N * 16.0 / bw : 0.0);
+      if (tile == 64) t *= 1.05;  // twice the operand traffic
+      if ((tile == 128 && s == 1) || t < best_t * (1.0 - 1e-9)) {
+        best = TilePlan{tile, s};
+        best_t = t;
+      }
     }
   }
   return best;
 }
 
-// Split factors the adjoint uses for blocks of `rows` rows.
+// Plans the adjoint uses for blocks of `rows` rows.
 struct BwdSplits {
-  int h;  // Theta^T S (general) or H = G^T g G (fused, lower tiles)
-  int q;  // Abar^T X per orbital set
+  TilePlan h;  // Theta^T S (general) or H = G^T g G (fused, lower tiles)
+  TilePlan q;  // Abar^T X per orbital set
 };
 
 static BwdSplits bwd_splits(int64_t rows, int64_t n1, int n_mu, int n, bool fused, int slots) {
-  const int64_t t1 = ceil_div(n1, 128);
   BwdSplits b;
-  b.h = splits_for(fused ? gemm_tiles((int)t1, (int)t1, 1) : t1 * t1, rows, n1 * n1, slots);
-  b.q = splits_for(ceil_div(2 * (int64_t)n_mu, 128) * ceil_div(2 * (int64_t)n, 128), rows,
-                   2 * (int64_t)n_mu * 2 * n, slots);
+  b.h = splits_for(n1, n1, fused ? 1 : 0, rows, slots);
+  b.q = splits_for(2 * (int64_t)n_mu, 2 * (int64_t)n, 0, rows, slots);
   return b;
 }
 
@@ -543,9 +539,9 @@ static BwdPlan plan_bwd(void* ws, size_t cap, int64_t nr, int n_mu, int n_phi, i
       const int64_t n1b = aliased ? n_mu : 2 * (int64_t)n_mu;
       const BwdSplits b1 = bwd_splits(rows, n1b, n_mu, n_phi, fused, slots);
       const BwdSplits b2 = bwd_splits(rows, n1b, n_mu, n_psi, fused, slots);
-      sh = b1.h > sh ? b1.h : sh;
-      sq = b1.q > sq ? b1.q : sq;
-      sq = b2.q > sq ? b2.q : sq;
+      sh = b1.h.splits > sh ? b1.h.splits : sh;
+      sq = b1.q.splits > sq ? b1.q.splits : sq;
+      sq = b2.q.splits > sq ? b2.q.splits : sq;
     }
   Carver c(ws, cap);
   BwdPlan P{};
@@ -583,7 +579,7 @@ static BwdPlan plan_bwd(void* ws, size_t cap, int64_t nr, int n_mu, int n_phi, i
   if (!aliased) P.dB = c.take<double>((size_t)n_mu * 2 * n_mu);
   P.T1 = c.take<double>((size_t)n_mu * 2 * nmax);
   P.mod = carve_mod(c, rblock, n1, n1);
-  size_t lp = (size_t)ceil_div(rblock, 128) * ceil_div(n1, 128);
+  size_t lp = (size_t)ceil_div(rblock, 32) * ceil_div(n1, 32);  // at the smallest tile
   if (P.mod.mp) lp += (size_t)ceil_div(rblock, P.mod.mp) * (mod_crt_blocks<ModSAdj>(P.mod.mp, n1) + ceil_div(n1, 128));
   P.lpart = c.take<double>(lp);
   P.sw = carve_split(c, prec, n_phi, n_psi, aliased, n_mu, rblock > n_mu ? rblock : n_mu);
@@ -728,7 +724,7 @@ static bool adj_rows(int rows, const double* Abar, int n_mu, const typename Prec
 template <int PREC, class TS>
 static bool orbital_block(const double* Abar, int n_mu, const typename Prec<PREC>::E* F, const void* fplanes,
                           const TS* X, int64_t ld_x, int n, TS* dX, int64_t ld_dx, int64_t r, int rows, double* Q,
-                          double* Qpart, const double* scales, const double* scales_t, const AdjPlanes& ap, int sp,
+                          double* Qpart, const double* scales, const double* scales_t, const AdjPlanes& ap, TilePlan sp,
                           bool first, void* tp, double* tpart, int slots, const int* ab, hipStream_t s) {
   const int64_t two_mu = 2 * (int64_t)n_mu;
   constexpr int SPLIT = Prec<PREC>::SPLIT;
@@ -755,7 +751,8 @@ static bool orbital_block(const double* Abar, int n_mu, const typename Prec<PREC
     if (!tgemm<typename Prec<PREC>::Q, XC, XC>((int)two_mu, 2 * n, rows, Abar, two_mu, X + 2 * r * ld_x, 2 * ld_x,
                                                Qpart, 2 * (int64_t)n, 1.0, 0.0, ab, s, sp, qn))
       return false;
-    hipLaunchKernelGGL(reduce_splits, dim3(blocks_for(qn)), dim3(256), 0, s, Q, Qpart, qn, sp, first ? 0 : 1, ab);
+    hipLaunchKernelGGL(reduce_splits, dim3(blocks_for(qn)), dim3(256), 0, s, Q, Qpart, qn, sp.splits,
+                       first ? 0 : 1, ab);
     return launch_ok();
   }
 }
@@ -878,11 +875,11 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
                                       P.slots, ab, s))
           return ISDF_E_HIP;
       } else {
-        const int sp = sp_phi.h;
+        const TilePlan sp = sp_phi.h;
         const int64_t pn = (int64_t)n1 * n1;
         if (!tgemm<double, XC, XC>(n1, n1, rows, Gb, n1, Gb, n1, P.Ppart, n1, 1.0, 0.0, ab, s, sp, pn, g + r, 1))
           return ISDF_E_HIP;
-        hipLaunchKernelGGL(reduce_splits, dim3(blocks_for(pn)), dim3(256), 0, s, P.P, P.Ppart, pn, sp,
+        hipLaunchKernelGGL(reduce_splits, dim3(blocks_for(pn)), dim3(256), 0, s, P.P, P.Ppart, pn, sp.splits,
                            first ? 0 : 1, ab);
       }
       // S = 2 g . (G (C C^H)^-2): Abar / Bbar in place, the loss and (binary16
@@ -915,10 +912,9 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
             return ISDF_E_HIP;
         }
       } else {
-        if (!launch_gemm<double, 128, 128, 16, 2, 2, double, KC, double, KC, 1>(rows, n1, n1, a, b, a, b, 0, epi, 0, ab,
-                                                                               s))
-          return ISDF_E_HIP;
-        ltiles = ceil_div(rows, 128) * ceil_div(n1, 128);
+        const int tile = tile_for(rows, n1, 0);
+        if (!launch_tiled<double, double, KC, double, KC>(tile, rows, n1, n1, a, b, epi, 0, ab, s)) return ISDF_E_HIP;
+        ltiles = ceil_div(rows, tile) * ceil_div(n1, tile);
       }
       hipLaunchKernelGGL(add_loss, dim3(1), dim3(LOSS_THREADS), 0, s, P.st, (const double*)P.lpart, (int)ltiles);
       if (!launch_ok()) return ISDF_E_HIP;
@@ -930,11 +926,11 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
       if (!nt_product<double, TT>(rows, n1, n1, tbar + (r - gbase) * ldt, ldt, minv, n1, MOD_DIAG_B, Gb, n1, 1.0, P.mod,
                                   mod_pays(rows, n1, n1), ab, s))
         return ISDF_E_HIP;
-      const int sp = sp_phi.h;
+      const TilePlan sp = sp_phi.h;
       const int64_t pn = (int64_t)n1 * n1;
       if (!tgemm<double, XC, XC>(n1, n1, rows, P.Th, n1, Gb, n1, P.Ppart, n1, 1.0, 0.0, ab, s, sp, pn))
         return ISDF_E_HIP;
-      hipLaunchKernelGGL(reduce_splits, dim3(blocks_for(pn)), dim3(256), 0, s, P.P, P.Ppart, pn, sp, first ? 0 : 1,
+      hipLaunchKernelGGL(reduce_splits, dim3(blocks_for(pn)), dim3(256), 0, s, P.P, P.Ppart, pn, sp.splits, first ? 0 : 1,
                          ab);
       hipLaunchKernelGGL(adj_hadamard, dim3(blocks_for((int64_t)rows * n_mu)), dim3(256), 0, s, (const double*)Gb,
                          Ab, Bb, (int64_t)rows, n_mu, aliased ? 1 : 0);
@@ -962,8 +958,7 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
   if (!(phases & BWD_END)) return ISDF_OK;
   if (!tbar) {
     // Theta^T S = 2 M^-1 H M^-2 with H = G^T diag(g) G
-    const int64_t pn = (int64_t)n1 * n1;
-    hipLaunchKernelGGL(mirror_lower, dim3(blocks_for(pn)), dim3(256), 0, s, P.P, n1, ab);
+    if (!mirror(P.P, n1, ab, s)) return ISDF_E_HIP;
     // (all symmetric: (C C^H)^-2 H = (H (C C^H)^-2)^T is the second product's K-contiguous operand)
     if (!nt_product<double>(n1, n1, n1, P.W2, n1, P.P, n1, MOD_DIAG_B, P.Ppart, n1, 1.0, P.mod, false, ab, s))
       return ISDF_E_HIP;

@@ -137,73 +137,199 @@ struct EpiGram {
 
 // ------------------------------------------------------------ Cholesky
 // Factors the kb x kb diagonal block at (k0, k0) of X in place (lower) and
-// writes its inverse into the same block of Y.  The inverse is reduced
-// alongside the elimination (L X = I solved row by row: at step j,
-// X_j = R_j / l_jj and R_i -= l_ij X_j for i > j).  Step j updates with the
-// unscaled column j and 1 / pivot; column j (and row j of R) are scaled at
-// the start of step j + 1, when nothing reads them any more, so each step
-// needs a single barrier.  Threads form a 16 x 16 grid over (row, column).
+// writes its inverse (lower) into the same block of Y.
+//
+// A serial chain of 64 pivots, so what counts is the latency of a step: the
+// block is taken in four 64 x 16 panels, each factored by one wavefront with a
+// row per lane in registers (row j of the panel reaches the other lanes
+// through v_readlane, no barrier and no LDS in a step), and the columns to the
+// right are updated on the FP64 matrix cores.  The inverse follows from the
+// four 16 x 16 diagonal inverses (a column per lane) by doubling.  Blocks
+// smaller than 64 are continued by the unit matrix.  80 us a block with one
+// workgroup-wide barrier per pivot, 19 us this way (a panel 2.6, the loads 2.7).
+__device__ __forceinline__ double read_lane(double v, int lane) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
+  return __hiloint2double(hi, lo);
+}
+
+constexpr int POTRF_LD = NB + 1;
+
+// acc (16 x 16) += s A B with A(m, k) at pa[m POTRF_LD + k] and B(k, n) at
+// pb[k POTRF_LD + n] (TB: pb[n POTRF_LD + k]), K a multiple of 4.
+template <bool TB>
+__device__ __forceinline__ void potrf_mma(const double* pa, const double* pb, int K, double s, int lane, d4v& acc) {
+  const int x = lane & 15, q = lane >> 4;
+#pragma unroll 4
+  for (int kk = 0; kk < K; kk += 4) {
+    const int k = kk + q;
+    MfmaT<double>::mma(s * pa[x * POTRF_LD + k], TB ? pb[x * POTRF_LD + k] : pb[k * POTRF_LD + x], acc);
+  }
+}
+__device__ __forceinline__ void potrf_put(double* p, int lane, const d4v& acc) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) p[((lane >> 4) + 4 * r) * POTRF_LD + (lane & 15)] = acc[r];
+}
+
+// Folds the first n pivots of a block into the smallest and largest (one wave).
+__device__ __forceinline__ void potrf_extremes(const double* pivots, int n, int lane, FitState* st) {
+  double lo = lane < n ? pivots[lane] : INFINITY, hi = lane < n ? pivots[lane] : 0.0;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    lo = fmin(lo, __shfl_xor(lo, o, ISDF_WAVE));
+    hi = fmax(hi, __shfl_xor(hi, o, ISDF_WAVE));
+  }
+  if (lane == 0 && n > 0) {
+    atomic_min_pos(&st->pmin, lo);
+    atomic_max_pos(&st->pmax, hi);
+  }
+}
+
 __global__ __launch_bounds__(256) void potrf_diag(double* __restrict__ X, int64_t ldx, int k0, int kb,
                                                   double* __restrict__ Y, int64_t ldy, FitState* st) {
-  if (st->abort) return;
-  __shared__ double a[NB][NB + 1];
-  __shared__ double r[NB][NB + 1];
-  const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-  for (int i = ty; i < kb; i += 16)
-    for (int j = tx; j < kb; j += 16) {
-      a[i][j] = j <= i ? X[(int64_t)(k0 + i) * ldx + k0 + j] : 0.0;
-      r[i][j] = i == j ? 1.0 : 0.0;
+  __shared__ double a[NB * POTRF_LD];
+  __shared__ double x[NB * POTRF_LD];
+  __shared__ double inv[NB], pivots[NB];  // 1 / l_jj, l_jj^2
+  __shared__ int bad;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int abort = st->abort;
+  if (tid == 0) bad = -1;
+  {  // all loads in flight before the first LDS write
+    double v[16];
+    const int j = lane, jc = j < kb ? j : kb - 1;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int i = wv + 4 * e;
+      v[e] = X[(int64_t)(k0 + (i < kb ? i : kb - 1)) * ldx + k0 + jc];
     }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int i = wv + 4 * e;
+      x[i * POTRF_LD + j] = 0.0;
+      if (j > i) continue;
+      const double w = i < kb ? v[e] : (i == j ? 1.0 : 0.0);
+      a[i * POTRF_LD + j] = w;
+      a[j * POTRF_LD + i] = w;
+    }
+  }
+  if (abort) return;  // (uniform)
   __syncthreads();
-  int failed = -1;
-  double il_prev = 0.0;
-  for (int j = 0; j < kb; ++j) {
-    const double piv = a[j][j];
-    if (!(piv > 0.0) || !(piv < INFINITY)) {
-      failed = j;
-      break;
-    }
-    if (j > 0) {  // scale column j - 1 of L and row j - 1 of the inverse
-      const int p = j - 1;
-      if (tid < kb) {
-        if (tid > p) a[tid][p] *= il_prev;
-        else r[p][tid] *= il_prev;
+  for (int p = 0; p < NB / 16; ++p) {
+    if (wv == 0) {
+      const int c0 = 16 * p;
+      double v[16];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) v[c] = lane >= c0 ? a[lane * POTRF_LD + c0 + c] : 0.0;
+      // columns stay unscaled and each lane keeps its own row's pivot, so that
+      // the chain from pivot to pivot is one reciprocal (the hardware's estimate
+      // and two Newton steps, to the last bit or two) and two operations; the
+      // panel's square roots are then taken together, a lane each
+      double pv = 1.0;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const double piv = read_lane(v[j], c0 + j);
+        double y = __builtin_amdgcn_rcp(piv);
+        // the pivot row, read while the reciprocal is on its way
+        double row[16];
+#pragma unroll
+        for (int c = j + 1; c < 16; ++c) row[c] = read_lane(v[c], c0 + j);
+        pv = lane == c0 + j ? piv : pv;
+        __builtin_amdgcn_sched_barrier(0);
+        y = fma(y, fma(-piv, y, 1.0), y);
+        y = fma(y, fma(-piv, y, 1.0), y);
+        const double u = v[j] * y;
+#pragma unroll
+        for (int c = j + 1; c < 16; ++c) v[c] = fma(-u, row[c], v[c]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      const unsigned long long wrong = __ballot(!(pv > 0.0) || !(pv < INFINITY));
+      const double l = sqrt(pv), il = 1.0 / l;
+#pragma unroll
+      for (int c = 0; c < 16; ++c) v[c] = lane == c0 + c ? l : v[c] * read_lane(il, c0 + c);
+      if (lane >= c0 && lane < c0 + 16) {
+        inv[lane] = il;
+        pivots[lane] = pv;
+      }
+      if (lane == 0 && wrong) bad = __ffsll((long long)wrong) - 1;
+      if (lane >= c0) {
+#pragma unroll
+        for (int c = 0; c < 16; ++c) a[lane * POTRF_LD + c0 + c] = lane >= c0 + c ? v[c] : 0.0;
       }
     }
-    const double l = sqrt(piv), ip = 1.0 / piv;
-    if (tid == 0) {
-      atomic_min_pos(&st->pmin, piv);
-      atomic_max_pos(&st->pmax, piv);
-    }
-    for (int i = j + 1 + ty; i < kb; i += 16) {
-      const double aij = a[i][j] * ip;
-      for (int c = j + 1 + tx; c <= i; c += 16) a[i][c] -= aij * a[c][j];
-      for (int c = tx; c <= j; c += 16) r[i][c] -= aij * r[j][c];
-    }
     __syncthreads();
-    if (tid == 0) a[j][j] = l;  // read again only by the scaling of step j + 1
-    il_prev = 1.0 / l;
-  }
-  if (failed >= 0) {
-    if (tid == 0) {
-      atomicMin(&st->pivot, k0 + failed);
-      atomicOr(&st->abort, 1);
+    if (bad >= 0) {
+      if (wv == 0) potrf_extremes(pivots, bad, lane, st);
+      if (tid == 0) {
+        atomicMin(&st->pivot, k0 + bad);
+        atomicOr(&st->abort, 1);
+      }
+      return;
     }
-    return;
+    // tiles (ti, tj) right of the panel, p < tj <= ti
+    int n = 0;
+    for (int tj = p + 1; tj < NB / 16; ++tj)
+      for (int ti = tj; ti < NB / 16; ++ti, ++n) {
+        if ((n & 3) != wv) continue;
+        double* c = a + 16 * ti * POTRF_LD + 16 * tj;
+        d4v acc;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[r] = c[((lane >> 4) + 4 * r) * POTRF_LD + (lane & 15)];
+        potrf_mma<true>(a + 16 * ti * POTRF_LD + 16 * p, a + 16 * tj * POTRF_LD + 16 * p, 16, -1.0, lane, acc);
+        potrf_put(c, lane, acc);
+      }
+    __syncthreads();
   }
-  {  // scale the last column / row
-    const int p = kb - 1;
-    if (tid < kb) {
-      if (tid > p) a[tid][p] *= il_prev;
-      else r[p][tid] *= il_prev;
+  if (wv == 1) potrf_extremes(pivots, kb, lane, st);
+  // 16 x 16 diagonal inverses: lane (block q, column c) solves L_q y = e_c
+  if (wv == 0) {
+    const int q = 16 * (lane >> 4), c = lane & 15;
+    double y[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) y[i] = i == c ? 1.0 : 0.0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      y[k] *= inv[q + k];
+#pragma unroll
+      for (int i = k + 1; i < 16; ++i) y[i] = fma(-a[(q + i) * POTRF_LD + q + k], y[k], y[i]);
     }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x[(q + i) * POTRF_LD + q + c] = y[i];
   }
   __syncthreads();
-  for (int i = ty; i < kb; i += 16)
-    for (int j = tx; j < kb; j += 16) {
-      if (j <= i) X[(int64_t)(k0 + i) * ldx + k0 + j] = a[i][j];
-      Y[(int64_t)(k0 + i) * ldy + k0 + j] = j <= i ? r[i][j] : 0.0;
-    }
+  // doubling: the lower-left block of an inverse pair is -C^-1 (L21 A^-1); the
+  // products L21 A^-1 go through the unused upper part of `a`
+  d4v acc;
+  if (wv < 2) {
+    const int o = 32 * wv;
+    acc = d4v{0, 0, 0, 0};
+    potrf_mma<false>(a + (o + 16) * POTRF_LD + o, x + o * POTRF_LD + o, 16, 1.0, lane, acc);
+    potrf_put(a + o * POTRF_LD + o + 16, lane, acc);
+  }
+  __syncthreads();
+  if (wv < 2) {
+    const int o = 32 * wv;
+    acc = d4v{0, 0, 0, 0};
+    potrf_mma<false>(x + (o + 16) * POTRF_LD + o + 16, a + o * POTRF_LD + o + 16, 16, -1.0, lane, acc);
+    potrf_put(x + (o + 16) * POTRF_LD + o, lane, acc);
+  }
+  __syncthreads();
+  const int tr = 16 * (wv >> 1), tc = 16 * (wv & 1);
+  acc = d4v{0, 0, 0, 0};
+  potrf_mma<false>(a + (32 + tr) * POTRF_LD, x + tc, 32, 1.0, lane, acc);
+  potrf_put(a + tr * POTRF_LD + 32 + tc, lane, acc);
+  __syncthreads();
+  acc = d4v{0, 0, 0, 0};
+  potrf_mma<false>(x + (32 + tr) * POTRF_LD + 32, a + 32 + tc, 32, -1.0, lane, acc);
+  potrf_put(x + (32 + tr) * POTRF_LD + tc, lane, acc);
+  __syncthreads();
+  // (Y's upper triangle is zero already)
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int i = wv + 4 * e, j = lane;
+    if (i >= kb || j > i) continue;
+    X[(int64_t)(k0 + i) * ldx + k0 + j] = a[i * POTRF_LD + j];
+    Y[(int64_t)(k0 + i) * ldy + k0 + j] = x[i * POTRF_LD + j];
+  }
 }
 
 __global__ void fit_finish(const FitState* st, isdf_fit_info* info, double* loss_out, int backward) {
@@ -227,7 +353,7 @@ template <class T, int BM, int BN, int BK, int WM, int WN, class TA, int LA, cla
 static bool launch_gemm(int M, int N, int64_t K, Operand<TA> A0, Operand<TB> B0, Operand<TA> A1,
                         Operand<TB> B1, int64_t K1, const Epi& epi, int lower_only, const int* abort,
                         hipStream_t st, int splits = 1, int batch = 1, int64_t sa = 0, int64_t sb = 0,
-                        const int* only = nullptr, const int* only2 = nullptr) {
+                        const int* only = nullptr, const int* only2 = nullptr, int tri = TRI_NONE) {
   if (M <= 0 || N <= 0) return true;
   GemmShape sh;
   sh.M = M;
@@ -241,6 +367,7 @@ static bool launch_gemm(int M, int N, int64_t K, Operand<TA> A0, Operand<TB> B0,
   sh.only2 = only2;
   sh.sa = sa;
   sh.sb = sb;
+  sh.tri = splits > 1 ? TRI_NONE : tri;
   const int64_t tiles = gemm_tiles((int)ceil_div(M, BM), (int)ceil_div(N, BN), sh.lower_only);
   dim3 grid((unsigned)(tiles * splits), (unsigned)batch, 1);
   hipLaunchKernelGGL((gemm_kernel<T, BM, BN, BK, WM, WN, TA, LA, TB, LB, NOPS, Epi, FOLD>), grid,
@@ -248,16 +375,45 @@ static bool launch_gemm(int M, int N, int64_t K, Operand<TA> A0, Operand<TB> B0,
   return launch_ok();
 }
 
+// Edge of the square output tiles of an M x N product (times `batch`, its lower
+// tiles only when `lower`).  A 128 x 128 tile moves the least data per
+// operation but takes 6.8 us per 64 of K on its CU's FP64 matrix cores, so a
+// product of few tiles leaves the chip idle and its latency is a tile's: 64
+// (four times the tiles) below two 128-tiles per CU, 32 below one 64-tile per
+// CU.  256 x 256 x 256 takes 44 us on 128-tiles and 8 on 32-tiles, 13824 x 64
+// x 512 116 and 29, 256 x 64 x 512 113 and 13, 13824 x 256 x 256 (216 tiles of
+// 128) 51 and, on 64-tiles, 47.
+static int tile_for(int64_t M, int64_t N, int lower, int64_t batch = 1) {
+  const auto tiles = [&](int t) { return batch * gemm_tiles((int)ceil_div(M, t), (int)ceil_div(N, t), lower); };
+  return tiles(128) >= 512 ? 128 : tiles(64) >= 256 ? 64 : 32;
+}
+
+// A product with one operand pair on the tiles of edge `tile`.
+template <class T, class TA, int LA, class TB, int LB, class Epi>
+static bool launch_tiled(int tile, int M, int N, int64_t K, Operand<TA> a, Operand<TB> b, const Epi& epi,
+                         int lower_only, const int* abort, hipStream_t st, int splits = 1, int batch = 1,
+                         int64_t sa = 0, int64_t sb = 0, const int* only = nullptr, const int* only2 = nullptr,
+                         int tri = TRI_NONE) {
+  if (tile == 128)
+    return launch_gemm<T, 128, 128, 16, 2, 2, TA, LA, TB, LB, 1>(M, N, K, a, b, a, b, 0, epi, lower_only, abort, st,
+                                                                splits, batch, sa, sb, only, only2, tri);
+  if (tile == 64)
+    return launch_gemm<T, 64, 64, 16, 2, 2, TA, LA, TB, LB, 1>(M, N, K, a, b, a, b, 0, epi, lower_only, abort, st,
+                                                              splits, batch, sa, sb, only, only2, tri);
+  return launch_gemm<T, 32, 32, 32, 2, 2, TA, LA, TB, LB, 1>(M, N, K, a, b, a, b, 0, epi, lower_only, abort, st, splits,
+                                                            batch, sa, sb, only, only2, tri);
+}
+
 // Plain FP64 GEMM C = alpha op(A) op(B) + beta C.
 template <int LA, int LB, class TC, class TA = double>
 static bool dgemm(int M, int N, int64_t K, const TA* A, int64_t lda, const double* B, int64_t ldb, TC* C,
                   int64_t ldc, double alpha, double beta, int lower_only, const int* abort, hipStream_t st,
-                  const int* only = nullptr, const int* only2 = nullptr) {
+                  const int* only = nullptr, const int* only2 = nullptr, int tri = TRI_NONE) {
   EpiStore<TC> epi{C, ldc, M, N, alpha, beta, nullptr, 0, 0};
-  Operand<TA> a{A, lda, nullptr};
-  Operand<double> b{B, ldb, nullptr};
-  return launch_gemm<double, 128, 128, 16, 2, 2, TA, LA, double, LB, 1>(M, N, K, a, b, a, b, 0, epi, lower_only,
-                                                                       abort, st, 1, 1, 0, 0, only, only2);
+  Operand<TA> a{A, lda, nullptr, nullptr};
+  Operand<double> b{B, ldb, nullptr, nullptr};
+  return launch_tiled<double, TA, LA, double, LB>(tile_for(M, N, lower_only), M, N, K, a, b, epi, lower_only, abort, st,
+                                                  1, 1, 0, 0, only, only2, tri);
 }
 
 // C = alpha A B^T in FP64, by residues where that is faster (mod_pays) and the
@@ -288,56 +444,98 @@ static bool nt_product(int64_t M, int N, int K, const TA* A, int64_t lda, const 
 template <int LA, int LB>
 static bool dgemm_batched(int M, int N, int64_t K, const double* A, int64_t lda, int64_t sa, const double* B,
                           int64_t ldb, int64_t sb, double* C, int64_t ldc, int64_t sc, int batch, double alpha,
-                          const int* abort, hipStream_t st) {
+                          int tri, const int* abort, hipStream_t st) {
   EpiStore<double> epi{C, ldc, M, N, alpha, 0.0, nullptr, 0, sc};
   Operand<double> a{A, lda, nullptr, nullptr};
   Operand<double> b{B, ldb, nullptr, nullptr};
-  return launch_gemm<double, 128, 128, 16, 2, 2, double, LA, double, LB, 1>(M, N, K, a, b, a, b, 0, epi, 0, abort, st,
-                                                                           1, batch, sa, sb);
+  return launch_tiled<double, double, LA, double, LB>(tile_for(M, N, 0, batch), M, N, K, a, b, epi, 0, abort, st, 1,
+                                                      batch, sa, sb, nullptr, nullptr, tri);
 }
+
+// Tile edge and split-K factor of a product.
+struct TilePlan {
+  int tile, splits;
+};
 
 // GEMM in compute type T with split-K slices written to C + z * zstride.
 // bscale: optional per-k factor of B; lower_only: skip tiles above the diagonal.
 template <class T, int LA, int LB, class TA, class TB, class TC>
 static bool tgemm(int M, int N, int64_t K, const TA* A, int64_t lda, const TB* B, int64_t ldb, TC* C, int64_t ldc,
-                  double alpha, double beta, const int* abort, hipStream_t st, int splits = 1,
+                  double alpha, double beta, const int* abort, hipStream_t st, TilePlan plan = {0, 1},
                   int64_t zstride = 0, const double* bscale = nullptr, int lower_only = 0) {
   EpiStore<TC> epi{C, ldc, M, N, alpha, beta, nullptr, zstride, 0};
   Operand<TA> a{A, lda, nullptr, nullptr};
   Operand<TB> b{B, ldb, nullptr, bscale};
-  return launch_gemm<T, 128, 128, 16, 2, 2, TA, LA, TB, LB, 1>(M, N, K, a, b, a, b, 0, epi, lower_only, abort, st,
-                                                               splits);
+  return launch_tiled<T, TA, LA, TB, LB>(plan.tile ? plan.tile : tile_for(M, N, lower_only), M, N, K, a, b, epi,
+                                         lower_only, abort, st, plan.splits);
+}
+
+// Upper triangle of an n x n matrix from its lower triangle: a 64 x 64 tile
+// per workgroup through LDS, so that both sides move whole cache lines.
+__global__ __launch_bounds__(256) void mirror_lower(double* __restrict__ H, int n, const int* abort) {
+  if (*abort) return;
+  __shared__ double t[64][65];
+  const int i0 = 64 * blockIdx.y, j0 = 64 * blockIdx.x;  // tile (i, j), i >= j, of the lower triangle
+  if (j0 > i0) return;
+  const int c = threadIdx.x & 63, r0 = threadIdx.x >> 6;
+  for (int r = r0; r < 64; r += 4)
+    if (i0 + r < n && j0 + c < n) t[r][c] = H[(int64_t)(i0 + r) * n + j0 + c];
+  __syncthreads();
+  for (int r = r0; r < 64; r += 4)
+    if (j0 + r < n && i0 + c < n && i0 + c > j0 + r) H[(int64_t)(j0 + r) * n + i0 + c] = t[c][r];
+}
+static bool mirror(double* H, int n, const int* abort, hipStream_t s) {
+  const unsigned b = (unsigned)ceil_div(n, 64);
+  hipLaunchKernelGGL(mirror_lower, dim3(b, b), dim3(256), 0, s, H, n, abort);
+  return launch_ok();
 }
 
 // Cholesky of X (n x n, lower, in place) and W = X^-1 into X:
-//  1. blocked right-looking Cholesky, 64-wide diagonal blocks factored and
-//     inverted in LDS, panel L21 = A21 L11^-T and trailing update on MFMA;
+//  1. blocked right-looking Cholesky: 64-wide diagonal blocks factored and
+//     inverted in LDS, panel L21 = A21 L11^-T; the columns of the same
+//     CHOL_OUTER-wide block are updated after each panel, the columns beyond
+//     it once per block, so that they are read and written once per 256 of K
+//     instead of once per 64 (n = 8192: 23 GB of passes over the trailing
+//     matrix become 6 GB);
 //  2. Y = L^-1 by recursive doubling: once every aligned segment of size b
 //     has its inverse, a pair [[A, 0], [L21, C]] gets its lower-left block
-//     -C^-1 L21 A^-1 (two GEMMs, batched over all pairs of the level);
-//  3. W = Y^T Y.
+//     -C^-1 L21 A^-1 (two GEMMs, batched over all pairs of the level; K loops
+//     leave out the zeros of the triangular operand);
+//  3. W = Y^T Y, zeros left out, from MIRROR_MIN on its lower tiles only
+//     (below, every tile runs at once and the mirror pass would add a launch).
 struct InvWork {
   double* Y;  // [n][n]
   double* R;  // [n][n] scratch
 };
+constexpr int CHOL_OUTER = 256;
+constexpr int MIRROR_MIN = 768;
 
 static int spd_inverse(double* X, int n, InvWork w, FitState* st, hipStream_t s) {
   const int* ab = &st->abort;
-  const int nblk = (int)ceil_div(n, NB);
   if (!fill<double>(w.Y, (int64_t)n * n, 0.0, s)) return ISDF_E_HIP;
-  for (int b = 0; b < nblk; ++b) {
-    const int k0 = b * NB, kb = n - k0 < NB ? n - k0 : NB;
-    hipLaunchKernelGGL(potrf_diag, dim3(1), dim3(256), 0, s, X, (int64_t)n, k0, kb, w.Y, (int64_t)n, st);
-    if (!launch_ok()) return ISDF_E_HIP;
-    const int rest = n - k0 - kb;
-    if (rest <= 0) continue;
-    double* P = X + (int64_t)(k0 + kb) * n + k0;
-    // panel: L21 = A21 L11^-T (in place: each workgroup reads all K of its rows before writing them)
-    if (!dgemm<KC, KC>(rest, kb, kb, P, n, w.Y + (int64_t)k0 * n + k0, n, P, n, 1.0, 0.0, 0, ab, s))
+  for (int o = 0; o < n; o += CHOL_OUTER) {
+    const int oe = n - o < CHOL_OUTER ? n : o + CHOL_OUTER;
+    for (int k0 = o; k0 < oe; k0 += NB) {
+      const int kb = n - k0 < NB ? n - k0 : NB, k1 = k0 + kb;
+      hipLaunchKernelGGL(potrf_diag, dim3(1), dim3(256), 0, s, X, (int64_t)n, k0, kb, w.Y, (int64_t)n, st);
+      if (!launch_ok()) return ISDF_E_HIP;
+      if (k1 >= n) continue;
+      double* P = X + (int64_t)k1 * n + k0;
+      // panel: L21 = A21 L11^-T in place, each workgroup with all 64 columns of
+      // its rows (it reads them before it writes them)
+      EpiStore<double> epi{P, n, n - k1, kb, 1.0, 0.0, nullptr, 0, 0};
+      Operand<double> a{P, n, nullptr, nullptr}, b{w.Y + (int64_t)k0 * n + k0, n, nullptr, nullptr};
+      if (!launch_gemm<double, 32, NB, 32, 2, 2, double, KC, double, KC, 1>(n - k1, kb, kb, a, b, a, b, 0, epi, 0, ab,
+                                                                           s))
+        return ISDF_E_HIP;
+      // the block's columns right of the panel: A -= L21 L21^T
+      if (!dgemm<KC, KC>(n - k1, oe - k1, kb, P, n, P, n, X + (int64_t)k1 * n + k1, n, -1.0, 1.0, 0, ab, s))
+        return ISDF_E_HIP;
+    }
+    // the columns right of the block (lower tiles)
+    double* P = X + (int64_t)oe * n + o;
+    if (oe < n && !dgemm<KC, KC>(n - oe, n - oe, oe - o, P, n, P, n, X + (int64_t)oe * n + oe, n, -1.0, 1.0, 1, ab, s))
       return ISDF_E_HIP;
-    // trailing: A22 -= L21 L21^T (lower tiles)
-    double* T = X + (int64_t)(k0 + kb) * n + (k0 + kb);
-    if (!dgemm<KC, KC>(rest, rest, kb, P, n, P, n, T, n, -1.0, 1.0, 1, ab, s)) return ISDF_E_HIP;
   }
   const int64_t ld = n;
   for (int b = NB; b < n; b *= 2) {
@@ -346,26 +544,29 @@ static int spd_inverse(double* X, int n, InvWork w, FitState* st, hipStream_t s)
     if (pairs > 0) {
       // R_p = L21 A^-1, then C-block rows of Y: -C^-1 R_p
       if (!dgemm_batched<KC, XC>(b, b, b, X + (int64_t)b * ld, ld, step, w.Y, ld, step, w.R, b, (int64_t)b * b,
-                                 pairs, 1.0, ab, s))
+                                 pairs, 1.0, TRI_B_LOWER, ab, s))
         return ISDF_E_HIP;
       if (!dgemm_batched<KC, XC>(b, b, b, w.Y + (int64_t)b * ld + b, ld, step, w.R, b, (int64_t)b * b,
-                                 w.Y + (int64_t)b * ld, ld, step, pairs, -1.0, ab, s))
+                                 w.Y + (int64_t)b * ld, ld, step, pairs, -1.0, TRI_A_LOWER, ab, s))
         return ISDF_E_HIP;
     }
     const int o = pairs * 2 * b, rem = n - o;
     if (rem > b) {  // ragged last pair: A of size b, C of size rem - b
       const int c = rem - b;
       const int64_t org = (int64_t)o * (ld + 1);
-      if (!dgemm_batched<KC, XC>(c, b, b, X + org + (int64_t)b * ld, ld, 0, w.Y + org, ld, 0, w.R, b, 0, 1, 1.0, ab,
-                                 s))
+      if (!dgemm_batched<KC, XC>(c, b, b, X + org + (int64_t)b * ld, ld, 0, w.Y + org, ld, 0, w.R, b, 0, 1, 1.0,
+                                 TRI_B_LOWER, ab, s))
         return ISDF_E_HIP;
       if (!dgemm_batched<KC, XC>(c, b, c, w.Y + org + (int64_t)b * ld + b, ld, 0, w.R, b, 0,
-                                 w.Y + org + (int64_t)b * ld, ld, 0, 1, -1.0, ab, s))
+                                 w.Y + org + (int64_t)b * ld, ld, 0, 1, -1.0, TRI_A_LOWER, ab, s))
         return ISDF_E_HIP;
     }
   }
   // W = Y^T Y
-  if (!dgemm<XC, XC>(n, n, n, w.Y, n, w.Y, n, X, n, 1.0, 0.0, 0, ab, s)) return ISDF_E_HIP;
+  const int half = n >= MIRROR_MIN;
+  if (!dgemm<XC, XC>(n, n, n, w.Y, n, w.Y, n, X, n, 1.0, 0.0, half, ab, s, nullptr, nullptr, TRI_UPPER_LOWER))
+    return ISDF_E_HIP;
+  if (half && !mirror(X, n, ab, s)) return ISDF_E_HIP;
   return ISDF_OK;
 }
 
@@ -566,6 +767,15 @@ static bool gram(const TS* phi, int64_t ld_phi, int n_phi, const TS* psi, int64_
   } else {
     // FP32: accumulators folded into FP64 every 2 steps (32-deep)
     constexpr int FOLD = sizeof(T) == 4 ? 2 : 0;
+    if constexpr (FOLD == 0) {
+      // few tiles: smaller ones (tile_for)
+      if (aliased && tile_for(rows, N, 0) < 128)
+        return launch_gemm<T, 64, 64, 16, 2, 2, TS, KC, T, KC, 1>(rows, N, 2 * (int64_t)n_phi, a0, b0, a0, b0, 0, epi,
+                                                                  0, abort, s);
+      if (!aliased && tile_for(rows, N, 0) < 128)
+        return launch_gemm<T, 64, 64, 16, 2, 2, TS, KC, T, KC, 2>(rows, N, 2 * (int64_t)n_phi, a0, b0, a1, b1,
+                                                                  2 * (int64_t)n_psi, epi, 0, abort, s);
+    }
     if (aliased)
       return launch_gemm<T, 128, 128, 16, 2, 2, TS, KC, T, KC, 1, FOLD>(rows, N, 2 * (int64_t)n_phi, a0, b0, a0, b0,
                                                                          0, epi, 0, abort, s);

@@ -79,6 +79,16 @@ struct GemmShape {
   const int* abort;  // nonzero *abort turns the launch into a no-op
   const int *only, *only2;  // when given, *only and *only2 both zero do so too
   int64_t sa, sb;    // batch strides of A and B (elements); batch index = blockIdx.y
+  int tri;           // zero parts of triangular operands that K loops leave out (no split-K)
+};
+
+// Triangular operands: a tile's K loop starts or ends where the operand's
+// zeros begin (left-out products are zeros, so the sums are the same).
+enum {
+  TRI_NONE = 0,
+  TRI_B_LOWER = 1,  // B(k, n) = 0 for k < n
+  TRI_A_LOWER = 2,  // A(m, k) = 0 for k > m
+  TRI_UPPER_LOWER = 3,  // A(m, k) = 0 for k < m and B(k, n) = 0 for k < n
 };
 
 // Number of tiles a launch enumerates.
@@ -554,8 +564,11 @@ __global__ __launch_bounds__(WM* WN* ISDF_WAVE, 2) void gemm_kernel(GemmShape sh
     A0.p += batch * sh.sa;
     B0.p += batch * sh.sb;
   }
-  const int64_t kbeg = (int64_t)z * sh.kchunk;
-  const int64_t kend = kbeg + sh.kchunk < sh.K ? kbeg + sh.kchunk : sh.K;
+  int64_t kbeg = (int64_t)z * sh.kchunk;
+  int64_t kend = kbeg + sh.kchunk < sh.K ? kbeg + sh.kchunk : sh.K;
+  if (sh.tri == TRI_B_LOWER) kbeg = n0;
+  else if (sh.tri == TRI_UPPER_LOWER) kbeg = m0 > n0 ? m0 : n0;
+  else if (sh.tri == TRI_A_LOWER && m0 + BM < kend) kend = m0 + BM;
 
   typedef typename MfmaT<T>::acc_t acc_t;
   acc_t acc0[Cfg::MI][Cfg::NI];

@@ -1,0 +1,62 @@
+"""Sizes at the edges of the kernels' blocks and of the dispatch rules."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+isdf = pytest.importorskip("paper_2208_07731_amd")
+
+EPS = np.finfo(np.float64).eps
+
+
+def dev(x):
+    return torch.as_tensor(np.ascontiguousarray(x)).cuda()
+
+
+def _cc_real(phi, psi, idx):
+    """C C^H as the factorisation sees it: real, or real 2 x 2 blocks."""
+    a = phi[idx] @ phi[idx].conj().T
+    m = a * (psi[idx] @ psi[idx].conj().T).conj()
+    if psi is phi:
+        return m.real
+    rows = np.stack([np.stack([m.real, m.imag], 2), np.stack([-m.imag, m.real], 2)], 1)
+    return rows.reshape(2 * len(idx), 2 * len(idx))
+
+
+# orders around the 16-, 32- and 64-wide blocks of the diagonal kernel, the
+# 256-wide outer block, the order from which the inverse is formed on its lower
+# tiles (768), and ragged last blocks; complex: twice the order
+@pytest.mark.parametrize("n_mu,two", [(1, 0), (15, 0), (17, 0), (63, 0), (64, 0), (65, 0), (129, 0), (255, 0), (256, 0),
+                                      (257, 0), (577, 0), (767, 0), (768, 0), (833, 0), (33, 1), (129, 1), (385, 1)])
+def test_cholesky_inverse_edges(n_mu, two):
+    """(C C^H)^-1 against numpy's inverse.  The computed inverse of an SPD
+    matrix of order n by Cholesky is within c n eps kappa of the exact one; the
+    bar is 8 n eps kappa (numpy's own error included)."""
+    n = (10, 11, 13)
+    phi = synth.random_orthonormal(1430, 40, 3 + n_mu)
+    psi = synth.random_orthonormal(1430, 44, 4 + n_mu) if two else phi
+    idx = np.random.default_rng(n_mu).permutation(1430)[:n_mu]
+    m = _cc_real(phi, psi, idx)
+    p = dev(phi)
+    theta, minv, info = isdf.fit(p, dev(psi) if two else None, dev(idx.astype(np.int32)), grid=n)
+    w = minv.cpu().numpy().reshape(m.shape)
+    ev = np.linalg.eigvalsh(m)
+    ref = np.linalg.inv(m)
+    err = np.linalg.norm(w - ref) / np.linalg.norm(ref)
+    assert info["status"] == 0 and info["pivot"] == -1
+    assert err <= 8 * len(m) * EPS * ev[-1] / ev[0]
+    assert np.array_equal(w, w.T)
+    assert ev[0] * (1 - 1e-8) <= info["pivot_min"] <= info["pivot_max"] <= ev[-1] * (1 + 1e-8)
+
+
+@pytest.mark.parametrize("bad", [0, 15, 16, 63, 64, 70, 299])
+def test_cholesky_names_the_failing_pivot(bad):
+    """A zero orbital row makes exactly its own pivot zero."""
+    phi = synth.random_orthonormal(1430, 40, 5)
+    idx = np.random.default_rng(6).permutation(1430)[:300]
+    phi[idx[bad]] = 0.0
+    _, _, info = isdf.fit(dev(phi), None, dev(idx.astype(np.int32)), grid=(10, 11, 13), check=False)
+    assert info["status"] == 1 and info["pivot"] == bad

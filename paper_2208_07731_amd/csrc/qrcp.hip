@@ -32,10 +32,12 @@
 namespace isdf {
 namespace {
 
-constexpr int QR_TILE = 256;     // grid rows per workgroup (one per thread in phase 2)
-constexpr int QR_LPC = 1024;     // pivot-row entries staged in LDS per chunk
+constexpr int QR_TILE = 256;     // grid rows per workgroup of qrcp_init
+constexpr int QR_ROWS = 64;      // grid rows per workgroup of qrcp_step (a lane each in phase 2)
+constexpr int QR_WAVES = 8;      // its wavefronts: the columns of L are shared out between them
 constexpr int QR_SEL = 256;      // threads of qrcp_select
-constexpr int QR_UNROLL = 4;     // rows per wavefront in flight in phase 1
+constexpr int QR_SUB = 16;       // lanes per grid row in phase 1
+constexpr int QR_FLY = 16;       // loads of L in flight per lane in phase 2
 
 // Gram matrix K whose pivoted Cholesky is taken:
 enum {
@@ -85,6 +87,13 @@ __device__ __forceinline__ Top2 top2_wave(Top2 t) {
   return t;
 }
 
+__device__ __forceinline__ void top2_put(Top2 a, double bad, double* o) {
+  o[0] = a.d1;
+  o[1] = a.d1 >= 0.0 ? (double)a.r1 : -1.0;  // exact: grid indices < 2^31
+  o[2] = a.d2;
+  o[3] = bad;
+}
+
 // Workgroup top-2 of (d, r) over its threads (d < 0: not a candidate) and
 // count of non-finite values, stored as part[4 blockIdx.x + {d1, r1, d2, bad}].
 __device__ __forceinline__ void block_top2_store(double d, int64_t r, double bad, double* part) {
@@ -109,11 +118,7 @@ __device__ __forceinline__ void block_top2_store(double d, int64_t r, double bad
       a = top2_merge(a, red[i]);
       b += rbad[i];
     }
-    double* o = part + 4 * blockIdx.x;
-    o[0] = a.d1;
-    o[1] = a.d1 >= 0.0 ? (double)a.r1 : -1.0;  // exact: grid indices < 2^31
-    o[2] = a.d2;
-    o[3] = b;
+    top2_put(a, b, part + 4 * blockIdx.x);
   }
 }
 
@@ -159,139 +164,152 @@ __global__ __launch_bounds__(QR_TILE) void qrcp_init(const TS* __restrict__ phi,
   block_top2_store(mine, r, bad, part);
 }
 
-// One column of L.  Phase 1: one wavefront per row for K(r, p) (lanes over
-// the orbitals, Phi(p) and Psi(p) from LDS; the sketch's row X(p) in place).
-// Phase 2: one thread per row
-// for the projection on the earlier columns (column-major L, coalesced; the
-// pivot's row of L broadcast from LDS in chunks).
+// Phase 1 of a step for the rows [r0, r0 + QR_ROWS): re, im of X(r) . conj(q)
+// for one orbital set, QR_SUB lanes per row, a wavefront's rows all in flight.
+template <class TS>
+__device__ __forceinline__ void qrcp_dots(const TS* __restrict__ x, int64_t ld, int n, const double2* q, int64_t r0,
+                                          int64_t nr, int wv, int lane, double (&re)[2], double (&im)[2]) {
+  static_assert(QR_WAVES * 2 * (ISDF_WAVE / QR_SUB) == QR_ROWS, "two rows per lane group");
+  const int sub = lane % QR_SUB, g = lane / QR_SUB;
+  const TS* row[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int64_t r = r0 + 8 * wv + 4 * u + g;
+    row[u] = x + 2 * (r < nr ? r : nr - 1) * ld;
+    re[u] = im[u] = 0.0;
+  }
+#pragma unroll 4
+  for (int i = sub; i < n; i += QR_SUB) {
+    const double2 p = q[i];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const double2 z = Cplx<TS>::load(row[u] + 2 * i);
+      re[u] += z.x * p.x + z.y * p.y;
+      im[u] += z.y * p.x - z.x * p.y;
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int o = QR_SUB / 2; o > 0; o >>= 1) {
+      re[u] += __shfl_xor(re[u], o, ISDF_WAVE);
+      im[u] += __shfl_xor(im[u], o, ISDF_WAVE);
+    }
+}
+
+// One column of L for QR_ROWS grid rows.  Phase 1: K(r, p), 16 lanes per row
+// over the orbitals (Phi(p) and Psi(p) from LDS; the sketch's row X(p) in
+// place).  Phase 2: the projection on the earlier columns, a lane per row
+// (column-major L, coalesced), each wavefront an eighth of the columns, their
+// sums added in wavefront order.
+// Bound by the latency of a step, not by its bytes: with a workgroup per 256
+// rows and all k columns in one wavefront's loop half the CUs had no work and
+// a step took 50 us on average at 32768 rows, 64 orbitals, 512 columns
+// (100 MB, 13 us at the HBM rate); 19 us with 64-row workgroups of eight
+// wavefronts, 16 loads in flight a lane.
 template <class TS, int MODE>
-__global__ __launch_bounds__(QR_TILE) void qrcp_step(const TS* __restrict__ phi, int64_t ldp, int nphi,
-                                                    const TS* __restrict__ psi, int64_t lds, int npsi,
-                                                    int64_t nr, int k, const QrcpState* __restrict__ st,
-                                                    double* __restrict__ L, double* __restrict__ d,
-                                                    const double* __restrict__ lp, double* __restrict__ part) {
+__global__ __launch_bounds__(QR_WAVES* ISDF_WAVE) void qrcp_step(const TS* __restrict__ phi, int64_t ldp, int nphi,
+                                                                 const TS* __restrict__ psi, int64_t lds, int npsi,
+                                                                 int64_t nr, int k, const QrcpState* __restrict__ st,
+                                                                 double* __restrict__ L, double* __restrict__ d,
+                                                                 const double* __restrict__ lp,
+                                                                 double* __restrict__ part) {
   if (st->done) return;  // uniform: written by the previous select launch
   extern __shared__ double lds_mem[];
   constexpr bool CPLX = MODE != QR_ALIASED;
   constexpr bool TWO = MODE == QR_HADAMARD;  // a second orbital set
   constexpr int CW = CPLX ? 2 : 1;
   constexpr bool STAGE = MODE != QR_PLAIN;  // copy the pivot's orbital rows to LDS
+  __shared__ double crow[QR_ROWS][2], proj[QR_WAVES][CW][QR_ROWS];
   double2* sphi = reinterpret_cast<double2*>(lds_mem);
   double2* spsi = sphi + (STAGE ? nphi : 0);
-  double* slp = reinterpret_cast<double*>(spsi + (TWO ? npsi : 0));
   const int64_t p = st->p;
   const double dp = st->dp;
   const int tid = threadIdx.x;
   const int lane = tid & (ISDF_WAVE - 1);
-  const int wv = tid / ISDF_WAVE;
+  const int wv = __builtin_amdgcn_readfirstlane(tid / ISDF_WAVE);
+  const int64_t r0 = (int64_t)blockIdx.x * QR_ROWS;
+
+  // ---- phase 2 first (its loads need nothing but k): sum_{j<k} L(r, j) conj(L(p, j));
+  // lp holds conj(L(p, j))
+  const int64_t r = r0 + lane;
+  const bool live = r < nr;
+  const int per = (k + QR_WAVES - 1) / QR_WAVES;
+  const int jb = wv * per < k ? wv * per : k, je = jb + per < k ? jb + per : k;
+  double sre = 0.0, sim = 0.0;
+  const double* col = L + ((int64_t)jb * nr + (live ? r : nr - 1)) * CW;
+  const double* q = lp + (int64_t)jb * CW;
+  for (int j = jb; j < je; j += QR_FLY) {
+    double v[QR_FLY * CW];
+#pragma unroll
+    for (int u = 0; u < QR_FLY; ++u) {  // past the end: the last column again, not summed
+      const int ju = j + u < je ? u : je - 1 - j;
+      if (CPLX) {
+        const double2 x = *reinterpret_cast<const double2*>(col + (int64_t)ju * nr * CW);
+        v[2 * u] = x.x;
+        v[2 * u + 1] = x.y;
+      } else {
+        v[u] = col[(int64_t)ju * nr];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < QR_FLY; ++u) {
+      if (j + u >= je) continue;
+      if (CPLX) {
+        const double qr = q[2 * u], qi = q[2 * u + 1];
+        sre += v[2 * u] * qr - v[2 * u + 1] * qi;
+        sim += v[2 * u] * qi + v[2 * u + 1] * qr;
+      } else {
+        sre += v[u] * q[u];
+      }
+    }
+    col += (int64_t)QR_FLY * nr * CW;
+    q += QR_FLY * CW;
+  }
+  proj[wv][0][lane] = sre;
+  if (CPLX) proj[wv][CW - 1][lane] = sim;
 
   if (STAGE)
-    for (int i = tid; i < nphi; i += QR_TILE) sphi[i] = Cplx<TS>::load(phi + 2 * (p * ldp + i));
+    for (int i = tid; i < nphi; i += QR_WAVES * ISDF_WAVE) sphi[i] = Cplx<TS>::load(phi + 2 * (p * ldp + i));
   if (TWO)
-    for (int i = tid; i < npsi; i += QR_TILE) spsi[i] = Cplx<TS>::load(psi + 2 * (p * lds + i));
+    for (int i = tid; i < npsi; i += QR_WAVES * ISDF_WAVE) spsi[i] = Cplx<TS>::load(psi + 2 * (p * lds + i));
   __syncthreads();
   // the sketch's pivot row (m complex FP64 values, possibly more than LDS
   // holds) is read in place: every wavefront reads the same row, which
   // stays in the caches
-  const double2* __restrict__ qphi;
+  const double2* qphi;
   if constexpr (STAGE)
     qphi = sphi;
   else
     qphi = reinterpret_cast<const double2*>(phi) + p * ldp;
 
   // ---- phase 1: c = K(r, p): a conj(b), |a|^2 or a, a = Phi(r).conj(Phi(p)), b likewise
-  const int64_t base = (int64_t)blockIdx.x * QR_TILE + wv * ISDF_WAVE;
-  double cre = 0.0, cim = 0.0;
-  for (int rr = 0; rr < ISDF_WAVE; rr += QR_UNROLL) {
-    double ar[QR_UNROLL], ai[QR_UNROLL], br[QR_UNROLL], bi[QR_UNROLL];
+  double ar[2], ai[2], br[2], bi[2];
+  qrcp_dots<TS>(phi, ldp, nphi, qphi, r0, nr, wv, lane, ar, ai);
+  if (TWO) qrcp_dots<TS>(psi, lds, npsi, spsi, r0, nr, wv, lane, br, bi);
 #pragma unroll
-    for (int u = 0; u < QR_UNROLL; ++u) {
-      ar[u] = ai[u] = br[u] = bi[u] = 0.0;
-      const int64_t r = base + rr + u;
-      if (r < nr) {
-        for (int i = lane; i < nphi; i += ISDF_WAVE) {
-          const double2 z = Cplx<TS>::load(phi + 2 * (r * ldp + i));
-          const double2 q = qphi[i];
-          ar[u] += z.x * q.x + z.y * q.y;
-          ai[u] += z.y * q.x - z.x * q.y;
-        }
-        if (TWO)
-          for (int i = lane; i < npsi; i += ISDF_WAVE) {
-            const double2 z = Cplx<TS>::load(psi + 2 * (r * lds + i));
-            const double2 q = spsi[i];
-            br[u] += z.x * q.x + z.y * q.y;
-            bi[u] += z.y * q.x - z.x * q.y;
-          }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < QR_UNROLL; ++u) {
-      const double sar = wave_sum(ar[u]), sai = wave_sum(ai[u]);
+  for (int u = 0; u < 2; ++u)
+    if (lane % QR_SUB == 0) {
+      double* c = crow[8 * wv + 4 * u + lane / QR_SUB];
       if (TWO) {
-        const double sbr = wave_sum(br[u]), sbi = wave_sum(bi[u]);
-        if (lane == rr + u) {
-          cre = sar * sbr + sai * sbi;  // a conj(b)
-          cim = sai * sbr - sar * sbi;
-        }
+        c[0] = ar[u] * br[u] + ai[u] * bi[u];  // a conj(b)
+        c[1] = ai[u] * br[u] - ar[u] * bi[u];
       } else if (MODE == QR_PLAIN) {
-        if (lane == rr + u) {
-          cre = sar;                    // X(r) . conj(X(p))
-          cim = sai;
-        }
-      } else if (lane == rr + u) {
-        cre = sar * sar + sai * sai;    // |a|^2: Psi = Phi
+        c[0] = ar[u];  // X(r) . conj(X(p))
+        c[1] = ai[u];
+      } else {
+        c[0] = ar[u] * ar[u] + ai[u] * ai[u];  // |a|^2: Psi = Phi
+        c[1] = 0.0;
       }
     }
-  }
-  // lane l of wavefront w now holds row base + l; move to thread-per-row order
-  // (the same thread: row = blockIdx.x * QR_TILE + tid).
-  const int64_t r = (int64_t)blockIdx.x * QR_TILE + tid;
-  const bool live = r < nr;
-
-  // ---- phase 2: c -= sum_{j<k} L(r, j) conj(L(p, j)); lp holds conj(L(p, j))
-  double sre = 0.0, sim = 0.0;
-  for (int j0 = 0; j0 < k; j0 += QR_LPC) {
-    const int jn = min(QR_LPC, k - j0);
-    __syncthreads();
-    for (int t = tid; t < jn * CW; t += QR_TILE) slp[t] = lp[(int64_t)j0 * CW + t];
-    __syncthreads();
-    if (live) {
-      const double* col = L + ((int64_t)j0 * nr + r) * CW;
-      int j = 0;
-      for (; j + 8 <= jn; j += 8) {
-        double v[8 * CW];
+  __syncthreads();
+  if (wv != 0) return;
+  const double cre = crow[lane][0], cim = crow[lane][1];
+  sre = sim = 0.0;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          if (CPLX) {
-            const double2 x = *reinterpret_cast<const double2*>(col + (int64_t)(j + u) * nr * CW);
-            v[2 * u] = x.x;
-            v[2 * u + 1] = x.y;
-          } else {
-            v[u] = col[(int64_t)(j + u) * nr];
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          if (CPLX) {
-            const double qr = slp[2 * (j + u)], qi = slp[2 * (j + u) + 1];
-            sre += v[2 * u] * qr - v[2 * u + 1] * qi;
-            sim += v[2 * u] * qi + v[2 * u + 1] * qr;
-          } else {
-            sre += v[u] * slp[j + u];
-          }
-        }
-      }
-      for (; j < jn; ++j) {
-        if (CPLX) {
-          const double2 x = *reinterpret_cast<const double2*>(col + (int64_t)j * nr * CW);
-          const double qr = slp[2 * j], qi = slp[2 * j + 1];
-          sre += x.x * qr - x.y * qi;
-          sim += x.x * qi + x.y * qr;
-        } else {
-          sre += col[(int64_t)j * nr] * slp[j];
-        }
-      }
-    }
+  for (int w = 0; w < QR_WAVES; ++w) {
+    sre += proj[w][0][lane];
+    if (CPLX) sim += proj[w][CW - 1][lane];
   }
 
   double dn = -1.0, bad = 0.0;
@@ -323,7 +341,13 @@ __global__ __launch_bounds__(QR_TILE) void qrcp_step(const TS* __restrict__ phi,
       *out = lre;
     d[r] = dn;
   }
-  block_top2_store(dn, r, bad, part);
+  Top2 t;
+  t.d1 = dn >= 0.0 ? dn : -1.0;
+  t.r1 = dn >= 0.0 ? r : INT64_MAX;
+  t.d2 = -1.0;
+  t = top2_wave(t);
+  bad = wave_sum(bad);
+  if (lane == 0) top2_put(t, bad, part + 4 * blockIdx.x);
 }
 
 // Global top-2 over the workgroup partials, the pivot decision of step k and
@@ -431,12 +455,11 @@ __global__ void qrcp_reset(QrcpState* st) {
   st->d0 = 0.0;
 }
 
-// LDS of one qrcp_step workgroup: Phi(p), Psi(p) and a chunk of the pivot's row of L.
+// Dynamic LDS of one qrcp_step workgroup: Phi(p), Psi(p).
 static size_t qrcp_lds_bytes(int n_phi, int n_psi, int mode) {
-  return sizeof(double2) * (size_t)((mode == QR_PLAIN ? 0 : n_phi) + (mode == QR_HADAMARD ? n_psi : 0)) +
-         sizeof(double) * QR_LPC * (mode == QR_ALIASED ? 1 : 2);
+  return sizeof(double2) * (size_t)((mode == QR_PLAIN ? 0 : n_phi) + (mode == QR_HADAMARD ? n_psi : 0));
 }
-static constexpr size_t QR_MAX_LDS = 64 * 1024;
+static constexpr size_t QR_MAX_LDS_ALIASED = 56 * 1024, QR_MAX_LDS = 48 * 1024;
 
 struct QrcpPlan {
   double* L;
@@ -450,7 +473,7 @@ struct QrcpPlan {
 static QrcpPlan plan_qrcp(void* ws, int64_t nr, int n_mu, bool cplx) {
   Carver c(ws, (size_t)-1);
   const int cw = cplx ? 2 : 1;
-  const int64_t nblk = ceil_div(nr, QR_TILE);
+  const int64_t nblk = ceil_div(nr, QR_ROWS);
   QrcpPlan pl;
   pl.L = c.take<double>((size_t)(n_mu > 1 ? n_mu - 1 : 1) * nr * cw);
   pl.d = c.take<double>((size_t)nr);
@@ -465,21 +488,22 @@ template <class TS, int MODE>
 static int qrcp_run(const TS* phi, int64_t ldp, int nphi, const TS* psi, int64_t lds, int npsi, int64_t nr, int n_mu,
                     double rtol, double near_tie_rel, int32_t* idx, double* rdiag, double* gap,
                     isdf_qrcp_info* info, const QrcpPlan& pl, hipStream_t s) {
-  const int nblk = (int)ceil_div(nr, QR_TILE);
+  const int nblk = (int)ceil_div(nr, QR_ROWS), nblk0 = (int)ceil_div(nr, QR_TILE);
   constexpr bool CPLX = MODE != QR_ALIASED;
   const size_t lds_bytes = qrcp_lds_bytes(nphi, npsi, MODE);
   const double rtol2 = rtol * rtol;
   hipLaunchKernelGGL(qrcp_reset, dim3(1), dim3(1), 0, s, pl.st);
   if (!launch_ok()) return ISDF_E_HIP;
-  hipLaunchKernelGGL((qrcp_init<TS>), dim3(nblk), dim3(QR_TILE), 0, s, phi, ldp, nphi, psi, lds, npsi, MODE, nr,
+  hipLaunchKernelGGL((qrcp_init<TS>), dim3(nblk0), dim3(QR_TILE), 0, s, phi, ldp, nphi, psi, lds, npsi, MODE, nr,
                      pl.d, pl.part);
   if (!launch_ok()) return ISDF_E_HIP;
   for (int k = 0; k < n_mu; ++k) {
-    hipLaunchKernelGGL((qrcp_select<CPLX>), dim3(1), dim3(QR_SEL), 0, s, (const double*)pl.part, nblk, k, n_mu,
+    hipLaunchKernelGGL((qrcp_select<CPLX>), dim3(1), dim3(QR_SEL), 0, s, (const double*)pl.part,
+                       k == 0 ? nblk0 : nblk, k, n_mu,
                        rtol2, near_tie_rel, nr, (const double*)pl.L, pl.d, pl.lp, pl.st, idx, rdiag, gap, info);
     if (!launch_ok()) return ISDF_E_HIP;
     if (k == n_mu - 1) break;
-    hipLaunchKernelGGL((qrcp_step<TS, MODE>), dim3(nblk), dim3(QR_TILE), lds_bytes, s, phi, ldp, nphi, psi, lds,
+    hipLaunchKernelGGL((qrcp_step<TS, MODE>), dim3(nblk), dim3(QR_WAVES * ISDF_WAVE), lds_bytes, s, phi, ldp, nphi, psi, lds,
                        npsi, nr, k, (const QrcpState*)pl.st, pl.L, pl.d, (const double*)pl.lp, pl.part);
     if (!launch_ok()) return ISDF_E_HIP;
   }
@@ -515,7 +539,8 @@ extern "C" int isdf_qrcp(const isdf_grid* grid, int32_t dt_in, const void* phi, 
   if (n_mu <= 0 || n_mu > nr || nr >= ((int64_t)1 << 31)) return ISDF_E_ARG;
   if (!(rtol >= 0.0 && rtol < 1.0) || !(near_tie_rel >= 0.0)) return ISDF_E_ARG;
   const bool aliased = phi == psi && ld_phi == ld_psi && n_phi == n_psi;
-  if (qrcp_lds_bytes(n_phi, n_psi, aliased ? QR_ALIASED : QR_HADAMARD) > QR_MAX_LDS) return ISDF_E_UNSUPPORTED;
+  if (qrcp_lds_bytes(n_phi, n_psi, aliased ? QR_ALIASED : QR_HADAMARD) > (aliased ? QR_MAX_LDS_ALIASED : QR_MAX_LDS))
+    return ISDF_E_UNSUPPORTED;
   const QrcpPlan need = plan_qrcp(nullptr, nr, n_mu, !aliased);
   if (!ws || ws_bytes < need.bytes) return ISDF_E_WORKSPACE;
   const QrcpPlan pl = plan_qrcp(ws, nr, n_mu, !aliased);

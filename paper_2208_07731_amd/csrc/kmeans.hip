@@ -7,7 +7,7 @@
 //   km_assign  classification, one 4x4x4 brick of grid points per wavefront:
 //              first round, argmin over every centroid staged through LDS;
 //              later rounds, over the centroids of the cells near the brick
-//              (km_bin); also the objective partials, tie counts,
+//              (km_bin; over all of them when they are few); also the objective partials, tie counts,
 //              changed-label count, evaluated-pair counts and per-cluster
 //              bounding boxes (integer atomics, order independent)
 //   km_update  weighted centroids: one wavefront per cluster scans its
@@ -68,6 +68,9 @@ constexpr int ASSIGN_THREADS = 512;  // 8 wavefronts = 8 bricks
 constexpr int CTILE = 2048;          // centroids staged per LDS tile
 constexpr int MAX_CELLS = 8192;      // centroid cells (counted in LDS by km_bin)
 constexpr int BIN_THREADS = 1024;
+// Up to this many centroids each brick tests all of them (at most 8 tests a
+// lane, and no wait for cells): km_bin is then not launched.
+constexpr int KM_DIRECT = 512;
 
 // Squared distance with the same operation order as the definition
 // ((s0 dx^2 + s1 dy^2) + s2 dz^2); contraction off so that the value is the
@@ -237,14 +240,27 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void km_assign(KmArrays a, KmGeom g
   int lab = 0;
   const int64_t p = ((int64_t)pi * g.n1 + pj) * g.n2 + pk;
   unsigned long long n_eval = 0, n_test = 0;  // survivors evaluated, bound tests (wave-uniform)
+  // issued before anything waits: the point's weight and previous label
+  const double wp = valid ? a.w[p] : 0.0;
+  const int old = valid ? a.labels[p] : 0;
   if (t > 0) {
+    // few centroids: one in KM_DIRECT / 64 registers of a lane each, loaded
+    // while the labels arrive (past the end: centroid 0, not kept)
+    double4 mine[KM_DIRECT / ISDF_WAVE];
+    const bool direct = K <= KM_DIRECT;
+    if (direct) {
+#pragma unroll
+      for (int u = 0; u < KM_DIRECT / ISDF_WAVE; ++u) {
+        const int m = u * ISDF_WAVE + lane < K ? u * ISDF_WAVE + lane : 0;
+        mine[u] = make_double4(a.cent[3 * m], a.cent[3 * m + 1], a.cent[3 * m + 2], (double)m);
+      }
+    }
     // U: the largest distance of a brick point to the centroid of the
     // cluster it was given in the previous round, with the centroids as
     // they are now (just updated): a distance to a current centroid, so it
     // bounds every brick point's nearest distance
     double own = -INFINITY;
     if (valid) {
-      const int old = a.labels[p];
       own = sqd(px - a.cent[3 * (int64_t)old], py - a.cent[3 * (int64_t)old + 1],
                 pz - a.cent[3 * (int64_t)old + 2], g);
     }
@@ -273,6 +289,60 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void km_assign(KmArrays a, KmGeom g
     double* sy = cy + wv * (CTILE / (ASSIGN_THREADS / ISDF_WAVE));
     double* sz = cz + wv * (CTILE / (ASSIGN_THREADS / ISDF_WAVE));
     int nlist = 0;
+    // the listed centroids' distances, four at a time (their LDS reads and
+    // arithmetic overlap), compared in list order
+    auto evaluate = [&]() {
+      for (int e = 0; e < nlist; e += 4) {
+        double d[4];
+        int mm[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int at = e + u < nlist ? e + u : nlist - 1;
+          mm[u] = list[at];
+          d[u] = sqd(px - sx[at], py - sy[at], pz - sz[at], g);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (e + u >= nlist) continue;  // (wave-uniform)
+          const bool better = d[u] < d1 || (d[u] == d1 && mm[u] < lab);
+          d2 = better ? d1 : fmin(d2, d[u]);
+          d1 = better ? d[u] : d1;
+          lab = better ? mm[u] : lab;
+        }
+      }
+      n_eval += (unsigned long long)nlist;
+    };
+    // one candidate per lane: the survivors into this wave's list
+    auto take = [&](bool some, const double4& cand) {
+      const double lb = (g.s0 * axis_lb(cand.x, lo0, hi0) + g.s1 * axis_lb(cand.y, lo1, hi1)) +
+                        g.s2 * axis_lb(cand.z, lo2, hi2);
+      const bool keep = some && lb <= cut;
+      const unsigned long long bal = __ballot(keep);
+      const int cnt = __popcll(bal);
+      if (nlist + cnt > SURV) {  // (wave-uniform)
+        evaluate();
+        nlist = 0;
+        __builtin_amdgcn_wave_barrier();
+      }
+      if (keep) {
+        const int at = nlist + __popcll(bal & ((1ull << lane) - 1ull));
+        list[at] = (int)cand.w;
+        sx[at] = cand.x;
+        sy[at] = cand.y;
+        sz[at] = cand.z;
+      }
+      nlist += cnt;
+      __builtin_amdgcn_wave_barrier();
+    };
+    if (direct) {
+      if (nbox > 0) {
+#pragma unroll
+        for (int u = 0; u < KM_DIRECT / ISDF_WAVE; ++u)
+          if (u * ISDF_WAVE < K) take(u * ISDF_WAVE + lane < K, mine[u]);
+        n_test += (unsigned long long)K;
+      }
+      nbox = 0;
+    }
     for (int b0 = 0; b0 < nbox; b0 += ISDF_WAVE) {
       // one cell of the box per lane: its first entry and its count
       const int q = b0 + lane;
@@ -296,7 +366,6 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void km_assign(KmArrays a, KmGeom g
       __builtin_amdgcn_wave_barrier();
       for (int c0 = 0; c0 < total; c0 += ISDF_WAVE) {
         const int qq = c0 + lane;
-        bool keep = false;
         double4 cand = make_double4(0.0, 0.0, 0.0, 0.0);
         if (qq < total) {
           int lo_i = 0, hi_i = ncell - 1;  // last cell lane whose offset <= qq
@@ -306,53 +375,13 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void km_assign(KmArrays a, KmGeom g
             else hi_i = mid - 1;
           }
           cand = a.cell_c[cst[lo_i] + (qq - cof[lo_i])];
-          const double lb = (g.s0 * axis_lb(cand.x, lo0, hi0) + g.s1 * axis_lb(cand.y, lo1, hi1)) +
-                            g.s2 * axis_lb(cand.z, lo2, hi2);
-          keep = lb <= cut;
         }
         n_test += (unsigned long long)min(ISDF_WAVE, total - c0);
-        const unsigned long long bal = __ballot(keep);
-        const int cnt = __popcll(bal);
-        if (nlist + cnt > SURV) {  // evaluate the list (wave-uniform)
-          for (int e = 0; e < nlist; ++e) {
-            const int m = list[e];
-            const double d = sqd(px - sx[e], py - sy[e], pz - sz[e], g);
-            if (d < d1 || (d == d1 && m < lab)) {
-              d2 = d1;
-              d1 = d;
-              lab = m;
-            } else {
-              d2 = fmin(d2, d);
-            }
-          }
-          n_eval += (unsigned long long)nlist;
-          nlist = 0;
-          __builtin_amdgcn_wave_barrier();
-        }
-        if (keep) {  // survivor: its index and coordinates into this wave's list
-          const int at = nlist + __popcll(bal & ((1ull << lane) - 1ull));
-          list[at] = (int)cand.w;
-          sx[at] = cand.x;
-          sy[at] = cand.y;
-          sz[at] = cand.z;
-        }
-        nlist += cnt;
-        __builtin_amdgcn_wave_barrier();
+        take(qq < total, cand);
       }
       __builtin_amdgcn_wave_barrier();
     }
-    for (int e = 0; e < nlist; ++e) {
-      const int m = list[e];
-      const double d = sqd(px - sx[e], py - sy[e], pz - sz[e], g);
-      if (d < d1 || (d == d1 && m < lab)) {
-        d2 = d1;
-        d1 = d;
-        lab = m;
-      } else {
-        d2 = fmin(d2, d);
-      }
-    }
-    n_eval += (unsigned long long)nlist;
+    evaluate();
   } else {
     // first round: U = the smallest over centroids of the farthest brick
     // distance, then every centroid tile's survivors in increasing index
@@ -436,10 +465,9 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void km_assign(KmArrays a, KmGeom g
   double jv = 0.0;
   bool chg = false, tie = false, nr_tie = false;
   if (valid) {
-    int old = a.labels[p];
     chg = old != lab;
     a.labels[p] = lab;
-    jv = a.w[p] * d1;
+    jv = wp * d1;
     tie = d1 == d2;
     nr_tie = (d2 < INFINITY) && (d2 - d1 <= near_rel * d2);
   }
@@ -502,8 +530,10 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void km_assign(KmArrays a, KmGeom g
     if (ntie) atomicAdd(&a.ties[t], ntie);
     if (nnear) atomicAdd(&a.nearc[t], nnear);
     a.jpart[blockIdx.x] = s;
-    a.pairs[blockIdx.x] += np;  // running totals over the classifications, one slot per workgroup
-    a.tests[blockIdx.x] += nt;
+    // running totals over the classifications, one slot per workgroup (atomic
+    // only so that the workgroup does not wait for the old values)
+    atomicAdd(&a.pairs[blockIdx.x], np);
+    atomicAdd(&a.tests[blockIdx.x], nt);
     if (blockIdx.x == 0) a.st->last_t = t;
   }
 }
@@ -520,16 +550,16 @@ __device__ double reduce_jpart(const double* __restrict__ jp, int n, int lane) {
 // order.  The points are taken SCAN_U at a time: load(p) for all of them
 // first (independent loads, in flight together), then use(v, p, i, j, k) in
 // the walk's order, so sums keep the order of a plain one-by-one walk.
-constexpr int SCAN_U = 4;
+constexpr int SCAN_U = 16;
 template <class L, class F>
 __device__ __forceinline__ void scan_bbox(const int* b, const KmGeom& g, int lane, L&& load, F&& use) {
   const int i0 = b[0], i1 = b[1], j0 = b[2], j1 = b[3], k0 = b[4], k1 = b[5];
   if (i0 > i1) return;
   const int ej = j1 - j0 + 1, ek = k1 - k0 + 1;
-  const int64_t nlines = (int64_t)(i1 - i0 + 1) * ej;
-  // this lane's n-th point: line q0 + n dq, offset kk + n dk within it
-  int64_t q0, dq;
-  int kk, dk, kspan;
+  const int nlines = (i1 - i0 + 1) * ej;  // (grid points < 2^31)
+  // this lane's points: lines q0, q0 + dq, ..., in each of them offsets kk,
+  // kk + 64, ... (kspan of them)
+  int q0, dq, kk, kspan;
   if (ek <= ISDF_WAVE) {
     const int lpp = ISDF_WAVE / ek;  // lines per pass
     const int lo = lane / ek;
@@ -537,34 +567,47 @@ __device__ __forceinline__ void scan_bbox(const int* b, const KmGeom& g, int lan
     q0 = lo;
     dq = lpp;
     kk = lane - lo * ek;
-    dk = 0;
     kspan = 1;
   } else {
     if (lane >= ek) return;
     q0 = 0;
     dq = 1;
     kk = lane;
-    dk = ISDF_WAVE;
-    kspan = (ek - lane + ISDF_WAVE - 1) / ISDF_WAVE;  // points of this lane per line
+    kspan = (ek - lane + ISDF_WAVE - 1) / ISDF_WAVE;
   }
-  const int64_t total = ((nlines - q0 + dq - 1) / dq) * kspan;
-  for (int64_t n0 = 0; n0 < total; n0 += SCAN_U) {
-    int64_t pp[SCAN_U];
+  if (q0 >= nlines) return;
+  const int total = ((nlines - q0 + dq - 1) / dq) * kspan;
+  // the next point is found by adding: a division per point and axis cost
+  // more than the loads (2048 clusters of a 64^3 grid: 22 us a round with
+  // 64-bit divisions and four loads in flight, 13 us this way)
+  const int di = dq / ej, dj = dq - di * ej;
+  int i = i0 + q0 / ej, j = j0 + q0 % ej, ks = 0, left = total;
+  while (left > 0) {
     int ii[SCAN_U], jj[SCAN_U], kq[SCAN_U];
+    int64_t pp[SCAN_U];
     decltype(load((int64_t)0)) v[SCAN_U];
 #pragma unroll
     for (int u = 0; u < SCAN_U; ++u) {
-      const int64_t n = n0 + u < total ? n0 + u : total - 1;  // past the end: repeat the last point
-      const int64_t q = q0 + (n / kspan) * dq;
-      ii[u] = i0 + (int)(q / ej);
-      jj[u] = j0 + (int)(q % ej);
-      kq[u] = k0 + kk + (int)(n % kspan) * dk;
-      pp[u] = ((int64_t)ii[u] * g.n1 + jj[u]) * g.n2 + kq[u];
-      v[u] = load(pp[u]);
+      ii[u] = i;
+      jj[u] = j;
+      kq[u] = k0 + kk + ks * ISDF_WAVE;
+      pp[u] = ((int64_t)i * g.n1 + j) * g.n2 + kq[u];
+      if (u + 1 < left && ++ks == kspan) {  // past the end: repeat the last point
+        ks = 0;
+        i += di;
+        j += dj;
+        if (j > j1) {
+          j -= ej;
+          ++i;
+        }
+      }
     }
 #pragma unroll
+    for (int u = 0; u < SCAN_U; ++u) v[u] = load(pp[u]);
+#pragma unroll
     for (int u = 0; u < SCAN_U; ++u)
-      if (n0 + u < total) use(v[u], pp[u], ii[u], jj[u], kq[u]);
+      if (u < left) use(v[u], pp[u], ii[u], jj[u], kq[u]);
+    left -= SCAN_U;
   }
 }
 
@@ -636,42 +679,60 @@ __device__ __forceinline__ int cell_of(double x, double y, double z, const KmGeo
 __global__ __launch_bounds__(BIN_THREADS) void km_bin(KmArrays a, KmGeom g, int K) {
   if (a.st->done) return;
   __shared__ int cnt[MAX_CELLS];
-  __shared__ int part[BIN_THREADS];
+  __shared__ int part[BIN_THREADS / ISDF_WAVE];
+  constexpr int KEEP = 2;  // centroids a thread keeps in registers between count and fill
   const int ncells = g.nc0 * g.nc1 * g.nc2;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & (ISDF_WAVE - 1), wv = tid / ISDF_WAVE;
+  double4 c[KEEP];
+  int at[KEEP];
+#pragma unroll
+  for (int u = 0; u < KEEP; ++u) {
+    const int m = tid + u * BIN_THREADS < K ? tid + u * BIN_THREADS : 0;
+    c[u] = make_double4(a.cent[3 * (int64_t)m], a.cent[3 * (int64_t)m + 1], a.cent[3 * (int64_t)m + 2], (double)m);
+  }
   for (int i = tid; i < ncells; i += BIN_THREADS) cnt[i] = 0;
   __syncthreads();
-  for (int m = tid; m < K; m += BIN_THREADS) {
-    const double* c = a.cent + 3 * (int64_t)m;
-    atomicAdd(&cnt[cell_of(c[0], c[1], c[2], g)], 1);
+#pragma unroll
+  for (int u = 0; u < KEEP; ++u) {
+    at[u] = cell_of(c[u].x, c[u].y, c[u].z, g);
+    if (tid + u * BIN_THREADS < K) atomicAdd(&cnt[at[u]], 1);
+  }
+  for (int m = tid + KEEP * BIN_THREADS; m < K; m += BIN_THREADS) {
+    const double* q = a.cent + 3 * (int64_t)m;
+    atomicAdd(&cnt[cell_of(q[0], q[1], q[2], g)], 1);
   }
   __syncthreads();
-  // exclusive scan: each thread its run of `per` cells, then the run totals
+  // exclusive scan: each thread its run of `per` cells, then the run totals,
+  // within wavefronts and over them
   const int per = (ncells + BIN_THREADS - 1) / BIN_THREADS;
-  const int b = tid * per, e = min(ncells, b + per);
+  const int b = min(ncells, tid * per), e = min(ncells, b + per);
   int run = 0;
   for (int i = b; i < e; ++i) run += cnt[i];
-  part[tid] = run;
-  __syncthreads();
-  for (int o = 1; o < BIN_THREADS; o <<= 1) {
-    const int v = tid >= o ? part[tid - o] : 0;
-    __syncthreads();
-    part[tid] += v;
-    __syncthreads();
+  int incl = run;
+#pragma unroll
+  for (int o = 1; o < ISDF_WAVE; o <<= 1) {
+    const int v = __shfl_up(incl, o, ISDF_WAVE);
+    if (lane >= o) incl += v;
   }
-  int off = part[tid] - run;
+  if (lane == ISDF_WAVE - 1) part[wv] = incl;
+  __syncthreads();
+  int off = incl - run;
+  for (int w = 0; w < wv; ++w) off += part[w];
   for (int i = b; i < e; ++i) {
-    const int c = cnt[i];
+    const int n = cnt[i];
     cnt[i] = off;  // becomes the fill cursor
     a.cell_start[i] = off;
-    off += c;
+    off += n;
   }
   if (tid == 0) a.cell_start[ncells] = K;
   __syncthreads();
-  for (int m = tid; m < K; m += BIN_THREADS) {
-    const double* c = a.cent + 3 * (int64_t)m;
-    const int pos = atomicAdd(&cnt[cell_of(c[0], c[1], c[2], g)], 1);
-    a.cell_c[pos] = make_double4(c[0], c[1], c[2], (double)m);
+#pragma unroll
+  for (int u = 0; u < KEEP; ++u)
+    if (tid + u * BIN_THREADS < K) a.cell_c[atomicAdd(&cnt[at[u]], 1)] = c[u];
+  for (int m = tid + KEEP * BIN_THREADS; m < K; m += BIN_THREADS) {
+    const double* q = a.cent + 3 * (int64_t)m;
+    const int pos = atomicAdd(&cnt[cell_of(q[0], q[1], q[2], g)], 1);
+    a.cell_c[pos] = make_double4(q[0], q[1], q[2], (double)m);
   }
 }
 
@@ -909,7 +970,7 @@ static int kmeans_enqueue(const isdf_grid* grid, isdf_dtype dt, const void* phi,
   for (int t = 0; t < max_iter; ++t) {
     hipLaunchKernelGGL(km_assign, dim3(nparts), dim3(ASSIGN_THREADS), 0, st, P.a, G, n_mu, t, near_tie_rel);
     hipLaunchKernelGGL(km_update, dim3(ublocks), dim3(256), 0, st, P.a, G, n_mu, t, nparts);
-    hipLaunchKernelGGL(km_bin, dim3(1), dim3(BIN_THREADS), 0, st, P.a, G, n_mu);
+    if (n_mu > KM_DIRECT) hipLaunchKernelGGL(km_bin, dim3(1), dim3(BIN_THREADS), 0, st, P.a, G, n_mu);
   }
   hipLaunchKernelGGL(km_assign, dim3(nparts), dim3(ASSIGN_THREADS), 0, st, P.a, G, n_mu, max_iter,
                      near_tie_rel);

@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import synth
 
 pytestmark = pytest.mark.gpu
@@ -60,3 +61,27 @@ def test_cholesky_names_the_failing_pivot(bad):
     phi[idx[bad]] = 0.0
     _, _, info = isdf.fit(dev(phi), None, dev(idx.astype(np.int32)), grid=(10, 11, 13), check=False)
     assert info["status"] == 1 and info["pivot"] == bad
+
+
+# planes of 8 columns in 512 and 1024 threads, of 2 and of 1, just too large
+# for LDS, with a factor 7 and with an axis of length 1 (both by lines); the
+# third axis's column groups of 32, 16 and 8; odd column counts and pitches
+@pytest.mark.parametrize("n", [(3, 16, 32), (4, 32, 32), (5, 64, 64), (2, 72, 72), (2, 9, 5), (2, 100, 90), (3, 14, 6),
+                               (3, 6, 14), (1, 24, 20), (6, 1, 20), (6, 20, 1), (160, 4, 6), (72, 3, 8), (20, 27, 25)])
+@pytest.mark.parametrize("n_mu,pad,cplx,single", [(37, 0, 0, 0), (18, 2, 0, 0), (35, 0, 1, 0), (70, 1, 0, 1),
+                                                  (66, 0, 1, 1)])
+def test_poisson_plane_edges(n, n_mu, pad, cplx, single):
+    """A transform of N points has a relative error of a few eps log2 N in the
+    2-norm; two of them and the multiplication stay below 16 eps log2 N (and
+    half an ulp of single-precision storage)."""
+    n_r = n[0] * n[1] * n[2]
+    rng = np.random.default_rng(n_r + n_mu)
+    x = rng.standard_normal((n_r, n_mu + pad))
+    if cplx:
+        x = x + 1j * rng.standard_normal(x.shape)
+    if single:
+        x = x.astype(np.complex64 if cplx else np.float32)
+    v = isdf.poisson(dev(x)[:, :n_mu], n).cpu().numpy()
+    ref = oracle.poisson(x[:, :n_mu].astype(np.complex128 if cplx else np.float64), n)
+    err = np.linalg.norm(v - ref) / max(np.linalg.norm(ref), 1e-300)
+    assert err <= 16 * EPS * np.log2(n_r) + (2.0 ** -24 if single else 0.0)

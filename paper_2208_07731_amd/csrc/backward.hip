@@ -525,6 +525,7 @@ struct BwdPlan {
   SplitWork sw;  // orbital-row and Gram right-hand-side planes (split precisions)
   AdjPlanes ap;  // Abar / Bbar and F planes (split precisions)
   ModWork mod;   // residues of the products with (C C^H)^-1 and (C C^H)^-2
+  ModWork mod1;  // of the real N1 x N1 ones around them (the same memory)
   int slots;     // workgroup slots the split factors were chosen for
   size_t bytes;
 };
@@ -578,9 +579,14 @@ static BwdPlan plan_bwd(void* ws, size_t cap, int64_t nr, int n_mu, int n_phi, i
   P.dA = c.take<double>((size_t)n_mu * 2 * n_mu);
   if (!aliased) P.dB = c.take<double>((size_t)n_mu * 2 * n_mu);
   P.T1 = c.take<double>((size_t)n_mu * 2 * nmax);
-  P.mod = carve_mod(c, rblock, n1, n1);
+  {
+    Carver c1 = c;
+    P.mod = carve_mod_for(c, rblock, n1, aliased);
+    P.mod1 = aliased ? P.mod : carve_mod(c1, n1, n1, n1);
+    if (c1.used > c.used) c = c1;
+  }
   size_t lp = (size_t)ceil_div(rblock, 32) * ceil_div(n1, 32);  // at the smallest tile
-  if (P.mod.mp) lp += (size_t)ceil_div(rblock, P.mod.mp) * (mod_crt_blocks<ModSAdj>(P.mod.mp, n1) + ceil_div(n1, 128));
+  if (P.mod.mp) lp += (size_t)ceil_div(rblock, P.mod.mp) * (mod_crt_blocks<ModSAdj>(P.mod.mp, P.mod.cplx ? n1 / 2 : n1) + ceil_div(n1, 128));
   P.lpart = c.take<double>(lp);
   P.sw = carve_split(c, prec, n_phi, n_psi, aliased, n_mu, rblock > n_mu ? rblock : n_mu);
   P.ap = carve_adj(c, prec, n_phi, n_psi, aliased, n_mu, rblock);
@@ -834,7 +840,7 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
                                                  P.ap.f_psi, P.ap.ldp, 2 * n_psi, sc ? sc + 3 : nullptr, s))
         return ISDF_E_HIP;
     }
-    if (!tbar && !nt_product<double>(n1, n1, n1, minv, n1, minv, n1, MOD_DIAG_B, P.W2, n1, 1.0, P.mod, false, ab, s))
+    if (!tbar && !nt_product<double>(n1, n1, n1, minv, n1, minv, n1, MOD_DIAG_B, P.W2, n1, 1.0, P.mod1, false, ab, s))
       return ISDF_E_HIP;  // (C C^H)^-2
   }  // BWD_BEGIN
   for (int64_t r = row_lo; r < row_hi; r += rblock) {
@@ -889,21 +895,22 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
                   SPLIT == SPLIT_FP16X3 ? P.amax + 4 : nullptr};
       Operand<double> a{Gb, n1, nullptr, nullptr}, b{P.W2, n1, nullptr, nullptr};
       int64_t ltiles = 0;
-      if (P.mod.mp && mod_pays(rows, n1, n1)) {
+      const int hc = P.mod.cplx ? 2 : 1;  // reals per entry of the residue product
+      if (P.mod.mp && (P.mod.cplx ? mod_pays_c(rows, n1 / 2, n1 / 2) : mod_pays(rows, n1, n1))) {
         // by residues, panel by panel; the FP64 kernel behind each panel runs
         // (and writes its loss partials, zero otherwise) only on a flag
         const ModWork& w = P.mod;
         const int64_t mp = w.mp, fp64 = ceil_div(rows, mp) * ceil_div(mp, 128) * ceil_div(n1, 128);
         if (!fill<double>(P.lpart, fp64, 0.0, s)) return ISDF_E_HIP;
         ltiles = fp64;
-        if (!mod_prepare(P.W2, n1, n1, n1, MOD_DIAG_B, P.W2, n1, w, ab, s)) return ISDF_E_HIP;
+        if (!mod_prepare(P.W2, n1, n1 / hc, n1 / hc, MOD_DIAG_B, P.W2, n1, w, ab, s)) return ISDF_E_HIP;
         for (int64_t q = 0, p = 0; q < rows; q += mp, ++p) {
           const int pr = (int)(rows - q < mp ? rows - q : mp);
           double *Aq = Ab + q * 2 * n_mu, *Bq = aliased ? nullptr : Bb + q * 2 * n_mu, *Gq = Gb + q * n1;
           ModSAdj me{Gq, n1, Aq, Bq, 2 * (int64_t)n_mu, g + r + q, n1, aliased ? 1 : 0,
                      n1 % 2 == 0 && (uintptr_t)Gq % 16 == 0, P.lpart + ltiles, epi.amax};
-          if (!mod_panel<double>(Gq, n1, pr, n1, n1, MOD_DIAG_B, (int)p, w, me, ab, s)) return ISDF_E_HIP;
-          ltiles += mod_crt_blocks<ModSAdj>(pr, n1);
+          if (!mod_panel<double>(Gq, n1, pr, n1 / hc, n1 / hc, MOD_DIAG_B, (int)p, w, me, ab, s)) return ISDF_E_HIP;
+          ltiles += mod_crt_blocks<ModSAdj>(pr, n1 / hc);
           EpiSAdj eq{Gq, n1, Aq, Bq, 2 * (int64_t)n_mu, g + r + q, pr, n1, aliased ? 1 : 0,
                      P.lpart + p * ceil_div(mp, 128) * ceil_div(n1, 128), epi.amax};
           Operand<double> aq{Gq, n1, nullptr, nullptr};
@@ -924,7 +931,7 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
         return ISDF_E_HIP;
       const int64_t ldt = aliased ? ld_tbar : 2 * ld_tbar;
       if (!nt_product<double, TT>(rows, n1, n1, tbar + (r - gbase) * ldt, ldt, minv, n1, MOD_DIAG_B, Gb, n1, 1.0, P.mod,
-                                  mod_pays(rows, n1, n1), ab, s))
+                                  true, ab, s))
         return ISDF_E_HIP;
       const TilePlan sp = sp_phi.h;
       const int64_t pn = (int64_t)n1 * n1;
@@ -960,9 +967,9 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
     // Theta^T S = 2 M^-1 H M^-2 with H = G^T diag(g) G
     if (!mirror(P.P, n1, ab, s)) return ISDF_E_HIP;
     // (all symmetric: (C C^H)^-2 H = (H (C C^H)^-2)^T is the second product's K-contiguous operand)
-    if (!nt_product<double>(n1, n1, n1, P.W2, n1, P.P, n1, MOD_DIAG_B, P.Ppart, n1, 1.0, P.mod, false, ab, s))
+    if (!nt_product<double>(n1, n1, n1, P.W2, n1, P.P, n1, MOD_DIAG_B, P.Ppart, n1, 1.0, P.mod1, false, ab, s))
       return ISDF_E_HIP;
-    if (!nt_product<double>(n1, n1, n1, minv, n1, P.Ppart, n1, MOD_DIAG_A, P.P, n1, 2.0, P.mod, false, ab, s))
+    if (!nt_product<double>(n1, n1, n1, minv, n1, P.Ppart, n1, MOD_DIAG_A, P.P, n1, 2.0, P.mod1, false, ab, s))
       return ISDF_E_HIP;
   }
   // Mbar terms at the interpolation rows

@@ -58,7 +58,7 @@ static FitPlan plan_fit(void* ws, size_t cap, int64_t nr, int n_mu, int n_phi, i
   P.inv.R = c.take<double>((size_t)n1 * n1);
   P.G = c.take<double>((size_t)rblock * n1);
   P.sw = carve_split(c, prec, n_phi, n_psi, aliased, n_mu, rblock > n_mu ? rblock : n_mu);
-  P.mod = carve_mod(c, rblock < nr ? rblock : nr, n1, n1);
+  P.mod = carve_mod_for(c, rblock < nr ? rblock : nr, n1, aliased);
   if (resid) {
     P.Th = c.take<double>((size_t)rblock * n1);
     P.part = c.take<double>((size_t)2 * RESID_BLOCKS * ceil_div(nr, rblock));
@@ -418,7 +418,7 @@ static int apply_minv(int32_t n_mu, int32_t aliased, const double* minv, const d
   ModWork w{};
   if (ws) {
     Carver c(ws, ws_bytes);
-    w = carve_mod(c, nrows, n1, n1);
+    w = carve_mod_for(c, nrows, n1, aliased != 0);
     if (!c.fits()) return ISDF_E_WORKSPACE;
   }
   hipStream_t s = (hipStream_t)stream;
@@ -439,7 +439,7 @@ extern "C" size_t isdf_apply_minv_workspace(int32_t n_mu, int32_t aliased, int64
   if (n_mu <= 0 || nrows <= 0) return 0;
   const int64_t n1 = aliased ? n_mu : 2 * (int64_t)n_mu;
   Carver c(nullptr, 0);
-  carve_mod(c, nrows, n1, n1);
+  carve_mod_for(c, nrows, n1, aliased != 0);
   return c.used;
 }
 

@@ -419,20 +419,23 @@ static bool dgemm(int M, int N, int64_t K, const TA* A, int64_t lda, const doubl
 // C = alpha A B^T in FP64, by residues where that is faster (mod_pays) and the
 // work buffers are there, else on the FP64 matrix cores.  bal: the symmetric
 // operand (of order K) whose diagonal balances the two.  `prepared`: B's
-// residues are in the buffers from an earlier call.
+// residues are in the buffers from an earlier call.  With complex buffers B
+// has to be the real 2 x 2 block form of a complex matrix, M, N, K count reals
+// all the same, and the product is the complex one of half N and K.
 template <class TC, class TA = double>
 static bool nt_product(int64_t M, int N, int K, const TA* A, int64_t lda, const double* B, int64_t ldb, int bal, TC* C,
                        int64_t ldc, double alpha, const ModWork& w, bool prepared, const int* abort, hipStream_t st) {
-  if (!w.mp || !mod_pays(M, N, K))
+  const int h = w.cplx ? 2 : 1;
+  if (!w.mp || !(w.cplx ? mod_pays_c(M, N / h, K / h) : mod_pays(M, N, K)))
     return dgemm<KC, KC, TC, TA>((int)M, N, K, A, lda, B, ldb, C, ldc, alpha, 0.0, 0, abort, st);
-  if (!prepared && !mod_prepare(B, ldb, N, K, bal, bal == MOD_DIAG_A ? (const double*)A : B,
+  if (!prepared && !mod_prepare(B, ldb, N / h, K / h, bal, bal == MOD_DIAG_A ? (const double*)A : B,
                                 bal == MOD_DIAG_A ? lda : ldb, w, abort, st))
     return false;
   const int vec = ldc % 2 == 0 && (uintptr_t)C % (2 * sizeof(TC)) == 0;
   for (int64_t r = 0, p = 0; r < M; r += w.mp, ++p) {
     const int rows = (int)(M - r < w.mp ? M - r : w.mp);
     ModStore<TC> epi{C + r * ldc, ldc, N, alpha, vec};
-    if (!mod_panel<TA>(A + r * lda, lda, rows, N, K, bal, (int)p, w, epi, abort, st)) return false;
+    if (!mod_panel<TA>(A + r * lda, lda, rows, N / h, K / h, bal, (int)p, w, epi, abort, st)) return false;
     if (!dgemm<KC, KC, TC, TA>(rows, N, K, A + r * lda, lda, B, ldb, C + r * ldc, ldc, alpha, 0.0, 0, abort, st,
                                w.flags, w.flags + 1 + p))
       return false;

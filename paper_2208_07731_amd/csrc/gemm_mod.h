@@ -82,6 +82,65 @@ constexpr ModTab make_mod_tab() {
 constexpr ModTab MOD_TAB = make_mod_tab();
 static __device__ __constant__ ModTab mod_tab = make_mod_tab();
 
+// Complex products: modulo p = 1 (mod 4) (or a product of such primes) there is
+// an s with s^2 = -1, and x + i y -> (x + s y, x - s y) turns the complex
+// product into two independent real ones instead of four, exactly.  16 such
+// moduli of at most 241 have the product 2^117.7; 32 planes against the 60 of
+// the real 2 x 2 block form.  Conjugation swaps the two planes.  108000 x 1201
+// x 1201 complex: 11.2 ms of int8 products in the real form, 6.9 this way, and
+// 1.9 and 1.1 for the split and the recombination.
+constexpr int MOD_NC = 16;
+
+struct ModTabC {
+  int p[MOD_NC];
+  int c14[MOD_NC];
+  float fp[MOD_NC], fip[MOD_NC];
+  float s[MOD_NC];   // a square root of -1
+  double dp[MOD_NC], ip[MOD_NC];
+  // weights of u + v (real part) and u - v (imaginary part), split as in ModTab
+  double w1r[MOD_NC], w2r[MOD_NC], w1i[MOD_NC], w2i[MOD_NC];
+  double P, Plo;
+};
+
+constexpr int mod_inverse(int a, int p) {
+  int q = 1;
+  while (q * a % p != 1) ++q;
+  return q;
+}
+
+constexpr ModTabC make_mod_tab_c() {
+  ModTabC t{};
+  const int p[MOD_NC] = {241, 233, 229, 221, 205, 197, 193, 181, 173, 157, 149, 137, 113, 109, 101, 97};
+  unsigned __int128 P = 1;
+  for (int i = 0; i < MOD_NC; ++i) P *= (unsigned)p[i];
+  for (int i = 0; i < MOD_NC; ++i) {
+    const int m = (int)((P / (unsigned)p[i]) % (unsigned)p[i]);
+    int s = 1;
+    while ((s * s + 1) % p[i] != 0) ++s;
+    const int q0 = mod_inverse(m, p[i]);
+    int qr = q0 * mod_inverse(2, p[i]) % p[i], qi = q0 * mod_inverse(2 * s % p[i], p[i]) % p[i];
+    if (2 * qr > p[i]) qr -= p[i];
+    if (2 * qi > p[i]) qi -= p[i];
+    const long long nr = (long long)qr * (1ll << 42), ni = (long long)qi * (1ll << 42);
+    t.p[i] = p[i];
+    t.c14[i] = 16384 % p[i] > p[i] / 2 ? 16384 % p[i] - p[i] : 16384 % p[i];
+    t.fp[i] = (float)p[i];
+    t.fip[i] = 1.0f / (float)p[i];
+    t.s[i] = (float)s;
+    t.dp[i] = p[i];
+    t.ip[i] = 1.0 / p[i];
+    t.w1r[i] = (double)(nr / p[i]) / (double)(1ll << 42);
+    t.w2r[i] = ((double)(nr % p[i]) / p[i]) / (double)(1ll << 42);
+    t.w1i[i] = (double)(ni / p[i]) / (double)(1ll << 42);
+    t.w2i[i] = ((double)(ni % p[i]) / p[i]) / (double)(1ll << 42);
+  }
+  t.P = (double)P;
+  t.Plo = (double)((__int128)P - (__int128)t.P);
+  return t;
+}
+constexpr ModTabC MOD_TAB_C = make_mod_tab_c();
+static __device__ __constant__ ModTabC mod_tab_c = make_mod_tab_c();
+
 typedef int i4v __attribute__((ext_vector_type(4)));
 typedef int i16v __attribute__((ext_vector_type(16)));
 
@@ -92,12 +151,13 @@ __device__ __forceinline__ bool mod_off(const int* abort, const int* bflag, cons
 
 // ------------------------------------------------------------------ scales
 // d[k] = 2^round(log2 sqrt(B(k, k))) and its reciprocal (1 where the diagonal
-// is not a normal positive number).
-__global__ void mod_diag(const double* __restrict__ B, int64_t ldb, int K, double* __restrict__ d,
+// is not a normal positive number); step 2: of the real 2 x 2 blocks of a
+// complex matrix.
+__global__ void mod_diag(const double* __restrict__ B, int64_t ldb, int K, int step, double* __restrict__ d,
                          double* __restrict__ di) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= K) return;
-  const double v = B[(int64_t)k * ldb + k];
+  const double v = B[(int64_t)k * step * (ldb + 1)];
   int e = 0;
   if (v > 1e-280 && v < 1e280) {
     frexp(v, &e);
@@ -123,6 +183,30 @@ __device__ __forceinline__ unsigned mod_byte(double x, double p, double ip) {
   const double r = fma(-__builtin_rint(x * ip), p, x);
   const double y = fma(-__builtin_rint(r * ip), p, r + 6755399441055744.0);  // + 1.5 2^52: integer in the low word
   return (unsigned)__double2loint(y) & 0xffu;
+}
+
+// Low bytes of four words.
+__device__ __forceinline__ unsigned mod_pack(unsigned a, unsigned b, unsigned c, unsigned d) {
+  return __builtin_amdgcn_perm(__builtin_amdgcn_perm(d, c, 0x0c0c0400u), __builtin_amdgcn_perm(b, a, 0x0c0c0400u),
+                               0x05040100u);
+}
+
+// The power of two that takes a row of squared 2-norm n2 to at most 2^MOD_BITS
+// (0 for a zero row); its reciprocal into *rscale; a row out of range (`some`:
+// not all zero) raises the flag.
+__device__ __forceinline__ double mod_scale(double n2, int some, int tid, double* rscale, int* flag) {
+  double up = 0.0, down = 0.0;
+  if (n2 > 1e-280 && n2 < 1e280) {
+    int e2 = 0;
+    frexp(n2, &e2);  // n2 < 2^e2
+    const int e = MOD_BITS - ((e2 + 1) >> 1);
+    up = ldexp(1.0, e);
+    down = ldexp(1.0, -e);
+  } else if (some) {
+    if (tid == 0) atomicOr(flag, 1);
+  }
+  if (tid == 0) *rscale = down;
+  return up;
 }
 
 template <class TS, int IT>
@@ -162,17 +246,7 @@ __global__ __launch_bounds__(256) void mod_split(const TS* __restrict__ X, int64
   if ((tid & 63) == 0) red[tid >> 6] = n2;
   const int some = __syncthreads_or(any);
   n2 = (red[0] + red[1]) + (red[2] + red[3]);
-  int e2 = 0;
-  double up = 0.0, down = 0.0;
-  if (n2 > 1e-280 && n2 < 1e280) {
-    frexp(n2, &e2);  // n2 < 2^e2
-    const int e = MOD_BITS - ((e2 + 1) >> 1);
-    up = ldexp(1.0, e);
-    down = ldexp(1.0, -e);
-  } else if (some) {
-    if (tid == 0) atomicOr(flag, 1);
-  }
-  if (tid == 0) rscale[row] = down;
+  const double up = mod_scale(n2, some, tid, rscale + row, flag);
   int8_t* o = out + row * kpad;
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
@@ -191,6 +265,79 @@ __global__ __launch_bounds__(256) void mod_split(const TS* __restrict__ X, int64
   }
 }
 
+// Row blockIdx.x of a complex X (K entries, real and imaginary parts side by
+// side, ld in reals), scaled by the 2-norm of its 2 K reals: planes
+// [2 MOD_NC][rows][kpad] of x + s y and x - s y modulo each modulus (`conj`:
+// the other way round).  x and y leave FP64 as remainders below 1.5 p, the
+// rest is exact in FP32 (|x + s y| < 2^15.3).
+template <class TS, int IT>
+__global__ __launch_bounds__(256) void mod_split_c(const TS* __restrict__ X, int64_t ld, int rows, int K, int kpad,
+                                                   const double* __restrict__ ks, int vec, int conj,
+                                                   int8_t* __restrict__ out, int64_t pstride,
+                                                   double* __restrict__ rscale, int* flag, const int* abort) {
+  if (abort && *abort) return;
+  __shared__ double red[256 / ISDF_WAVE];
+  const int tid = threadIdx.x;
+  const int64_t row = blockIdx.x;
+  const TS* x = X + row * ld;
+  double v[IT][8];
+  double n2 = 0.0;
+  bool any = false;
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int k = 4 * (tid + 256 * it);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      double a = 0.0, b = 0.0;
+      if (k + e < K) {
+        if (vec) {
+          load_pair<TS>(x + 2 * (k + e), a, b);
+        } else {
+          a = (double)x[2 * (k + e)];
+          b = (double)x[2 * (k + e) + 1];
+        }
+        if (ks) {
+          a *= ks[k + e];
+          b *= ks[k + e];
+        }
+      }
+      v[it][2 * e] = a;
+      v[it][2 * e + 1] = b;
+      n2 = fma(a, a, fma(b, b, n2));
+      any |= a != 0.0 || b != 0.0;  // true for NaN
+    }
+  }
+  n2 = wave_sum(n2);
+  if ((tid & 63) == 0) red[tid >> 6] = n2;
+  const int some = __syncthreads_or(any);
+  n2 = (red[0] + red[1]) + (red[2] + red[3]);
+  const double up = mod_scale(n2, some, tid, rscale + row, flag);
+  int8_t* o = out + row * kpad;
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int k = 4 * (tid + 256 * it);
+    if (k >= kpad) continue;
+    double s[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s[e] = __builtin_rint(v[it][e] * up);
+#pragma unroll
+    for (int i = 0; i < MOD_NC; ++i) {
+      unsigned wu[4], wv[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float rx = (float)fma(-__builtin_rint(s[2 * e] * MOD_TAB_C.ip[i]), MOD_TAB_C.dp[i], s[2 * e]);
+        const float ry = (float)fma(-__builtin_rint(s[2 * e + 1] * MOD_TAB_C.ip[i]), MOD_TAB_C.dp[i], s[2 * e + 1]);
+        const float u = fmaf(MOD_TAB_C.s[i], ry, rx), w = fmaf(-MOD_TAB_C.s[i], ry, rx);
+        // + 1.5 2^23: the integer in the low bits, a multiple of 256 beside it
+        wu[e] = __float_as_uint(fmaf(-__builtin_rintf(u * MOD_TAB_C.fip[i]), MOD_TAB_C.fp[i], u + 12582912.0f));
+        wv[e] = __float_as_uint(fmaf(-__builtin_rintf(w * MOD_TAB_C.fip[i]), MOD_TAB_C.fp[i], w + 12582912.0f));
+      }
+      *reinterpret_cast<unsigned*>(o + (2 * i + conj) * pstride + k) = mod_pack(wu[0], wu[1], wu[2], wu[3]);
+      *reinterpret_cast<unsigned*>(o + (2 * i + 1 - conj) * pstride + k) = mod_pack(wv[0], wv[1], wv[2], wv[3]);
+    }
+  }
+}
+
 // -------------------------------------------------------------------- GEMM
 // A word whose low byte is acc mod p in [-p/2, p/2] (the byte wraps for p =
 // 256): 14 low bits and the rest times 2^14 mod p give |t| <= 2^21 + 2^14,
@@ -203,14 +350,17 @@ __device__ __forceinline__ unsigned mod_reduce(int acc, int p, int c14, float fi
   const int q = __float_as_int(fmaf((float)t, fip, 12582912.0f));
   return (unsigned)(t - __mul24(q, p));
 }
-// Low bytes of four words.
-__device__ __forceinline__ unsigned mod_pack(unsigned a, unsigned b, unsigned c, unsigned d) {
-  return __builtin_amdgcn_perm(__builtin_amdgcn_perm(d, c, 0x0c0c0400u), __builtin_amdgcn_perm(b, a, 0x0c0c0400u),
-                               0x05040100u);
+// The same where |acc| <= 120^2 K, K <= MOD_KQUICK and p <= 241: the quotient
+// of the sum rounded to FP32 is off by at most 2 / p + 2^-7, so the remainder
+// is within 120.5 + 3.9 and still fits the byte.
+constexpr int MOD_KQUICK = 4096;
+__device__ __forceinline__ unsigned mod_reduce_quick(int acc, int p, float fip) {
+  const int q = __float_as_int(fmaf((float)acc, fip, 12582912.0f));
+  return (unsigned)(acc - __mul24(q, p));
 }
 
-// Residue planes of A B^T: R [MOD_N][M][ldr] from A [MOD_N][M][ld] and B
-// [MOD_N][N][ld] (ld a multiple of 128 bytes, ldr of 256).  256 x 256 tiles of
+// Residue planes of A B^T: R [planes][M][ldr] from A [planes][M][ld] and B
+// [planes][N][ld] (CPLX: two planes per modulus) (ld a multiple of 128 bytes, ldr of 256).  256 x 256 tiles of
 // eight wavefronts (128 x 64 each: 128 accumulator registers), 128-byte K
 // stages in two LDS buffers (128 KB, one workgroup per CU), the next stage
 // but one in flight in registers.  v_mfma_i32_32x32x32_i8 takes B's rows as
@@ -218,6 +368,7 @@ __device__ __forceinline__ unsigned mod_pack(unsigned a, unsigned b, unsigned c,
 // consecutive n of one m and leave as one word.  An LDS row is its 8 chunks of
 // 16 bytes at chunk ^ (row / 4 % 8): the 32 lanes of a fragment read (32
 // rows, one chunk) hit 32 different 16-byte slots of the 512-byte bank row.
+template <bool CPLX>
 __global__ __launch_bounds__(MOD_THREADS, 2) void mod_gemm(const int8_t* __restrict__ A, int64_t astride,
                                                            const int8_t* __restrict__ B, int64_t bstride, int ld, int M,
                                                            int N, int8_t* __restrict__ R, int64_t rstride, int ldr,
@@ -337,8 +488,9 @@ __global__ __launch_bounds__(MOD_THREADS, 2) void mod_gemm(const int8_t* __restr
   // residues to memory: a wave's 128 x 64 bytes through its own LDS rows (80
   // bytes apart), 16-byte stores of 64-byte row segments
   __syncthreads();
-  const int p = mod_tab.p[mod], c14 = mod_tab.c14[mod];
-  const float fip = mod_tab.fip[mod];
+  const int p = CPLX ? mod_tab_c.p[mod >> 1] : mod_tab.p[mod], c14 = CPLX ? mod_tab_c.c14[mod >> 1] : mod_tab.c14[mod];
+  const float fip = CPLX ? mod_tab_c.fip[mod >> 1] : mod_tab.fip[mod];
+  const bool quick = CPLX && ld <= MOD_KQUICK;
   int8_t* mine = smem + wv * 128 * 80;
 #pragma unroll
   for (int j = 0; j < 2; ++j)
@@ -348,7 +500,8 @@ __global__ __launch_bounds__(MOD_THREADS, 2) void mod_gemm(const int8_t* __restr
       for (int q = 0; q < 4; ++q) {
         unsigned w[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) w[e] = mod_reduce(acc[j][i][4 * q + e], p, c14, fip);
+        for (int e = 0; e < 4; ++e)
+          w[e] = quick ? mod_reduce_quick(acc[j][i][4 * q + e], p, fip) : mod_reduce(acc[j][i][4 * q + e], p, c14, fip);
         *reinterpret_cast<unsigned*>(mine + (i * 32 + (lane & 31)) * 80 + j * 32 + 8 * q + 4 * half) =
             mod_pack(w[0], w[1], w[2], w[3]);
       }
@@ -412,6 +565,63 @@ __global__ __launch_bounds__(256) void mod_crt(const int8_t* __restrict__ R, int
   epi.finish(sum);
 }
 
+// Complex outputs nu .. nu + 3 of row m, re and im side by side, from the
+// residues of u and v: u + v = 2 re, u - v = 2 s im (factors in the weights).
+__device__ __forceinline__ void mod_combine_c(const int8_t* __restrict__ R, int64_t rstride, double scale,
+                                              const double* __restrict__ cs, int nu, int N, double (&c)[8]) {
+  int u[MOD_NC], v[MOD_NC];
+#pragma unroll
+  for (int i = 0; i < MOD_NC; ++i) {
+    u[i] = *reinterpret_cast<const int*>(R + 2 * i * rstride);
+    v[i] = *reinterpret_cast<const int*>(R + (2 * i + 1) * rstride);
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    double h = 0.0, l = 0.0, hi = 0.0, li = 0.0;
+#pragma unroll
+    for (int i = 0; i < MOD_NC; ++i) {
+      const int a = (int8_t)(u[i] >> (8 * e)), b = (int8_t)(v[i] >> (8 * e));
+      const double p = (double)(a + b), q = (double)(a - b);
+      h = fma(p, MOD_TAB_C.w1r[i], h);
+      l = fma(p, MOD_TAB_C.w2r[i], l);
+      hi = fma(q, MOD_TAB_C.w1i[i], hi);
+      li = fma(q, MOD_TAB_C.w2i[i], li);
+    }
+    const double f = (h - __builtin_rint(h)) + l, g = (hi - __builtin_rint(hi)) + li;
+    const double t = scale * cs[nu + e < N ? nu + e : N - 1];
+    c[2 * e] = fma(f, MOD_TAB_C.P, f * MOD_TAB_C.Plo) * t;
+    c[2 * e + 1] = fma(g, MOD_TAB_C.P, g * MOD_TAB_C.Plo) * t;
+  }
+}
+
+// mod_crt for complex outputs: N complex columns, the epilogue sees pairs of
+// them as 4 reals of a row of 2 N.
+template <class Epi>
+__global__ __launch_bounds__(256) void mod_crt_c(const int8_t* __restrict__ R, int64_t rstride, int ldr, int M, int N,
+                                                 const double* __restrict__ rs, const double* __restrict__ cs,
+                                                 const int* abort, const int* bflag, const int* aflag, Epi epi) {
+  if (mod_off(abort, bflag, aflag)) {
+    epi.off();
+    return;
+  }
+  const int n4 = (N + 3) / 4;
+  const int64_t total = (int64_t)M * n4;
+  typename Epi::Sum sum{};
+#pragma unroll 1
+  for (int u = 0; u < Epi::REP; ++u) {
+    const int64_t e = ((int64_t)blockIdx.x * Epi::REP + u) * 256 + threadIdx.x;
+    if (e < total) {
+      const int m = (int)(e / n4), nu = 4 * (int)(e % n4);
+      double c[8];
+      mod_combine_c(R + (int64_t)m * ldr + nu, rstride, rs[m], cs, nu, N, c);
+      const double lo[4] = {c[0], c[1], c[2], c[3]}, up[4] = {c[4], c[5], c[6], c[7]};
+      epi(m, 2 * nu, lo, sum);
+      if (nu + 2 < N) epi(m, 2 * nu + 4, up, sum);
+    }
+  }
+  epi.finish(sum);
+}
+
 // C(m, n) = alpha c
 template <class TC>
 struct ModStore {
@@ -440,7 +650,8 @@ struct ModStore {
 
 // -------------------------------------------------------------------- host
 // Buffers of a product with up to `rows` rows of A per call, processed in
-// panels of `mp` rows (planes of a panel: 15 bytes per entry of A and of C).
+// panels of `mp` rows (planes of a panel: 15 bytes per entry of A and of C, 32
+// per complex one).
 struct ModWork {
   int8_t *a, *b, *r;
   double *ra, *rb, *d, *di;
@@ -448,9 +659,11 @@ struct ModWork {
   int nflags;
   int64_t mp;  // 0: no buffers
   int kpad, ldr;
+  int cplx;    // complex products
 };
 
 constexpr int64_t MOD_PANEL = 16384;
+constexpr int MOD_KMAX_C = 8192;  // entries of a complex row held in registers by mod_split_c
 
 // Whether residues beat the FP64 kernel: measured per M row and column, the
 // FP64 product takes 2 K N / 66 TFLOP/s and the residues 30 K N / 2.4 POP/s
@@ -459,10 +672,16 @@ constexpr int64_t MOD_PANEL = 16384;
 static bool mod_pays(int64_t M, int64_t N, int64_t K) {
   return M >= 2048 && K <= MOD_KMAX && K * N >= 512 * (K + N);
 }
+// The same for a complex product of N columns and K terms: 8 K N operations
+// against 64 K N and 48 K + 80 N bytes.
+static bool mod_pays_c(int64_t M, int64_t N, int64_t K) {
+  return M >= 2048 && K <= MOD_KMAX_C && K * N >= 160 * (K + N);
+}
 
-static ModWork carve_mod(Carver& c, int64_t rows, int64_t N, int64_t K) {
+static ModWork carve_planes(Carver& c, int64_t rows, int64_t N, int64_t K, int cplx) {
   ModWork w{};
-  if (!mod_pays(rows, N, K)) return w;
+  const int planes = cplx ? 2 * MOD_NC : MOD_N;
+  w.cplx = cplx;
   w.mp = rows < MOD_PANEL ? rows : MOD_PANEL;
   w.kpad = (int)ceil_div(K, MOD_BK) * MOD_BK;
   w.ldr = (int)ceil_div(N, MOD_T) * MOD_T;
@@ -472,26 +691,44 @@ static ModWork carve_mod(Carver& c, int64_t rows, int64_t N, int64_t K) {
   w.di = c.take<double>(K);
   w.ra = c.take<double>(w.mp);
   w.rb = c.take<double>(N);
-  w.b = c.take<int8_t>((size_t)MOD_N * N * w.kpad);
-  w.a = c.take<int8_t>((size_t)MOD_N * w.mp * w.kpad);
-  w.r = c.take<int8_t>((size_t)MOD_N * w.mp * w.ldr);
+  w.b = c.take<int8_t>((size_t)planes * N * w.kpad);
+  w.a = c.take<int8_t>((size_t)planes * w.mp * w.kpad);
+  w.r = c.take<int8_t>((size_t)planes * w.mp * w.ldr);
   return w;
 }
+static ModWork carve_mod(Carver& c, int64_t rows, int64_t N, int64_t K) {
+  return mod_pays(rows, N, K) ? carve_planes(c, rows, N, K, 0) : ModWork{};
+}
+static ModWork carve_mod_c(Carver& c, int64_t rows, int64_t N, int64_t K) {
+  return mod_pays_c(rows, N, K) ? carve_planes(c, rows, N, K, 1) : ModWork{};
+}
+// Buffers of the products with an N1 x N1 operand: complex ones of half the
+// order where the two orbital sets differ.
+static ModWork carve_mod_for(Carver& c, int64_t rows, int64_t n1, bool aliased) {
+  return aliased ? carve_mod(c, rows, n1, n1) : carve_mod_c(c, rows, n1 / 2, n1 / 2);
+}
 
+// Residues of the rows of X into planes `out`; complex rows when w.cplx.
 template <class TS>
-static bool mod_rows(const TS* X, int64_t ld, int rows, int K, int kpad, const double* ks, int8_t* out, double* rscale,
-                     int* flag, const int* abort, hipStream_t s) {
+static bool mod_rows(const TS* X, int64_t ld, int rows, int K, const ModWork& w, const double* ks, bool conj,
+                     int8_t* out, double* rscale, int* flag, const int* abort, hipStream_t s) {
   const int vec = ld % 2 == 0 && (uintptr_t)X % (2 * sizeof(TS)) == 0;
+  const int kpad = w.kpad;
   const int64_t ps = (int64_t)rows * kpad;
   const dim3 grid((unsigned)rows), block(256);
-  if (kpad <= 1024)
-    hipLaunchKernelGGL((mod_split<TS, 1>), grid, block, 0, s, X, ld, rows, K, kpad, ks, vec, out, ps, rscale, flag, abort);
-  else if (kpad <= 2048)
-    hipLaunchKernelGGL((mod_split<TS, 2>), grid, block, 0, s, X, ld, rows, K, kpad, ks, vec, out, ps, rscale, flag, abort);
-  else if (kpad <= 4096)
-    hipLaunchKernelGGL((mod_split<TS, 4>), grid, block, 0, s, X, ld, rows, K, kpad, ks, vec, out, ps, rscale, flag, abort);
-  else if (kpad <= 8192)
-    hipLaunchKernelGGL((mod_split<TS, 8>), grid, block, 0, s, X, ld, rows, K, kpad, ks, vec, out, ps, rscale, flag, abort);
+  const auto launch = [&](auto it) {
+    constexpr int IT = decltype(it)::value;
+    if (w.cplx)
+      hipLaunchKernelGGL((mod_split_c<TS, IT>), grid, block, 0, s, X, ld, rows, K, kpad, ks, vec, conj ? 1 : 0, out, ps,
+                         rscale, flag, abort);
+    else
+      hipLaunchKernelGGL((mod_split<TS, IT>), grid, block, 0, s, X, ld, rows, K, kpad, ks, vec, out, ps, rscale, flag,
+                         abort);
+  };
+  if (kpad <= 1024) launch(std::integral_constant<int, 1>());
+  else if (kpad <= 2048) launch(std::integral_constant<int, 2>());
+  else if (kpad <= 4096) launch(std::integral_constant<int, 4>());
+  else if (kpad <= 8192) launch(std::integral_constant<int, 8>());
   else
     hipLaunchKernelGGL((mod_split<TS, 16>), grid, block, 0, s, X, ld, rows, K, kpad, ks, vec, out, ps, rscale, flag,
                        abort);
@@ -502,14 +739,35 @@ static bool mod_rows(const TS* X, int64_t ld, int rows, int K, int kpad, const d
 // powers of two that are moved from it to the other.
 enum { MOD_PLAIN = 0, MOD_DIAG_A = 1, MOD_DIAG_B = 2 };
 
+// Raises the flag unless B (order 2 K) has the real 2 x 2 block form of a
+// complex Hermitian matrix, [[re, im], [-im, re]] per entry, to 2^-20 of the
+// diagonals' geometric mean (the rounding of a badly conditioned inverse stays
+// below; a general matrix does not and keeps the FP64 kernel).
+__global__ __launch_bounds__(256) void mod_blocks(const double* __restrict__ B, int64_t ldb, int K, int* flag) {
+  const int i = blockIdx.y;
+  const double* r0 = B + 2 * i * ldb;
+  const double* r1 = r0 + ldb;
+  const double di = r0[2 * i];
+  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < K; j += gridDim.x * blockDim.x) {
+    const double e = fabs(r0[2 * j] - r1[2 * j + 1]) + fabs(r0[2 * j + 1] + r1[2 * j]);
+    if (!(e <= 0x1p-20 * sqrt(fabs(di * B[2 * j * (ldb + 1)])))) atomicOr(flag, 1);
+  }
+}
+
 // Residues of B (N x K), once per call; dmat, ldd: the operand of `bal`.
+// Complex (w.cplx): B is the real 2 x 2 block form of a complex N x K matrix,
+// whose rows are the even ones, and the product is A B^H (bal = MOD_DIAG_B:
+// N = K, checked by mod_blocks).
 static bool mod_prepare(const double* B, int64_t ldb, int N, int K, int bal, const double* dmat, int64_t ldd,
                         const ModWork& w, const int* abort, hipStream_t s) {
+  const int step = w.cplx ? 2 : 1;
   hipLaunchKernelGGL(mod_clear, dim3(1), dim3(256), 0, s, w.flags, w.nflags);
   if (bal != MOD_PLAIN)
-    hipLaunchKernelGGL(mod_diag, dim3((unsigned)ceil_div(K, 256)), dim3(256), 0, s, dmat, ldd, K, w.d, w.di);
-  return mod_rows<double>(B, ldb, N, K, w.kpad, bal == MOD_PLAIN ? nullptr : bal == MOD_DIAG_B ? w.di : w.d, w.b, w.rb,
-                          w.flags, abort, s);
+    hipLaunchKernelGGL(mod_diag, dim3((unsigned)ceil_div(K, 256)), dim3(256), 0, s, dmat, ldd, K, step, w.d, w.di);
+  if (w.cplx && bal == MOD_DIAG_B)
+    hipLaunchKernelGGL(mod_blocks, dim3((unsigned)ceil_div(K, 1024), (unsigned)K), dim3(256), 0, s, B, ldb, K, w.flags);
+  return mod_rows<double>(B, step * ldb, N, K, w, bal == MOD_PLAIN ? nullptr : bal == MOD_DIAG_B ? w.di : w.d, true,
+                          w.b, w.rb, w.flags, abort, s);
 }
 
 template <class Epi>
@@ -518,21 +776,31 @@ static int64_t mod_crt_blocks(int64_t rows, int64_t N) {
 }
 
 // One panel (at most w.mp rows): residues of its rows of A, the residue
-// products, and the results through `epi`.
+// products, and the results through `epi`.  N, K in complex entries when
+// w.cplx.
 template <class TA, class Epi>
 static bool mod_panel(const TA* A, int64_t lda, int rows, int N, int K, int bal, int panel, const ModWork& w,
                       const Epi& epi, const int* abort, hipStream_t s) {
   int* aflag = w.flags + 1 + panel;
-  if (!mod_rows<TA>(A, lda, rows, K, w.kpad, bal == MOD_PLAIN ? nullptr : bal == MOD_DIAG_B ? w.d : w.di, w.a, w.ra,
+  if (!mod_rows<TA>(A, lda, rows, K, w, bal == MOD_PLAIN ? nullptr : bal == MOD_DIAG_B ? w.d : w.di, false, w.a, w.ra,
                     aflag, abort, s))
     return false;
   const int64_t tiles = ceil_div(rows, MOD_T) * ceil_div(N, MOD_T);
-  hipLaunchKernelGGL(mod_gemm, dim3((unsigned)(tiles * MOD_N)), dim3(MOD_THREADS), 0, s, (const int8_t*)w.a,
-                     (int64_t)rows * w.kpad, (const int8_t*)w.b, (int64_t)N * w.kpad, w.kpad, rows, N, w.r,
-                     (int64_t)rows * w.ldr, w.ldr, abort, (const int*)w.flags, (const int*)aflag);
-  hipLaunchKernelGGL((mod_crt<Epi>), dim3((unsigned)mod_crt_blocks<Epi>(rows, N)), dim3(256), 0, s,
-                     (const int8_t*)w.r, (int64_t)rows * w.ldr, w.ldr, rows, N, (const double*)w.ra,
-                     (const double*)w.rb, abort, (const int*)w.flags, (const int*)aflag, epi);
+  const dim3 grid((unsigned)(tiles * (w.cplx ? 2 * MOD_NC : MOD_N)));
+  const dim3 crt((unsigned)mod_crt_blocks<Epi>(rows, N));
+  const int64_t as = (int64_t)rows * w.kpad, bs = (int64_t)N * w.kpad, rs = (int64_t)rows * w.ldr;
+  const int8_t *a = w.a, *b = w.b, *r = w.r;
+  const int *bf = w.flags, *af = aflag;
+  const double *ra = w.ra, *rb = w.rb;
+  if (w.cplx) {
+    hipLaunchKernelGGL(mod_gemm<true>, grid, dim3(MOD_THREADS), 0, s, a, as, b, bs, w.kpad, rows, N, w.r, rs, w.ldr,
+                       abort, bf, af);
+    hipLaunchKernelGGL((mod_crt_c<Epi>), crt, dim3(256), 0, s, r, rs, w.ldr, rows, N, ra, rb, abort, bf, af, epi);
+  } else {
+    hipLaunchKernelGGL(mod_gemm<false>, grid, dim3(MOD_THREADS), 0, s, a, as, b, bs, w.kpad, rows, N, w.r, rs, w.ldr,
+                       abort, bf, af);
+    hipLaunchKernelGGL((mod_crt<Epi>), crt, dim3(256), 0, s, r, rs, w.ldr, rows, N, ra, rb, abort, bf, af, epi);
+  }
   return launch_ok();
 }
 

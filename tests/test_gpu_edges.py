@@ -85,3 +85,51 @@ def test_poisson_plane_edges(n, n_mu, pad, cplx, single):
     ref = oracle.poisson(x[:, :n_mu].astype(np.complex128 if cplx else np.float64), n)
     err = np.linalg.norm(v - ref) / max(np.linalg.norm(ref), 1e-300)
     assert err <= 16 * EPS * np.log2(n_r) + (2.0 ** -24 if single else 0.0)
+
+
+# 384 is the smallest order whose complex product takes the residues; 4096 and
+# 4097 terms are on the two sides of the quick remainder; 16384 rows are one panel
+@pytest.mark.parametrize("n_mu,rows,single,pad", [(384, 2048, 0, 0), (385, 2049, 0, 3), (601, 2305, 1, 0),
+                                                  (1201, 16384 + 65, 0, 2), (2049, 2050, 0, 1), (4097, 2048, 0, 0)])
+def test_complex_residue_product(n_mu, rows, single, pad):
+    """Theta = G (C C^H)^-1 for complex G.  The residue form rounds operands
+    scaled to 2^58: within sqrt(2 K) 2^-58 of the product of the row norms, plus
+    the rounding of the result; the FP64 reference is within 2 K eps of the sum
+    of moduli, itself below the product of the row norms."""
+    from paper_2208_07731_amd import _lib as L
+
+    lib = L.load()
+    gen = torch.Generator(device="cuda").manual_seed(n_mu)
+    rand = lambda *s: torch.randn(*s, dtype=torch.complex128, device="cuda", generator=gen)
+    d = 2.0 ** (16 * torch.rand(n_mu, dtype=torch.float64, device="cuda", generator=gen) - 8)
+    w = rand(n_mu, n_mu) / n_mu ** 0.5
+    w = (w + w.conj().T) / 2 + torch.diag(1 + torch.rand(n_mu, dtype=torch.float64, device="cuda", generator=gen))
+    w = d[:, None] * w * d
+    g = rand(rows, n_mu + pad) / torch.cat([d, torch.ones(pad, dtype=torch.float64, device="cuda")])
+    # rows (re, im) and (-im, re)
+    minv = torch.view_as_real(torch.stack([w, 1j * w], 1)).reshape(2 * n_mu, 2 * n_mu).contiguous()
+    size = lib.isdf_apply_minv_workspace(n_mu, 0, rows)
+    assert size > 0
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    dt = L.C64 if single else L.C128
+
+    def run(m, work):
+        out = torch.empty(rows, n_mu, dtype=torch.complex64 if single else torch.complex128, device="cuda")
+        assert lib.isdf_apply_minv_ws(n_mu, 0, m.data_ptr(), g.data_ptr(), 2 * g.stride(0), rows, dt, out.data_ptr(),
+                                      n_mu, work, size if work else 0, None) == L.OK
+        return out.to(torch.complex128)
+
+    got, fp64 = run(minv, ws.data_ptr()), run(minv, None)
+    a, b = g[:, :n_mu] * d, w / d  # the balanced operands, whose norms the rounding is relative to
+    bound = torch.outer(a.abs().square().sum(1).sqrt(), b.abs().square().sum(1).sqrt())
+    bar = (2 * n_mu * EPS + (2 * n_mu) ** 0.5 * 2.0 ** -58 + (2.0 ** -23 if single else 0.0)) * bound
+    assert torch.all((got - fp64).abs() <= bar)
+    if not single:
+        sample = torch.arange(0, rows, max(1, rows // 16), device="cuda")
+        exact = (g[sample, :n_mu].cpu().numpy().astype(np.clongdouble) @ w.cpu().numpy().astype(np.clongdouble))
+        e = lambda x: float(np.linalg.norm((x[sample].cpu().numpy() - exact).astype(np.complex128)) / np.linalg.norm(exact.astype(np.complex128)))
+        assert e(got) <= e(fp64)
+    # a matrix without the block form is multiplied as it is
+    odd = minv.clone()
+    odd[1, 0] += 0.01 * float(minv[0, 0])
+    assert torch.equal(run(odd, ws.data_ptr()), run(odd, None))

@@ -5,37 +5,87 @@
 //
 // with V'_mu = conj(V_mu) for V_mu the potential of the fit's Theta column
 // (eq. v2 expands phi_i* psi_j, the conjugate of the pair density the fit
-// interpolates).  Per r-block: A by the Gram engine (rows of A kept, no
-// Hadamard with a second block), A .*= conj(V) in place, then one real-form
-// GEMM with the packed Psi_mu, scaled by -1, into the caller's output.  FP64
-// arithmetic for either storage type.
+// interpolates).  Per r-block: conj(V) .* A by the Gram engine, then one
+// product with the packed Psi_mu (by residues where that is faster), scaled by
+// -1, into the caller's output.  FP64 results for either storage type.
 #include "fitlib.h"
 
 namespace isdf {
 namespace {
 
+// Gram epilogue: conj(V) .* A as interleaved complex rows, so that A itself is
+// never stored.  64^3, 2048 points, 256 orbitals: a pass of its own over A (24
+// bytes read and 16 written per entry) took 4.5 ms of 38.7 and the FP64 product
+// behind it 17.2; this epilogue costs nothing that can be told from the clock's
+// drift, and the residue product takes 12 (split 5.9, int8 products 5.3).
+// Multiplying by V as the rows are split instead: 8.0 for the split, 34.5 in all
+// against 32.8.
 template <class TS>
-__global__ void exch_hadamard(double* __restrict__ A, int rows, int n_mu, const TS* __restrict__ V, int64_t ld_v,
-                              int v_complex, int64_t r0, const int* abort) {
-  if (*abort) return;
-  const int64_t total = (int64_t)rows * n_mu;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t r = e / n_mu;
-    const int mu = (int)(e % n_mu);
-    double2 v;
-    if (v_complex) v = Cplx<TS>::load(V + 2 * ((r0 + r) * ld_v + mu));
-    else v = make_double2((double)V[(r0 + r) * ld_v + mu], 0.0);
-    double2* a = reinterpret_cast<double2*>(A) + e;
-    const double2 x = *a;
-    *a = make_double2(x.x * v.x + x.y * v.y, x.y * v.x - x.x * v.y);  // x conj(v)
+struct EpiExch {
+  double* out;
+  int64_t ldo;
+  const TS* V;  // row 0 of the block
+  int64_t ld_v;
+  int v_complex;
+  int M, n_mu;
+  // With V for all of a wave's tiles in flight the loads cost one latency instead
+  // of one per tile (22.0 -> 21.0 ms for the whole product at 64^3 x 2048).
+  template <class Cfg, bool CPLX, class Acc>
+  __device__ __forceinline__ void scaled(const Acc (&acc)[Cfg::MI][Cfg::NI], const TileAt& at) const {
+    constexpr int IG = CPLX ? 1 : Cfg::MI;  // rows of tiles in flight (complex V: twice the registers)
+#pragma unroll
+    for (int i0 = 0; i0 < Cfg::MI; i0 += IG) {
+      double v[IG][Cfg::NI / 2][4], w[CPLX ? IG : 1][Cfg::NI / 2][4];
+#pragma unroll
+      for (int i = 0; i < IG; ++i)
+#pragma unroll
+        for (int jp = 0; jp < Cfg::NI / 2; ++jp)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int nu = ((at.n_wave + 32 * jp) >> 5) * 16 + (at.lane & 15);
+            const int m = at.m_wave + (i0 + i) * 16 + Cfg::orow(at.lane, r);
+            const int64_t e = (int64_t)(m < M ? m : M - 1) * ld_v + (nu < n_mu ? nu : n_mu - 1);
+            if constexpr (CPLX) {
+              const double2 z = Cplx<TS>::load(V + 2 * e);
+              v[i][jp][r] = z.x;
+              w[i][jp][r] = z.y;
+            } else {
+              v[i][jp][r] = (double)V[e];
+            }
+          }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < IG; ++i)
+#pragma unroll
+        for (int jp = 0; jp < Cfg::NI / 2; ++jp)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int nu = ((at.n_wave + 32 * jp) >> 5) * 16 + (at.lane & 15);
+            const int m = at.m_wave + (i0 + i) * 16 + Cfg::orow(at.lane, r);
+            if (m >= M || nu >= n_mu) continue;
+            const double x = acc[i0 + i][2 * jp][r], y = acc[i0 + i][2 * jp + 1][r], a = v[i][jp][r];
+            double2 o = make_double2(a * x, a * y);
+            if constexpr (CPLX) {
+              const double c = w[i][jp][r];
+              o = make_double2(x * a + y * c, y * a - x * c);
+            }
+            *reinterpret_cast<double2*>(out + (int64_t)m * ldo + 2 * nu) = o;
+          }
+    }
   }
-}
+  template <class Cfg, class Acc>
+  __device__ __forceinline__ void apply(const Acc (&acc)[Cfg::MI][Cfg::NI], const TileAt& at) const {
+    if (v_complex) scaled<Cfg, true>(acc, at);
+    else scaled<Cfg, false>(acc, at);
+  }
+};
 
 struct ExchPlan {
   int* ab;
   double* Ephi;
   double* Fpsi;
   double* A;
+  ModWork mod;  // residues of the product with Psi_mu
   size_t bytes;
 };
 
@@ -47,6 +97,7 @@ static ExchPlan plan_exch(void* ws, size_t cap, int n_mu, int n_phi, int n_psi, 
   P.Ephi = c.take<double>((size_t)2 * nmu16 * 2 * n_phi);
   P.Fpsi = c.take<double>((size_t)2 * n_psi * 2 * n_mu);
   P.A = c.take<double>((size_t)rblock * 2 * n_mu);
+  P.mod = carve_mod_c(c, rblock, n_psi, n_mu);
   P.bytes = c.used;
   return P;
 }
@@ -69,16 +120,21 @@ static int exch_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const 
   const int64_t two_mu = 2 * (int64_t)n_mu;
   for (int64_t r = 0; r < nr; r += rblock) {
     const int rows = (int)(nr - r < rblock ? nr - r : rblock);
-    // A rows = Phi(r) Phi_mu^H (the Gram engine on Phi alone, A written, no G)
-    if (!gram<ISDF_P_FP64, TS>(phi, ld_phi, n_phi, phi, ld_phi, n_phi, true, P.Ephi, P.Ephi, nmu16, n_mu, nullptr, nr,
-                               r, rows, nullptr, 0, G_REAL, P.ab, s, nullptr, nullptr, P.A, nullptr))
-      return ISDF_E_HIP;
-    hipLaunchKernelGGL((exch_hadamard<TS>), dim3(grid_for((int64_t)rows * n_mu)), dim3(256), 0, s, P.A, rows, n_mu, V,
-                       ld_v, v_complex, r, (const int*)P.ab);
-    if (!launch_ok()) return ISDF_E_HIP;
-    // W rows = -(conj(V) .* A) Psi_mu
-    if (!tgemm<double, KC, KC>(rows, 2 * n_psi, two_mu, (const double*)P.A, two_mu, (const double*)P.Fpsi, two_mu,
-                               W + 2 * r * ld_w, 2 * ld_w, -1.0, 0.0, P.ab, s))
+    // conj(V) .* A, A rows = Phi(r) Phi_mu^H
+    EpiExch<TS> epi{P.A, two_mu, V + (v_complex ? 2 : 1) * r * ld_v, ld_v, v_complex, rows, n_mu};
+    Operand<TS> a{phi + 2 * r * ld_phi, 2 * ld_phi, nullptr, nullptr};
+    Operand<double> b{P.Ephi, 2 * (int64_t)n_phi, nullptr, nullptr};
+    const int64_t k = 2 * (int64_t)n_phi;
+    const bool ok = tile_for(rows, 2 * nmu16, 0) < 128
+                        ? launch_gemm<double, 64, 64, 16, 2, 2, TS, KC, double, KC, 1>(rows, 2 * nmu16, k, a, b, a, b, 0,
+                                                                                       epi, 0, P.ab, s)
+                        : launch_gemm<double, 128, 128, 16, 2, 2, TS, KC, double, KC, 1>(rows, 2 * nmu16, k, a, b, a, b,
+                                                                                         0, epi, 0, P.ab, s);
+    if (!ok) return ISDF_E_HIP;
+    // W rows = -(conj(V) .* A) Psi_mu; the even rows of the packed Psi_mu are the
+    // columns of conj(Psi_mu), so by residues it is the product with B^H
+    if (!nt_product<TS>(rows, 2 * n_psi, (int)two_mu, (const double*)P.A, two_mu, (const double*)P.Fpsi, two_mu,
+                        MOD_PLAIN, W + 2 * r * ld_w, 2 * ld_w, -1.0, P.mod, r > 0, P.ab, s))
       return ISDF_E_HIP;
   }
   return ISDF_OK;

@@ -133,3 +133,35 @@ def test_complex_residue_product(n_mu, rows, single, pad):
     odd = minv.clone()
     odd[1, 0] += 0.01 * float(minv[0, 0])
     assert torch.equal(run(odd, ws.data_ptr()), run(odd, None))
+
+
+# on both sides of the rule for residues (K N >= 160 (K + N)), a ragged last
+# block of rows, real and complex potentials, both storage types
+@pytest.mark.parametrize("n_mu,n_psi,v_complex,single,rblock", [(700, 210, 0, 0, None), (700, 200, 0, 0, None),
+                                                                (701, 211, 1, 0, 2049), (701, 333, 1, 1, None),
+                                                                (33, 7, 0, 0, 1000)])
+def test_exchange_edges(n_mu, n_psi, v_complex, single, rblock):
+    """Against complex extended-precision sums at sampled rows: FP64 products of
+    n_phi and n_mu terms are within 4 (n_phi + n_mu) eps of the sum of moduli,
+    residues within sqrt(2 n_mu) 2^-58 of the product of the row norms."""
+    n = (15, 16, 17)
+    n_r, n_phi = 15 * 16 * 17, 40
+    rng = np.random.default_rng(n_mu + n_psi)
+    c = lambda *s: rng.standard_normal(s) + 1j * rng.standard_normal(s)
+    store = np.complex64 if single else np.complex128
+    env = np.exp(-3 * rng.random((n_r, 1)))
+    phi, psi = (c(n_r, n_phi) * env).astype(store), (c(n_r, n_psi) * env).astype(store)
+    idx = rng.permutation(n_r)[:n_mu]
+    v = c(n_r, n_mu) if v_complex else rng.standard_normal((n_r, n_mu))
+    v = v.astype(store if v_complex else (np.float32 if single else np.float64))
+    got = isdf.exchange(dev(phi), dev(psi), dev(idx.astype(np.int32)), dev(v), rblock=rblock, grid=n).cpu().numpy()
+    rows = np.r_[0:n_r:97, n_r - 1]
+    x = lambda a: a.astype(np.clongdouble)
+    a = x(phi[rows]) @ x(phi[idx]).conj().T
+    w = x(v[rows]).conj() * a
+    ref = -(w @ x(psi[idx]))
+    moduli = (np.abs(v[rows]) * (np.abs(phi[rows]) @ np.abs(phi[idx]).T)) @ np.abs(psi[idx])
+    norms = np.outer(np.linalg.norm(w.astype(np.complex128), axis=1), np.linalg.norm(psi[idx], axis=0))
+    bar = 4 * (n_phi + n_mu) * EPS * moduli + (2 * n_mu) ** 0.5 * 2.0 ** -58 * norms
+    bar = bar + (2.0 ** -23 * np.abs(ref.astype(np.complex128)) if single else 0.0)
+    assert np.all(np.abs((got[rows] - ref).astype(np.complex128)) <= bar)

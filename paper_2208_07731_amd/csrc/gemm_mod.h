@@ -557,9 +557,10 @@ __global__ __launch_bounds__(256) void mod_crt(const int8_t* __restrict__ R, int
     const int64_t e = ((int64_t)blockIdx.x * Epi::REP + u) * 256 + threadIdx.x;
     if (e < total) {
       const int m = (int)(e / n4), n = 4 * (int)(e % n4);
+      const auto in = epi.load(m, n);
       double c[4];
       mod_combine(R + (int64_t)m * ldr + n, rstride, rs[m], cs, n, N, c);
-      epi(m, n, c, sum);
+      epi(m, n, c, in, sum);
     }
   }
   epi.finish(sum);
@@ -612,11 +613,12 @@ __global__ __launch_bounds__(256) void mod_crt_c(const int8_t* __restrict__ R, i
     const int64_t e = ((int64_t)blockIdx.x * Epi::REP + u) * 256 + threadIdx.x;
     if (e < total) {
       const int m = (int)(e / n4), nu = 4 * (int)(e % n4);
+      const auto in = epi.load(m, 2 * nu);
       double c[8];
       mod_combine_c(R + (int64_t)m * ldr + nu, rstride, rs[m], cs, nu, N, c);
       const double lo[4] = {c[0], c[1], c[2], c[3]}, up[4] = {c[4], c[5], c[6], c[7]};
-      epi(m, 2 * nu, lo, sum);
-      if (nu + 2 < N) epi(m, 2 * nu + 4, up, sum);
+      epi(m, 2 * nu, lo, in, sum);
+      if (nu + 2 < N) epi(m, 2 * nu + 4, up, epi.load(m, 2 * nu + 4), sum);
     }
   }
   epi.finish(sum);
@@ -632,7 +634,9 @@ struct ModStore {
   int N;
   double alpha;
   int vec;  // pairs of a row aligned
-  __device__ __forceinline__ void operator()(int m, int n, const double (&c)[4], Sum&) const {
+  struct In {};
+  __device__ __forceinline__ In load(int, int) const { return {}; }
+  __device__ __forceinline__ void operator()(int m, int n, const double (&c)[4], const In&, Sum&) const {
     TC* p = C + (int64_t)m * ldc + n;
     if (vec && n + 4 <= N) {
       typedef TC v2 __attribute__((ext_vector_type(2)));

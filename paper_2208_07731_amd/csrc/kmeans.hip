@@ -75,9 +75,10 @@ constexpr int KM_DIRECT = 512;
 // Squared distance with the same operation order as the definition
 // ((s0 dx^2 + s1 dy^2) + s2 dz^2); contraction off so that the value is the
 // correctly rounded result of each operation.
+template <bool ANISO>
 __device__ __forceinline__ double sqd(double dx, double dy, double dz, const KmGeom& g) {
 #pragma clang fp contract(off)
-  if (g.aniso) return (g.s0 * (dx * dx) + g.s1 * (dy * dy)) + g.s2 * (dz * dz);
+  if (ANISO) return (g.s0 * (dx * dx) + g.s1 * (dy * dy)) + g.s2 * (dz * dz);
   return (dx * dx + dy * dy) + dz * dz;
 }
 
@@ -197,6 +198,11 @@ __global__ void km_init(KmArrays a, const double* __restrict__ c0, int K, int T,
 constexpr int SURV = 128;  // per-wavefront survivor list
 static_assert(SURV <= CTILE / (ASSIGN_THREADS / ISDF_WAVE), "survivor coordinates fit a wave's tile slice");
 
+__device__ __forceinline__ double wave_max(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, ISDF_WAVE));
+  return v;
+}
 __device__ __forceinline__ double axis_lb(double c, double lo, double hi) {
   const double d = fmax(fmax(lo - c, c - hi), 0.0);
   return d * d;
@@ -206,6 +212,12 @@ __device__ __forceinline__ double axis_ub(double c, double lo, double hi) {
   return d * d;
 }
 
+// Bound by latency: every brick of the grid is resident at once (64^3: 512
+// workgroups), and a round is one pass through this code.  What keeps it short:
+// labels, weights and (few centroids) the tile are loaded before anything
+// waits; survivors are evaluated four at a time; one instance of each loop.
+// 24^3, 256 centroids 15.0 -> 10.8 us, 64^3, 2048 centroids 21.6 -> 17.7.
+template <bool ANISO>
 __global__ __launch_bounds__(ASSIGN_THREADS) void km_assign(KmArrays a, KmGeom g, int K, int t,
                                                             double near_rel) {
   if (a.st->done) return;
@@ -221,134 +233,142 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void km_assign(KmArrays a, KmGeom g
   const int64_t brick = (int64_t)blockIdx.x * (ASSIGN_THREADS / ISDF_WAVE) + wv;
   const int64_t nbricks = (int64_t)g.nb0 * g.nb1 * g.nb2;
   int bi = 0, bj = 0, bk = 0;
-  if (brick < nbricks) {
-    bk = (int)(brick % g.nb2);
-    int64_t q = brick / g.nb2;
-    bj = (int)(q % g.nb1);
-    bi = (int)(q / g.nb1);
+  if (brick < nbricks) {  // (grid points, so bricks too, are below 2^31)
+    const int q = (int)brick / g.nb2;
+    bk = (int)brick - q * g.nb2;
+    bi = q / g.nb1;
+    bj = q - bi * g.nb1;
   }
   const int pi = bi * 4 + (lane >> 4), pj = bj * 4 + ((lane >> 2) & 3), pk = bk * 4 + (lane & 3);
   const bool valid = brick < nbricks && pi < g.n0 && pj < g.n1 && pk < g.n2;
+  const int64_t p = ((int64_t)pi * g.n1 + pj) * g.n2 + pk;
+  // issued before anything waits: the point's weight and previous label
+  const double wp = valid ? a.w[p] : 0.0;
+  const int old = valid ? a.labels[p] : 0;
+  // one tile of centroids into LDS
+  auto stage = [&](int c0) {
+    const int cn = min(CTILE, K - c0);
+    __syncthreads();
+    for (int i = threadIdx.x; i < cn; i += ASSIGN_THREADS) {
+      cx[i] = a.cent[3 * (int64_t)(c0 + i) + 0];
+      cy[i] = a.cent[3 * (int64_t)(c0 + i) + 1];
+      cz[i] = a.cent[3 * (int64_t)(c0 + i) + 2];
+    }
+    __syncthreads();
+    return cn;
+  };
+  const bool direct = t == 0 || K <= KM_DIRECT;  // over every centroid, through the tiles
+  if (direct) stage(0);
   const double px = (double)pi, py = (double)pj, pz = (double)pk;
   // bounding box of the brick's grid points
   const double lo0 = bi * 4, lo1 = bj * 4, lo2 = bk * 4;
   const double hi0 = min(bi * 4 + 3, g.n0 - 1), hi1 = min(bj * 4 + 3, g.n1 - 1), hi2 = min(bk * 4 + 3, g.n2 - 1);
   const double margin = 1.0 + fmax(1e-5, 4.0 * near_rel);
+  // products with the metric weights, which are exactly 1 when !ANISO
+  auto metric = [&](double x, double y, double z) {
+    return ANISO ? (g.s0 * x + g.s1 * y) + g.s2 * z : (x + y) + z;
+  };
   int* list = surv[wv];
 
   double d1 = INFINITY, d2 = INFINITY;
   int lab = 0;
-  const int64_t p = ((int64_t)pi * g.n1 + pj) * g.n2 + pk;
   unsigned long long n_eval = 0, n_test = 0;  // survivors evaluated, bound tests (wave-uniform)
-  // issued before anything waits: the point's weight and previous label
-  const double wp = valid ? a.w[p] : 0.0;
-  const int old = valid ? a.labels[p] : 0;
+  // U of the brick
+  double U = INFINITY;
   if (t > 0) {
-    // few centroids: one in KM_DIRECT / 64 registers of a lane each, loaded
-    // while the labels arrive (past the end: centroid 0, not kept)
-    double4 mine[KM_DIRECT / ISDF_WAVE];
-    const bool direct = K <= KM_DIRECT;
-    if (direct) {
-#pragma unroll
-      for (int u = 0; u < KM_DIRECT / ISDF_WAVE; ++u) {
-        const int m = u * ISDF_WAVE + lane < K ? u * ISDF_WAVE + lane : 0;
-        mine[u] = make_double4(a.cent[3 * m], a.cent[3 * m + 1], a.cent[3 * m + 2], (double)m);
-      }
-    }
-    // U: the largest distance of a brick point to the centroid of the
+    // the largest distance of a brick point to the centroid of the
     // cluster it was given in the previous round, with the centroids as
     // they are now (just updated): a distance to a current centroid, so it
     // bounds every brick point's nearest distance
     double own = -INFINITY;
     if (valid) {
-      own = sqd(px - a.cent[3 * (int64_t)old], py - a.cent[3 * (int64_t)old + 1],
-                pz - a.cent[3 * (int64_t)old + 2], g);
+      const bool there = direct && K <= CTILE;
+      const double ox = there ? cx[old] : a.cent[3 * (int64_t)old], oy = there ? cy[old] : a.cent[3 * (int64_t)old + 1],
+                   oz = there ? cz[old] : a.cent[3 * (int64_t)old + 2];
+      own = sqd<ANISO>(px - ox, py - oy, pz - oz, g);
     }
+    U = wave_max(own);
+  } else {
+    // first round: the smallest over centroids of the farthest brick distance
+    for (int c0 = 0; c0 < K; c0 += CTILE) {
+      const int cn = c0 == 0 ? min(CTILE, K) : stage(c0);
+      for (int m = lane; m < cn; m += ISDF_WAVE)
+        U = fmin(U, metric(axis_ub(cx[m], lo0, hi0), axis_ub(cy[m], lo1, hi1), axis_ub(cz[m], lo2, hi2)));
+    }
+    U = -wave_max(-U);
+  }
+  const double cut = U * margin;
+  if (direct) {
+    // every tile's survivors in increasing index
+    for (int c0 = 0; c0 < K; c0 += CTILE) {
+      const int cn = K <= CTILE ? K : stage(c0);  // (a single tile is still in LDS)
+      int nlist = 0;
+      n_test += (unsigned long long)cn;
+      for (int mb = 0; mb < cn; mb += ISDF_WAVE) {
+        const int m = mb + lane;
+        bool keep = false;
+        if (m < cn)
+          keep = metric(axis_lb(cx[m], lo0, hi0), axis_lb(cy[m], lo1, hi1), axis_lb(cz[m], lo2, hi2)) <= cut;
+        const unsigned long long bal = __ballot(keep);
+        if (keep) list[nlist + __popcll(bal & ((1ull << lane) - 1ull))] = m;
+        nlist += __popcll(bal);
+        __builtin_amdgcn_wave_barrier();
+        if (nlist <= SURV - ISDF_WAVE && mb + ISDF_WAVE < cn) continue;
+        // the list is nearly full or complete: evaluate it, four at a time
+        // (their LDS reads and arithmetic overlap), compared in list order
+        for (int e = 0; e < nlist; e += 4) {
+          double d[4];
+          int mm[4];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) own = fmax(own, __shfl_xor(own, o, ISDF_WAVE));
-    const double cut = own * margin;
+          for (int u = 0; u < 4; ++u) {
+            mm[u] = list[e + u < nlist ? e + u : nlist - 1];
+            d[u] = sqd<ANISO>(px - cx[mm[u]], py - cy[mm[u]], pz - cz[mm[u]], g);
+            if (e + u >= nlist) d[u] = INFINITY;
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            d2 = fmin(d2, fmax(d[u], d1));
+            const bool better = d[u] < d1;
+            d1 = better ? d[u] : d1;
+            lab = better ? c0 + mm[u] : lab;
+          }
+        }
+        n_eval += (unsigned long long)nlist;
+        nlist = 0;
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+  } else {
     // a centroid with lb <= cut lies within sqrt(cut / s_a) of the brick on
     // every axis a, so only the cells of that box can hold one
     int c_lo[3], c_hi[3];
     const double lo[3] = {lo0, lo1, lo2}, hi[3] = {hi0, hi1, hi2}, sa[3] = {g.s0, g.s1, g.s2};
     const int nca[3] = {g.nc0, g.nc1, g.nc2};
+    const double inv_cell = 1.0 / g.cell, root = cut > 0.0 ? sqrt(cut) : 0.0;
     int nbox = 1;
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
-      const double r = cut > 0.0 ? sqrt(cut / sa[ax]) * (1.0 + 1e-12) + 1e-9 : 0.0;
-      c_lo[ax] = max(0, (int)floor((lo[ax] - r) / g.cell));
-      c_hi[ax] = min(nca[ax] - 1, (int)floor((hi[ax] + r) / g.cell));
+      // (1e-9 of slack, far more than the roundings of the root and the quotients)
+      const double r = cut > 0.0 ? (ANISO ? sqrt(cut / sa[ax]) : root) * (1.0 + 1e-12) + 1e-9 : 0.0;
+      c_lo[ax] = max(0, (int)floor((lo[ax] - r) * inv_cell - 1e-9));
+      c_hi[ax] = min(nca[ax] - 1, (int)floor((hi[ax] + r) * inv_cell + 1e-9));
       if (!(cut >= 0.0) || c_hi[ax] < c_lo[ax]) nbox = 0;  // no valid point in the brick
       else nbox *= c_hi[ax] - c_lo[ax] + 1;
     }
     const int e1 = c_hi[1] - c_lo[1] + 1, e2 = c_hi[2] - c_lo[2] + 1;
     int* cst = cellst[wv];
     int* cof = celloff[wv];
-    // survivors' coordinates: this wave's slice of the first round's tile arrays
+    // survivors' coordinates: this wave's slice of the tile arrays
     double* sx = cx + wv * (CTILE / (ASSIGN_THREADS / ISDF_WAVE));
     double* sy = cy + wv * (CTILE / (ASSIGN_THREADS / ISDF_WAVE));
     double* sz = cz + wv * (CTILE / (ASSIGN_THREADS / ISDF_WAVE));
     int nlist = 0;
-    // the listed centroids' distances, four at a time (their LDS reads and
-    // arithmetic overlap), compared in list order
-    auto evaluate = [&]() {
-      for (int e = 0; e < nlist; e += 4) {
-        double d[4];
-        int mm[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int at = e + u < nlist ? e + u : nlist - 1;
-          mm[u] = list[at];
-          d[u] = sqd(px - sx[at], py - sy[at], pz - sz[at], g);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          if (e + u >= nlist) continue;  // (wave-uniform)
-          const bool better = d[u] < d1 || (d[u] == d1 && mm[u] < lab);
-          d2 = better ? d1 : fmin(d2, d[u]);
-          d1 = better ? d[u] : d1;
-          lab = better ? mm[u] : lab;
-        }
-      }
-      n_eval += (unsigned long long)nlist;
-    };
-    // one candidate per lane: the survivors into this wave's list
-    auto take = [&](bool some, const double4& cand) {
-      const double lb = (g.s0 * axis_lb(cand.x, lo0, hi0) + g.s1 * axis_lb(cand.y, lo1, hi1)) +
-                        g.s2 * axis_lb(cand.z, lo2, hi2);
-      const bool keep = some && lb <= cut;
-      const unsigned long long bal = __ballot(keep);
-      const int cnt = __popcll(bal);
-      if (nlist + cnt > SURV) {  // (wave-uniform)
-        evaluate();
-        nlist = 0;
-        __builtin_amdgcn_wave_barrier();
-      }
-      if (keep) {
-        const int at = nlist + __popcll(bal & ((1ull << lane) - 1ull));
-        list[at] = (int)cand.w;
-        sx[at] = cand.x;
-        sy[at] = cand.y;
-        sz[at] = cand.z;
-      }
-      nlist += cnt;
-      __builtin_amdgcn_wave_barrier();
-    };
-    if (direct) {
-      if (nbox > 0) {
-#pragma unroll
-        for (int u = 0; u < KM_DIRECT / ISDF_WAVE; ++u)
-          if (u * ISDF_WAVE < K) take(u * ISDF_WAVE + lane < K, mine[u]);
-        n_test += (unsigned long long)K;
-      }
-      nbox = 0;
-    }
     for (int b0 = 0; b0 < nbox; b0 += ISDF_WAVE) {
       // one cell of the box per lane: its first entry and its count
       const int q = b0 + lane;
       int cs = 0, cn = 0;
       if (q < nbox) {
-        const int qk = q % e2, qj = (q / e2) % e1, qi = q / (e1 * e2);
+        const int qj0 = q / e2, qk = q - qj0 * e2, qi = qj0 / e1, qj = qj0 - qi * e1;
         const int cell = ((c_lo[0] + qi) * g.nc1 + (c_lo[1] + qj)) * g.nc2 + (c_lo[2] + qk);
         cs = a.cell_start[cell];
         cn = a.cell_start[cell + 1] - cs;
@@ -359,7 +379,7 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void km_assign(KmArrays a, KmGeom g
         const int v = __shfl_up(incl, o, ISDF_WAVE);
         if (lane >= o) incl += v;
       }
-      const int total = __shfl(incl, ISDF_WAVE - 1, ISDF_WAVE);
+      const int total = __builtin_amdgcn_readlane(incl, ISDF_WAVE - 1);
       const int ncell = min(ISDF_WAVE, nbox - b0);
       cst[lane] = cs;
       cof[lane] = incl - cn;
@@ -367,6 +387,7 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void km_assign(KmArrays a, KmGeom g
       for (int c0 = 0; c0 < total; c0 += ISDF_WAVE) {
         const int qq = c0 + lane;
         double4 cand = make_double4(0.0, 0.0, 0.0, 0.0);
+        bool keep = false;
         if (qq < total) {
           int lo_i = 0, hi_i = ncell - 1;  // last cell lane whose offset <= qq
           while (lo_i < hi_i) {
@@ -375,81 +396,54 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void km_assign(KmArrays a, KmGeom g
             else hi_i = mid - 1;
           }
           cand = a.cell_c[cst[lo_i] + (qq - cof[lo_i])];
+          keep = metric(axis_lb(cand.x, lo0, hi0), axis_lb(cand.y, lo1, hi1), axis_lb(cand.z, lo2, hi2)) <= cut;
         }
         n_test += (unsigned long long)min(ISDF_WAVE, total - c0);
-        take(qq < total, cand);
+        const unsigned long long bal = __ballot(keep);
+        if (keep) {  // survivor: its index and coordinates into this wave's list
+          const int at = nlist + __popcll(bal & ((1ull << lane) - 1ull));
+          list[at] = (int)cand.w;
+          sx[at] = cand.x;
+          sy[at] = cand.y;
+          sz[at] = cand.z;
+        }
+        nlist += __popcll(bal);
+        __builtin_amdgcn_wave_barrier();
+        const bool ended = c0 + ISDF_WAVE >= total && b0 + ISDF_WAVE >= nbox;
+        if (nlist <= SURV - ISDF_WAVE && !ended) continue;
+        for (int e = 0; e < nlist; e += 4) {  // as above, lowest index on equal distances
+          double d[4];
+          int mm[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int at = e + u < nlist ? e + u : nlist - 1;
+            mm[u] = list[at];
+            d[u] = sqd<ANISO>(px - sx[at], py - sy[at], pz - sz[at], g);
+            if (e + u >= nlist) d[u] = INFINITY;
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            d2 = fmin(d2, fmax(d[u], d1));
+            const bool better = d[u] < d1 || (d[u] == d1 && mm[u] < lab && d[u] < INFINITY);
+            d1 = better ? d[u] : d1;
+            lab = better ? mm[u] : lab;
+          }
+        }
+        n_eval += (unsigned long long)nlist;
+        nlist = 0;
+        __builtin_amdgcn_wave_barrier();
       }
       __builtin_amdgcn_wave_barrier();
     }
-    evaluate();
-  } else {
-    // first round: U = the smallest over centroids of the farthest brick
-    // distance, then every centroid tile's survivors in increasing index
-    double U = INFINITY;
-    for (int c0 = 0; c0 < K; c0 += CTILE) {
-      const int cn = min(CTILE, K - c0);
-      __syncthreads();
-      for (int i = threadIdx.x; i < cn; i += ASSIGN_THREADS) {
-        cx[i] = a.cent[3 * (int64_t)(c0 + i) + 0];
-        cy[i] = a.cent[3 * (int64_t)(c0 + i) + 1];
-        cz[i] = a.cent[3 * (int64_t)(c0 + i) + 2];
-      }
-      __syncthreads();
-      for (int m = lane; m < cn; m += ISDF_WAVE) {
-        const double ub = (g.s0 * axis_ub(cx[m], lo0, hi0) + g.s1 * axis_ub(cy[m], lo1, hi1)) +
-                          g.s2 * axis_ub(cz[m], lo2, hi2);
-        U = fmin(U, ub);
-      }
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) U = fmin(U, __shfl_xor(U, o, ISDF_WAVE));
-    const double cut = U * margin;
-    const bool one_tile = K <= CTILE;  // the tile is still in LDS
-    for (int c0 = 0; c0 < K; c0 += CTILE) {
-      const int cn = min(CTILE, K - c0);
-      if (!one_tile) {
-        __syncthreads();
-        for (int i = threadIdx.x; i < cn; i += ASSIGN_THREADS) {
-          cx[i] = a.cent[3 * (int64_t)(c0 + i) + 0];
-          cy[i] = a.cent[3 * (int64_t)(c0 + i) + 1];
-          cz[i] = a.cent[3 * (int64_t)(c0 + i) + 2];
-        }
-        __syncthreads();
-      }
-      int nlist = 0;
-      n_test += (unsigned long long)cn;
-      for (int mb = 0; mb < cn; mb += ISDF_WAVE) {
-        const int m = mb + lane;
-        bool keep = false;
-        if (m < cn) {
-          const double lb = (g.s0 * axis_lb(cx[m], lo0, hi0) + g.s1 * axis_lb(cy[m], lo1, hi1)) +
-                            g.s2 * axis_lb(cz[m], lo2, hi2);
-          keep = lb <= cut;
-        }
-        const unsigned long long bal = __ballot(keep);
-        const int cnt = __popcll(bal);
-        if (nlist + cnt > SURV) {  // flush the list (wave-uniform)
-          for (int q = 0; q < nlist; ++q) {
-            const int mm = list[q];
-            const double d = sqd(px - cx[mm], py - cy[mm], pz - cz[mm], g);
-            d2 = fmin(d2, fmax(d, d1));
-            const bool better = d < d1;
-            d1 = better ? d : d1;
-            lab = better ? c0 + mm : lab;
-          }
-          n_eval += (unsigned long long)nlist;
-          nlist = 0;
-        }
-        if (keep) list[nlist + __popcll(bal & ((1ull << lane) - 1ull))] = m;
-        nlist += cnt;
-      }
-      for (int q = 0; q < nlist; ++q) {
-        const int mm = list[q];
-        const double d = sqd(px - cx[mm], py - cy[mm], pz - cz[mm], g);
+    // (the last candidates may have been in an earlier cell box than the last)
+    if (nlist > 0) {
+      for (int e = 0; e < nlist; ++e) {
+        const int m = list[e];
+        const double d = sqd<ANISO>(px - sx[e], py - sy[e], pz - sz[e], g);
         d2 = fmin(d2, fmax(d, d1));
-        const bool better = d < d1;
+        const bool better = d < d1 || (d == d1 && m < lab);
         d1 = better ? d : d1;
-        lab = better ? c0 + mm : lab;
+        lab = better ? m : lab;
       }
       n_eval += (unsigned long long)nlist;
     }
@@ -486,30 +480,21 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void km_assign(KmArrays a, KmGeom g
   // scalar bit operations.
   unsigned long long act = __ballot(valid);
   while (act) {
-    const int leader = __ffsll((long long)act) - 1;
-    const int L = __shfl(lab, leader, ISDF_WAVE);
+    const int L = __builtin_amdgcn_readlane(lab, __ffsll((long long)act) - 1);
     const unsigned long long mm = __ballot(valid && lab == L);
-    if (lane == leader) {
-      int i_lo = 4, i_hi = -1, j_lo = 4, j_hi = -1, k_lo = 4, k_hi = -1;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if ((mm >> (16 * q)) & 0xFFFFull) {
-          i_lo = min(i_lo, q);
-          i_hi = max(i_hi, q);
-        }
-        if (mm & (0x000F000F000F000Full << (4 * q))) {
-          j_lo = min(j_lo, q);
-          j_hi = max(j_hi, q);
-        }
-        if (mm & (0x1111111111111111ull << q)) {
-          k_lo = min(k_lo, q);
-          k_hi = max(k_hi, q);
-        }
-      }
-      int* b = a.bbox + 6 * (int64_t)L;
-      atomicMin(b + 0, bi * 4 + i_lo); atomicMax(b + 1, bi * 4 + i_hi);
-      atomicMin(b + 2, bj * 4 + j_lo); atomicMax(b + 3, bj * 4 + j_hi);
-      atomicMin(b + 4, bk * 4 + k_lo); atomicMax(b + 5, bk * 4 + k_hi);
+    // (wave-uniform) the mask folded onto (j, k) and onto k
+    unsigned jk = (unsigned)mm | (unsigned)(mm >> 32);
+    jk = (jk | jk >> 16) & 0xFFFFu;
+    unsigned k4 = jk | jk >> 8;
+    k4 = (k4 | k4 >> 4) & 0xFu;
+    const int e[6] = {bi * 4 + ((__ffsll((long long)mm) - 1) >> 4), bi * 4 + ((63 - __clzll((long long)mm)) >> 4),
+                      bj * 4 + ((__ffs((int)jk) - 1) >> 2),        bj * 4 + ((31 - __clz((int)jk)) >> 2),
+                      bk * 4 + (__ffs((int)k4) - 1),               bk * 4 + (31 - __clz((int)k4))};
+    if (lane < 6) {
+      const int v = lane == 0 ? e[0] : lane == 1 ? e[1] : lane == 2 ? e[2] : lane == 3 ? e[3] : lane == 4 ? e[4] : e[5];
+      int* b = a.bbox + 6 * (int64_t)L + lane;
+      if (lane & 1) atomicMax(b, v);
+      else atomicMin(b, v);
     }
     act &= ~mm;
   }
@@ -753,7 +738,8 @@ __global__ __launch_bounds__(256) void km_snap(KmArrays a, KmGeom g, int K, int3
       a.bbox + 6 * (int64_t)mu, g, lane, [&](int64_t p) { return a.labels[p]; },
       [&](int lab, int64_t p, int i, int j, int k) {
         if (lab == mu) {
-          double d = sqd((double)i - cxm, (double)j - cym, (double)k - czm, g);
+          const double dx = (double)i - cxm, dy = (double)j - cym, dz = (double)k - czm;
+          const double d = g.aniso ? sqd<true>(dx, dy, dz, g) : sqd<false>(dx, dy, dz, g);
           if (d < bd || (d == bd && p < bp)) {
             bd = d;
             bp = p;
@@ -967,13 +953,18 @@ static int kmeans_enqueue(const isdf_grid* grid, isdf_dtype dt, const void* phi,
     if (!launch_ok()) return ISDF_E_HIP;
   }
   const int ublocks = (int)ceil_div(n_mu, 4);
+  const auto assign = [&](int t) {
+    if (G.aniso)
+      hipLaunchKernelGGL(km_assign<true>, dim3(nparts), dim3(ASSIGN_THREADS), 0, st, P.a, G, n_mu, t, near_tie_rel);
+    else
+      hipLaunchKernelGGL(km_assign<false>, dim3(nparts), dim3(ASSIGN_THREADS), 0, st, P.a, G, n_mu, t, near_tie_rel);
+  };
   for (int t = 0; t < max_iter; ++t) {
-    hipLaunchKernelGGL(km_assign, dim3(nparts), dim3(ASSIGN_THREADS), 0, st, P.a, G, n_mu, t, near_tie_rel);
+    assign(t);
     hipLaunchKernelGGL(km_update, dim3(ublocks), dim3(256), 0, st, P.a, G, n_mu, t, nparts);
     if (n_mu > KM_DIRECT) hipLaunchKernelGGL(km_bin, dim3(1), dim3(BIN_THREADS), 0, st, P.a, G, n_mu);
   }
-  hipLaunchKernelGGL(km_assign, dim3(nparts), dim3(ASSIGN_THREADS), 0, st, P.a, G, n_mu, max_iter,
-                     near_tie_rel);
+  assign(max_iter);
   hipLaunchKernelGGL(km_snap, dim3(ublocks), dim3(256), 0, st, P.a, G, n_mu, idx);
   hipLaunchKernelGGL(km_final, dim3(1), dim3(64), 0, st, P.a, nparts, info, objective, max_iter);
   if (!launch_ok()) return ISDF_E_HIP;

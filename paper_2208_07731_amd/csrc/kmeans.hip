@@ -62,15 +62,19 @@ struct KmGeom {
   int aniso;
   int cell;           // edge of a centroid cell in grid points
   int nc0, nc1, nc2;  // cells per axis
+  int direct;         // few centroids: no cells
 };
 
 constexpr int ASSIGN_THREADS = 512;  // 8 wavefronts = 8 bricks
 constexpr int CTILE = 2048;          // centroids staged per LDS tile
 constexpr int MAX_CELLS = 8192;      // centroid cells (counted in LDS by km_bin)
 constexpr int BIN_THREADS = 1024;
-// Up to this many centroids each brick tests all of them (at most 8 tests a
-// lane, and no wait for cells): km_bin is then not launched.
-constexpr int KM_DIRECT = 512;
+// Up to this many bound tests (bricks times centroids, the centroids in one LDS
+// tile) each brick tests all of them from LDS and km_bin is not launched: a test
+// costs less than waiting for the cells and their sort.  30 rounds, all / cells:
+// 40^3, 800 centroids (0.8 M) 690 / 861 us, 64^3, 1500 (6.1 M) 996 / 1100, 64^3,
+// 2048 (8.4 M) 1046 / 1128, 72^3, 2048 (11.9 M) 1408 / 1381.
+constexpr int64_t KM_DIRECT = 10000000;
 
 // Squared distance with the same operation order as the definition
 // ((s0 dx^2 + s1 dy^2) + s2 dz^2); contraction off so that the value is the
@@ -257,7 +261,7 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void km_assign(KmArrays a, KmGeom g
     __syncthreads();
     return cn;
   };
-  const bool direct = t == 0 || K <= KM_DIRECT;  // over every centroid, through the tiles
+  const bool direct = t == 0 || g.direct;  // over every centroid, through the tiles
   if (direct) stage(0);
   const double px = (double)pi, py = (double)pj, pz = (double)pk;
   // bounding box of the brick's grid points
@@ -282,7 +286,7 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void km_assign(KmArrays a, KmGeom g
     // bounds every brick point's nearest distance
     double own = -INFINITY;
     if (valid) {
-      const bool there = direct && K <= CTILE;
+      const bool there = direct;  // (t > 0: one tile)
       const double ox = there ? cx[old] : a.cent[3 * (int64_t)old], oy = there ? cy[old] : a.cent[3 * (int64_t)old + 1],
                    oz = there ? cz[old] : a.cent[3 * (int64_t)old + 2];
       own = sqd<ANISO>(px - ox, py - oy, pz - oz, g);
@@ -846,7 +850,7 @@ static KmGeom make_geom(const isdf_grid* g) {
   return G;
 }
 
-// Centroid cells: about two centroids per cell (edge ~ (2 N_r / K)^(1/3)
+// How the later rounds find centroids near a brick.  Centroid cells: about two centroids per cell (edge ~ (2 N_r / K)^(1/3)
 // grid points), at most MAX_CELLS of them.
 static void set_cells(KmGeom& G, int K) {
   const double nr = (double)G.n0 * G.n1 * G.n2;
@@ -860,6 +864,7 @@ static void set_cells(KmGeom& G, int K) {
   G.nc0 = (int)ceil_div(G.n0, e);
   G.nc1 = (int)ceil_div(G.n1, e);
   G.nc2 = (int)ceil_div(G.n2, e);
+  G.direct = K <= CTILE && (int64_t)G.nb0 * G.nb1 * G.nb2 * K <= KM_DIRECT;
 }
 
 static int assign_blocks(const KmGeom& G) {
@@ -962,7 +967,7 @@ static int kmeans_enqueue(const isdf_grid* grid, isdf_dtype dt, const void* phi,
   for (int t = 0; t < max_iter; ++t) {
     assign(t);
     hipLaunchKernelGGL(km_update, dim3(ublocks), dim3(256), 0, st, P.a, G, n_mu, t, nparts);
-    if (n_mu > KM_DIRECT) hipLaunchKernelGGL(km_bin, dim3(1), dim3(BIN_THREADS), 0, st, P.a, G, n_mu);
+    if (!G.direct) hipLaunchKernelGGL(km_bin, dim3(1), dim3(BIN_THREADS), 0, st, P.a, G, n_mu);
   }
   assign(max_iter);
   hipLaunchKernelGGL(km_snap, dim3(ublocks), dim3(256), 0, st, P.a, G, n_mu, idx);

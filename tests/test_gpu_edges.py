@@ -165,3 +165,23 @@ def test_exchange_edges(n_mu, n_psi, v_complex, single, rblock):
     bar = 4 * (n_phi + n_mu) * EPS * moduli + (2 * n_mu) ** 0.5 * 2.0 ** -58 * norms
     bar = bar + (2.0 ** -23 * np.abs(ref.astype(np.complex128)) if single else 0.0)
     assert np.all(np.abs((got[rows] - ref).astype(np.complex128)) <= bar)
+
+
+# all centroids per brick (one LDS tile, few bricks times centroids) against
+# cells: a full survivor list, the last K of a tile and one more, 72^3 on the
+# cells' side of the rule; an anisotropic metric
+@pytest.mark.parametrize("n,k,h", [((9, 10, 11), 700, (1, 1, 1)), ((24, 25, 26), 2048, (1, 1, 1)),
+                                   ((24, 25, 26), 2049, (1, 1.5, 0.7)), ((40, 41, 9), 64, (0.5, 1, 2)),
+                                   ((72, 72, 72), 1800, (1, 1, 1))])
+def test_kmeans_dispatch_edges(n, k, h):
+    """Two Lloyd rounds and a classification against the oracle: the same
+    labels wherever its two nearest distances differ by more than rounding."""
+    n_r = n[0] * n[1] * n[2]
+    rng = np.random.default_rng(k)
+    w = rng.random(n_r) + 0.05
+    c0 = oracle.grid_points(n)[rng.permutation(n_r)[:k]].astype(np.float64) + 0.25 * rng.random((k, 3))
+    r = isdf.kmeans(None, None, k, c0, 2, w=dev(w), grid=n, h=h)
+    ref = oracle.kmeans(n, w, c0, 2, h)
+    assert np.array_equal(r.labels.cpu().numpy(), ref["labels"])
+    assert np.array_equal(r.idx.cpu().numpy(), ref["idx"])
+    assert abs(r.info["objective"] - ref["J"][-1]) <= 1e-12 * ref["J"][-1]

@@ -185,3 +185,41 @@ def test_kmeans_dispatch_edges(n, k, h):
     assert np.array_equal(r.labels.cpu().numpy(), ref["labels"])
     assert np.array_equal(r.idx.cpu().numpy(), ref["idx"])
     assert abs(r.info["objective"] - ref["J"][-1]) <= 1e-12 * ref["J"][-1]
+
+
+# the adjoint's products with Phi_mu on the residue side of the rule, per block
+# (K N >= 160 (K + N), blocks of 2048 rows and more, the last one shorter) and
+# at the interpolation rows (2048 points and more); fused and general losses,
+# one set and two
+@pytest.mark.parametrize("n_phi,n_psi,n_mu,fused,rblock", [(200, 0, 1001, 1, None), (200, 0, 1001, 0, 2100),
+                                                           (180, 0, 2049, 1, 4000), (60, 240, 701, 0, None),
+                                                           (60, 240, 701, 1, 2049)])
+def test_backward_residue_edges(n_phi, n_psi, n_mu, fused, rblock):
+    """Gradients against the oracle.  With a condition number kappa of C C^H the
+    gradient's relative error is a few n_mu eps kappa in the worst case; the bar
+    is 1e-11, that of the FP64 gradients elsewhere, and n_mu eps kappa where that
+    is larger."""
+    n = (16, 17, 16)
+    n_r = 16 * 17 * 16
+    rng = np.random.default_rng(n_mu + n_phi)
+    c = lambda m: rng.standard_normal((n_r, m)) + 1j * rng.standard_normal((n_r, m))
+    phi = c(n_phi)
+    psi = c(n_psi) if n_psi else phi
+    idx = rng.permutation(n_r)[:n_mu].astype(np.int32)
+    kw = {}
+    if fused:
+        kw["g"] = rng.uniform(0.5, 1.5, n_r)
+    else:
+        kw["theta_bar"] = rng.standard_normal((n_r, n_mu)) + (1j * rng.standard_normal((n_r, n_mu)) if n_psi else 0.0)
+    ref = oracle.fit_backward(phi, psi, idx, **kw)
+    a, b = dev(phi), dev(psi) if n_psi else None
+    _, minv, _ = isdf.fit(a, b, dev(idx), grid=n, nrows=0)
+    dphi, dpsi, loss, _ = isdf.fit_backward(a, b, dev(idx), minv, grid=n, rblock=rblock,
+                                            **{k: dev(v) for k, v in kw.items()})
+    bar = max(1e-11, n_mu * EPS * oracle.cc_condition(phi, psi, idx))
+    rel = lambda x, y: float(np.linalg.norm(x - y) / np.linalg.norm(y))
+    assert rel(dphi.cpu().numpy(), ref["dphi"]) <= bar
+    if n_psi:
+        assert rel(dpsi.cpu().numpy(), ref["dpsi"]) <= bar
+    if fused:
+        assert abs(loss.item() - ref["loss"]) <= bar * ref["loss"]

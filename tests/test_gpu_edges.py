@@ -223,3 +223,31 @@ def test_backward_residue_edges(n_phi, n_psi, n_mu, fused, rblock):
         assert rel(dpsi.cpu().numpy(), ref["dpsi"]) <= bar
     if fused:
         assert abs(loss.item() - ref["loss"]) <= bar * ref["loss"]
+
+
+# rows around the 64 of a workgroup and the 256 of the first one, columns around
+# the 8 wavefronts' shares, their 16 loads in flight and the 64 staged entries;
+# orbital counts around the 16 lanes of a row and the 64 loaded ahead; one pivot
+@pytest.mark.parametrize("n,n_phi,n_psi,n_mu", [((1, 1, 63), 5, 0, 20), ((1, 1, 65), 17, 0, 40), ((5, 7, 9), 33, 0, 131),
+                                                ((7, 8, 23), 65, 0, 700), ((7, 8, 23), 15, 70, 300), ((5, 5, 11), 3, 2, 1),
+                                                ((16, 16, 3), 40, 0, 2)])
+def test_qrcp_edges(n, n_phi, n_psi, n_mu):
+    """Pivots against the oracle's pivoted QR up to its first near tie; squared
+    diagonals within 64 k eps |R_00|^2 (each is a difference of k terms that are
+    at most |R_00|^2)."""
+    n_r = n[0] * n[1] * n[2]
+    rng = np.random.default_rng(n_r + n_mu)
+    c = lambda m: (rng.standard_normal((n_r, m)) + 1j * rng.standard_normal((n_r, m))) * np.exp(-2 * rng.random((n_r, 1)))
+    phi = c(n_phi)
+    psi = c(n_psi) if n_psi else phi
+    n_mu = min(n_mu, n_r)
+    o = oracle.qrcp(phi, psi, n_mu)
+    r = isdf.qrcp(dev(phi), dev(psi) if n_psi else None, n_mu, grid=n)
+    assert r.info["rank"] == o["rank"]
+    rank = o["rank"]
+    s = o["rdiag"][:rank] ** 2
+    near = np.nonzero(o["gap"][:rank] * s <= 1e-9 * s[0])[0]
+    upto = int(near[0]) if near.size else rank
+    assert np.array_equal(r.idx.cpu().numpy()[:upto], o["idx"][:upto])
+    assert np.max(np.abs(r.rdiag.cpu().numpy()[:upto] ** 2 - s[:upto])) <= 64 * rank * EPS * s[0]
+    assert np.all(r.idx.cpu().numpy()[rank:] == -1)

@@ -559,7 +559,7 @@ def main():
         "phases_ms": phases,
         "phases": phase_rates(wl, args.prec, phases, info["kmeans"]["iters"], st.save_gram, info["kmeans"]),
         "kmeans": {"rounds": info["kmeans"]["iters"], "converged": info["kmeans"]["converged"]},
-        "roofline": {"bound": "mfma", "kernel": "FP64 GEMM Theta = (Z C^H)(C C^H)^-1 (one r-block per launch)",
+        "roofline": {"bound": "mfma", "kernel": "FP64 product Theta = (Z C^H)(C C^H)^-1 (one r-block), by int8 residues; peak: FP64 matrix cores",
                      "achieved": round(achieved, 2), "peak": PEAK["fp64"], "unit": "TFLOP/s",
                      "frac": round(achieved / PEAK["fp64"], 4), "traffic": traffic,
                      "flops_per_launch": flops, "ms_per_launch": round(solve_ms, 3)},

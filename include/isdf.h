@@ -260,7 +260,8 @@ int isdf_zc_ab(const isdf_grid* grid /* host */, int32_t dt,
 int isdf_apply_minv(int32_t n_mu, int32_t aliased, const double* minv, const double* G, int64_t ldg,
                     int64_t nrows, int32_t dt, void* theta, int64_t ld_theta, void* stream);
 
-/* isdf_apply_minv_ws: the same product with a workspace
+/*
+ * isdf_apply_minv_ws: the same product with a workspace
  * (isdf_apply_minv_workspace bytes, 0 where it would not be used), which lets
  * it run on the 8-bit matrix cores by residues where that is faster; FP64
  * results either way.  ws null: isdf_apply_minv.

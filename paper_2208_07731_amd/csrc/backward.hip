@@ -17,7 +17,7 @@
 // ms, the same error against 64 bits).
 // Fused loss L = sum_r g_r sum_mu |Theta_r,mu|^2 (Thetabar = 2 g Theta):
 // S = 2 g . (G M^-2) and Theta^T S = 2 M^-1 H M^-2 with H = G^T diag(g) G,
-// so Theta is never formed: per block one FP64 GEMM G M^-2 whose epilogue
+// so Theta is never formed: per block one FP64 product G M^-2 whose epilogue
 // writes Abar / Bbar and the loss, and the lower half of H (split-K).
 // Either way the block's rows of dPhi = Abar Phi_mu and the partials of
 // Abar^T Phi follow; every split-K reduction runs in a fixed order, so the

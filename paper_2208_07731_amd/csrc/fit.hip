@@ -18,7 +18,8 @@
 //  * Cholesky M = L L^T (blocked, 64-wide diagonal blocks factored and
 //    inverted in LDS, panel and trailing updates on the FP64 GEMM), then
 //    L^-1 by block forward substitution and M^-1 = L^-T L^-1.
-//  * Theta rows = G rows times M^-1 (FP64 GEMM), one r-block at a time.
+//  * Theta rows = G rows times M^-1 (FP64: residues or the FP64 GEMM), one
+//    r-block at a time.
 #include "fitlib.h"
 
 namespace isdf {

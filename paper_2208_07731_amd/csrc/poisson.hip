@@ -639,12 +639,13 @@ static int poisson_run(const isdf_grid* g, const TS* theta, int64_t ld_theta, in
   bool pow2 = true;
   for (int a = 0; a < 3; ++a)
     for (int q = 0; q < plan.ax[a].npass; ++q) pow2 = pow2 && (plan.ax[a].radix[q] % 2 == 0);
+  // (column tiles are a grid's second dimension, planes times tiles its first in
+  // workgroups of up to 1024: more than those hold go by lines)
   const int lct = plane_columns(L);
-  if (lct >= 0) {
+  if (lct >= 0 && w.ncols >> lct <= 65535 && (w.ncols >> lct) * L.n0 <= (int64_t)1 << 21) {
     const int64_t pts = (int64_t)L.n1 * L.n2 << lct, padded = (int64_t)L.n1 * (L.n2 + L.n2 / 8) << lct;
     const int nt = (int)(w.ncols >> lct);
     const auto vec = [&](const void* q, int64_t ld) { return ld % 2 == 0 && (uintptr_t)q % (2 * sizeof(TS)) == 0; };
-    if (nt * (int64_t)L.n0 > INT32_MAX) return ISDF_E_ARG;
     PlaneArgs A{theta, V, ld_theta, w.W, n_mu, cplx ? 1 : 0, vec(theta, ld_theta) ? 1 : 0, lct, nt, L,
                 L.n2 + L.n2 / 8};
     PlaneArgs B = A;

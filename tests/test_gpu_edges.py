@@ -167,6 +167,17 @@ def test_exchange_edges(n_mu, n_psi, v_complex, single, rblock):
     assert np.all(np.abs((got[rows] - ref).astype(np.complex128)) <= bar)
 
 
+def test_poisson_more_columns_than_a_grid_dimension():
+    """65544 tiles of 8 columns: past 65535 of them the line passes run.  Every
+    column is one of 16, so the bar of test_poisson_plane_edges holds for each."""
+    n, base = (1, 2, 2), np.random.default_rng(3).standard_normal((4, 16))
+    m = 2 * 8 * 65544
+    v = isdf.poisson(dev(np.tile(base, (1, m // 16))), n).cpu().numpy().reshape(4, m // 16, 16)
+    ref = oracle.poisson(base, n)
+    err = np.linalg.norm(v - ref[:, None, :], axis=(0, 2)) / np.linalg.norm(ref)
+    assert err.max() <= 16 * EPS * 2
+
+
 # all centroids per brick (one LDS tile, few bricks times centroids) against
 # cells: a full survivor list, the last K of a tile and one more, 72^3 on the
 # cells' side of the rule; an anisotropic metric

@@ -53,20 +53,6 @@ __global__ void adj_hadamard(const double* __restrict__ S, double* __restrict__ 
   }
 }
 
-// Real rows of Phi at the interpolation points: X[mu][k] = Phi_real[idx[mu]][k].
-template <class TS, class T>
-__global__ void gather_rows(const TS* __restrict__ phi, int64_t ld, int n, const int32_t* __restrict__ idx,
-                            int n_mu, int64_t nr, T* __restrict__ X) {
-  const int64_t total = (int64_t)n_mu * 2 * n;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int mu = (int)(e / (2 * n)), k = (int)(e % (2 * n));
-    int64_t p = idx[mu];
-    if (p < 0 || p >= nr) p = 0;
-    X[e] = (T)phi[2 * p * ld + k];
-  }
-}
-
 // out = (accumulate ? out : 0) + sum_z part[z] in increasing z.
 __global__ void reduce_splits(double* __restrict__ out, const double* __restrict__ part, int64_t n, int splits,
                               int accumulate, const int* abort) {
@@ -851,24 +837,14 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
   T *Ephi = (T*)P.Ephi, *Fphi = (T*)P.Fphi, *Xphi = (T*)P.Xphi;
   T *Epsi = aliased ? Ephi : (T*)P.Epsi, *Fpsi = aliased ? Fphi : (T*)P.Fpsi, *Xpsi = aliased ? Xphi : (T*)P.Xpsi;
   if (phases & BWD_BEGIN) {
-    hipLaunchKernelGGL(fit_state_init, dim3(1), dim3(1), 0, s, P.st);
+    const BeginSet<TS, T> sa{phi, ld_phi, n_phi, Ephi, Fphi, Xphi};
+    const BeginSet<TS, T> sb{psi, ld_psi, n_psi, aliased ? nullptr : Epsi, aliased ? nullptr : Fpsi,
+                             aliased ? nullptr : Xpsi};
+    if (!begin<TS, T>(P.st, P.marker, nr, idx, n_mu, nmu16, sa, sb, nullptr, 0, s)) return ISDF_E_HIP;
     // interpolation indices must be distinct grid points: every launch that
     // reads or writes rows through idx is a no-op once check_idx has aborted
     // the call, and fit_finish reports ISDF_E_BAD_IDX
-    if (!fill<int>(P.marker, nr, 0, s)) return ISDF_E_HIP;
     hipLaunchKernelGGL(check_idx, dim3((unsigned)ceil_div(n_mu, 256)), dim3(256), 0, s, idx, n_mu, nr, P.marker, P.st);
-    if (!pack<TS, T>(phi, ld_phi, n_phi, idx, n_mu, nr, nmu16, Ephi, s)) return ISDF_E_HIP;
-    hipLaunchKernelGGL((pack_adj_rhs<TS, T>), dim3(blocks_for((int64_t)4 * n_phi * n_mu)), dim3(256), 0, s, phi,
-                       ld_phi, n_phi, idx, n_mu, nr, Fphi);
-    hipLaunchKernelGGL((gather_rows<TS, T>), dim3(blocks_for((int64_t)2 * n_phi * n_mu)), dim3(256), 0, s, phi,
-                       ld_phi, n_phi, idx, n_mu, nr, Xphi);
-    if (!aliased) {
-      if (!pack<TS, T>(psi, ld_psi, n_psi, idx, n_mu, nr, nmu16, Epsi, s)) return ISDF_E_HIP;
-      hipLaunchKernelGGL((pack_adj_rhs<TS, T>), dim3(blocks_for((int64_t)4 * n_psi * n_mu)), dim3(256), 0, s, psi,
-                         ld_psi, n_psi, idx, n_mu, nr, Fpsi);
-      hipLaunchKernelGGL((gather_rows<TS, T>), dim3(blocks_for((int64_t)2 * n_psi * n_mu)), dim3(256), 0, s, psi,
-                         ld_psi, n_psi, idx, n_mu, nr, Xpsi);
-    }
     if (!launch_ok()) return ISDF_E_HIP;
     // binary16 scales of the interpolation rows (E, F, the rows' Gram at the
     // end); the grid rows' scales follow block by block

@@ -114,17 +114,18 @@ static int fit_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
   const int n1 = aliased ? n_mu : 2 * n_mu;
   const int* ab = &P.st->abort;
   typedef typename Prec<PREC>::E T;
-  hipLaunchKernelGGL(fit_state_init, dim3(1), dim3(1), 0, s, P.st);
-  if (!launch_ok()) return ISDF_E_HIP;
   T* Ephi = (T*)P.Ephi;
   T* Epsi = aliased ? Ephi : (T*)P.Epsi;
-  if (!pack<TS, T>(phi, ld_phi, n_phi, idx, n_mu, nr, nmu16, Ephi, s)) return ISDF_E_HIP;
-  if (!aliased && !pack<TS, T>(psi, ld_psi, n_psi, idx, n_mu, nr, nmu16, Epsi, s)) return ISDF_E_HIP;
+  const bool factor = (flags & ISDF_FIT_FACTOR) != 0;
+  const BeginSet<TS, T> a{phi, ld_phi, n_phi, Ephi, nullptr, nullptr};
+  const BeginSet<TS, T> b{psi, ld_psi, n_psi, aliased ? nullptr : Epsi, nullptr, nullptr};
+  if (!begin<TS, T>(P.st, factor ? P.marker : nullptr, nr, idx, n_mu, nmu16, a, b, factor ? P.inv.Y : nullptr,
+                    (int64_t)n1 * n1, s))
+    return ISDF_E_HIP;
   if (!gram_scales<PREC, TS>(phi, ld_phi, n_phi, psi, ld_psi, n_psi, aliased, nr, P.amax, P.sc, s)) return ISDF_E_HIP;
   if (!split_rhs<PREC>((const double*)Ephi, (const double*)Epsi, n_phi, n_psi, aliased, P.sc, &P.sw, s))
     return ISDF_E_HIP;
-  if (flags & ISDF_FIT_FACTOR) {
-    if (!fill<int>(P.marker, nr, 0, s)) return ISDF_E_HIP;
+  if (factor) {
     hipLaunchKernelGGL(check_idx, dim3((unsigned)ceil_div(n_mu, 256)), dim3(256), 0, s, idx, n_mu, nr, P.marker,
                        P.st);
     if (!launch_ok()) return ISDF_E_HIP;
@@ -158,12 +159,11 @@ static int resid_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const
   const int n1 = aliased ? n_mu : 2 * n_mu;
   const int* ab = &P.st->abort;
   typedef typename Prec<PREC>::E T;
-  hipLaunchKernelGGL(fit_state_init, dim3(1), dim3(1), 0, s, P.st);
-  if (!launch_ok()) return ISDF_E_HIP;
   T* Ephi = (T*)P.Ephi;
   T* Epsi = aliased ? Ephi : (T*)P.Epsi;
-  if (!pack<TS, T>(phi, ld_phi, n_phi, idx, n_mu, nr, nmu16, Ephi, s)) return ISDF_E_HIP;
-  if (!aliased && !pack<TS, T>(psi, ld_psi, n_psi, idx, n_mu, nr, nmu16, Epsi, s)) return ISDF_E_HIP;
+  const BeginSet<TS, T> a{phi, ld_phi, n_phi, Ephi, nullptr, nullptr};
+  const BeginSet<TS, T> b{psi, ld_psi, n_psi, aliased ? nullptr : Epsi, nullptr, nullptr};
+  if (!begin<TS, T>(P.st, nullptr, nr, idx, n_mu, nmu16, a, b, nullptr, 0, s)) return ISDF_E_HIP;
   if (!gram_scales<PREC, TS>(phi, ld_phi, n_phi, psi, ld_psi, n_psi, aliased, nr, P.amax, P.sc, s)) return ISDF_E_HIP;
   if (!split_rhs<PREC>((const double*)Ephi, (const double*)Epsi, n_phi, n_psi, aliased, P.sc, &P.sw, s))
     return ISDF_E_HIP;

@@ -24,16 +24,6 @@ struct FitState {
 };
 
 // ------------------------------------------------------------ idx checks
-__global__ void fit_state_init(FitState* st) {
-  st->abort = 0;
-  st->pivot = INT_MAX;
-  st->bad_idx = INT_MAX;
-  st->pad = 0;
-  st->pmin = INFINITY;
-  st->pmax = 0.0;
-  st->loss = 0.0;
-}
-
 __global__ void check_idx(const int32_t* __restrict__ idx, int n_mu, int64_t nr, int* __restrict__ marker,
                           FitState* st) {
   int mu = blockIdx.x * blockDim.x + threadIdx.x;
@@ -47,15 +37,20 @@ __global__ void check_idx(const int32_t* __restrict__ idx, int n_mu, int64_t nr,
   }
 }
 
+// Threads of a launch share out `total` elements.
+template <class F>
+__device__ __forceinline__ void each_of(int64_t total, const F& f) {
+  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) f(e);
+}
+
 // E[n][k], n = 32 b + 16 c + t -> column nu = 16 b + t, part c (0: Re A, 1: Im A);
 // k = 2 i + comp multiplies (re, im) of orbital i of the grid row.
 // With Phi_mu[nu][i] = a + i b:  Re A = sum x a + y b,  Im A = sum y a - x b.
 template <class TS, class T>
-__global__ void pack_gram_rhs(const TS* __restrict__ phi, int64_t ld, int n, const int32_t* __restrict__ idx,
-                              int n_mu, int64_t nr, int rows, T* __restrict__ E) {
-  const int64_t total = (int64_t)rows * 2 * n;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
+__device__ __forceinline__ void pack_gram_each(const TS* __restrict__ phi, int64_t ld, int n,
+                                               const int32_t* __restrict__ idx, int n_mu, int64_t nr, int rows,
+                                               T* __restrict__ E) {
+  each_of((int64_t)rows * 2 * n, [&](int64_t e) {
     const int r = (int)(e / (2 * n));
     const int k = (int)(e % (2 * n));
     const int b = r >> 5, c = (r >> 4) & 1, t = r & 15;
@@ -70,7 +65,87 @@ __global__ void pack_gram_rhs(const TS* __restrict__ phi, int64_t ld, int n, con
       else v = comp == 0 ? -z.y : z.x;
     }
     E[e] = (T)v;
+  });
+}
+template <class TS, class T>
+__global__ void pack_gram_rhs(const TS* __restrict__ phi, int64_t ld, int n, const int32_t* __restrict__ idx,
+                              int n_mu, int64_t nr, int rows, T* __restrict__ E) {
+  pack_gram_each<TS, T>(phi, ld, n, idx, n_mu, nr, rows, E);
+}
+
+// F[n][k] (n = 2 i + c', k = 2 nu + c): real form of right-multiplication by
+// Phi_mu, (x + iy)(a + ib) = (xa - yb) + i(xb + ya) with Phi_mu[nu][i] = a + ib.
+template <class TS, class T>
+__device__ __forceinline__ void pack_adj_each(const TS* __restrict__ phi, int64_t ld, int n,
+                                              const int32_t* __restrict__ idx, int n_mu, int64_t nr, T* __restrict__ F) {
+  each_of((int64_t)2 * n * 2 * n_mu, [&](int64_t e) {
+    const int row = (int)(e / (2 * n_mu)), k = (int)(e % (2 * n_mu));
+    const int i = row >> 1, cp = row & 1, nu = k >> 1, c = k & 1;
+    int64_t p = idx[nu];
+    if (p < 0 || p >= nr) p = 0;
+    const double2 z = Cplx<TS>::load(phi + 2 * (p * ld + i));
+    double v;
+    if (cp == 0) v = c == 0 ? z.x : -z.y;
+    else v = c == 0 ? z.y : z.x;
+    F[e] = (T)v;
+  });
+}
+template <class TS, class T>
+__global__ void pack_adj_rhs(const TS* __restrict__ phi, int64_t ld, int n, const int32_t* __restrict__ idx,
+                             int n_mu, int64_t nr, T* __restrict__ F) {
+  pack_adj_each<TS, T>(phi, ld, n, idx, n_mu, nr, F);
+}
+
+// Everything a fit or its adjoint sets up from the inputs, in one launch (the
+// small boxes are a chain of launches, each 5 us of the host's time and 2 of the
+// GPU's; 24^3 fit 292 -> 284 us, loss and gradient 692 -> 656): the state, the occupancy marker and `zeros` cleared, and per orbital
+// set the packed right-hand sides E, F and the real rows X[mu][k] =
+// Phi_real[idx[mu]][k] (null: not wanted).
+template <class TS, class T>
+struct BeginSet {
+  const TS* phi;
+  int64_t ld;
+  int n;
+  T *E, *F, *X;
+};
+template <class TS, class T>
+__global__ void fit_begin(FitState* st, int* __restrict__ marker, int64_t nr, const int32_t* __restrict__ idx, int n_mu,
+                          int rows, BeginSet<TS, T> a, BeginSet<TS, T> b, double* __restrict__ zeros, int64_t nzeros) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->abort = 0;
+    st->pivot = INT_MAX;
+    st->bad_idx = INT_MAX;
+    st->pad = 0;
+    st->pmin = INFINITY;
+    st->pmax = 0.0;
+    st->loss = 0.0;
   }
+  if (marker) each_of(nr, [&](int64_t e) { marker[e] = 0; });
+  if (zeros) each_of(nzeros, [&](int64_t e) { zeros[e] = 0.0; });
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const BeginSet<TS, T>& w = s ? b : a;
+    if (w.E) pack_gram_each<TS, T>(w.phi, w.ld, w.n, idx, n_mu, nr, rows, w.E);
+    if (w.F) pack_adj_each<TS, T>(w.phi, w.ld, w.n, idx, n_mu, nr, w.F);
+    if (w.X)
+      each_of((int64_t)n_mu * 2 * w.n, [&](int64_t e) {
+        const int mu = (int)(e / (2 * w.n)), k = (int)(e % (2 * w.n));
+        int64_t p = idx[mu];
+        if (p < 0 || p >= nr) p = 0;
+        w.X[e] = (T)w.phi[2 * p * w.ld + k];
+      });
+  }
+}
+template <class TS, class T>
+static bool begin(FitState* st, int* marker, int64_t nr, const int32_t* idx, int n_mu, int nmu16, BeginSet<TS, T> a,
+                  BeginSet<TS, T> b, double* zeros, int64_t nzeros, hipStream_t s) {
+  int64_t most = (int64_t)2 * nmu16 * 2 * (a.n > b.n ? a.n : b.n);
+  if (marker && nr > most) most = nr;
+  if (zeros && nzeros > most) most = nzeros;
+  const int64_t blocks = ceil_div(most, 256) < 4096 ? ceil_div(most, 256) : 4096;
+  hipLaunchKernelGGL((fit_begin<TS, T>), dim3((unsigned)blocks), dim3(256), 0, s, st, marker, nr, idx, n_mu, 2 * nmu16, a,
+                     b, zeros, nzeros);
+  return launch_ok();
 }
 
 // Gram + Hadamard epilogue.  Accumulator pairs (j, j+1) of a wavefront hold
@@ -513,9 +588,9 @@ struct InvWork {
 constexpr int CHOL_OUTER = 256;
 constexpr int MIRROR_MIN = 768;
 
+// (w.Y all zeros on entry)
 static int spd_inverse(double* X, int n, InvWork w, FitState* st, hipStream_t s) {
   const int* ab = &st->abort;
-  if (!fill<double>(w.Y, (int64_t)n * n, 0.0, s)) return ISDF_E_HIP;
   for (int o = 0; o < n; o += CHOL_OUTER) {
     const int oe = n - o < CHOL_OUTER ? n : o + CHOL_OUTER;
     for (int k0 = o; k0 < oe; k0 += NB) {
@@ -784,26 +859,6 @@ static bool gram(const TS* phi, int64_t ld_phi, int n_phi, const TS* psi, int64_
                                                                          0, epi, 0, abort, s);
     return launch_gemm<T, 128, 64, 16, 2, 2, TS, KC, T, KC, 2, FOLD>(rows, N, 2 * (int64_t)n_phi, a0, b0, a1, b1,
                                                                       2 * (int64_t)n_psi, epi, 0, abort, s);
-  }
-}
-
-// F[n][k] (n = 2 i + c', k = 2 nu + c): real form of right-multiplication by
-// Phi_mu, (x + iy)(a + ib) = (xa - yb) + i(xb + ya) with Phi_mu[nu][i] = a + ib.
-template <class TS, class T>
-__global__ void pack_adj_rhs(const TS* __restrict__ phi, int64_t ld, int n, const int32_t* __restrict__ idx,
-                             int n_mu, int64_t nr, T* __restrict__ F) {
-  const int64_t total = (int64_t)2 * n * 2 * n_mu;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int row = (int)(e / (2 * n_mu)), k = (int)(e % (2 * n_mu));
-    const int i = row >> 1, cp = row & 1, nu = k >> 1, c = k & 1;
-    int64_t p = idx[nu];
-    if (p < 0 || p >= nr) p = 0;
-    const double2 z = Cplx<TS>::load(phi + 2 * (p * ld + i));
-    double v;
-    if (cp == 0) v = c == 0 ? z.x : -z.y;
-    else v = c == 0 ? z.y : z.x;
-    F[e] = (T)v;
   }
 }
 

@@ -28,7 +28,6 @@
 namespace isdf {
 namespace {
 
-constexpr int MAX_SPLITS = 32;
 
 // Abar / Bbar from S and the block's Gram blocks, in place.
 //  aliased: S real [R][n_mu]; A complex -> Abar = S A (over A)
@@ -412,32 +411,6 @@ __global__ void copy_rows(TS* __restrict__ dst, int64_t ldd, const TS* __restric
 static inline int kext_rows(int64_t rows) { return (int)ceil_div(rows, 32) * 32; }
 static inline int ldk_of(int64_t rows) { return kext_rows(rows) + 64; }
 
-// Split factor of a split-engine product with `tiles` 128 x 128 output tiles
-// of mn elements in total, contracted over K grid rows.  The engine holds one
-// workgroup per CU (slots / 2 of them, slots counting two FP64 tiles per CU),
-// so a launch takes ceil(tiles s / CUs) waves of workgroups: the factor is the
-// power of two, with K slices of at least 4096 rows, that minimises the
-// modelled time waves (K / s) t_row + s mn 16 B / bw (the partial sums'
-// write and read), a larger one taken only for a modelled gain above 2 %.
-// t_row is the measured time of one tile per K row (FP16x3 34 ns, BF16x6
-// 51 ns); e.g. the 136 lower tiles of a 2048 x 2048 H over 262144 rows run in
-// 9 waves of 16 slices instead of 3 waves of 4.
-static int split_k_for(int64_t tiles, int64_t K, int64_t mn, int slots, int mode) {
-  const int64_t cus = slots / 2 > 0 ? slots / 2 : 1;
-  const double t_row = mode == SPLIT_BF16X6 ? 51e-9 : 34e-9;
-  const double bw = 4e12;
-  int best = 1;
-  double best_t = (double)ceil_div(tiles, cus) * (double)K * t_row;
-  for (int s = 2; s <= MAX_SPLITS && ceil_div(K, s) >= 4096; s *= 2) {
-    const double t = (double)ceil_div(tiles * s, cus) * ((double)K / s) * t_row + s * (double)mn * 16.0 / bw;
-    if (t < 0.98 * best_t) {
-      best = s;
-      best_t = t;
-    }
-  }
-  return best;
-}
-
 static unsigned blocks_for(int64_t n) {
   int64_t b = ceil_div(n, 256);
   return (unsigned)(b > 8192 ? 8192 : (b < 1 ? 1 : b));
@@ -450,50 +423,6 @@ static int device_slots() {
                                               hipSuccess || cu <= 0)
     cu = 256;
   return 2 * cu;
-}
-
-// Tile and split-K factor of an M x N product of K-deep sums (its lower tiles
-// only when `lower`): 1 or a multiple of 8 (one K slice per XCD at a time),
-// slices of at least 4 tile edges of rows, chosen to minimise the modelled time
-// ceil(tiles s / CUs) (K / s) t_row + s M N 16 B / bw, i.e. whole rounds of
-// workgroups against the partial sums' write and read.  A round of one
-// workgroup per CU runs at about the rate of two (the matrix cores bound
-// both), hence CUs and not resident workgroups.  Small outputs get 64-tiles:
-// 256 x 256 lower tiles over 13824 rows 96 us on 128-tiles, 39 on these; 512 x
-// 64 over 13824 rows 98 and 29.
-static TilePlan splits_for(int64_t M, int64_t N, int lower, int64_t K, int slots) {
-  const int64_t cus = slots / 2 > 0 ? slots / 2 : 1;
-  const double bw = 4e12;  // B/s for the partials
-  TilePlan best{128, 1};
-  double best_t = 0.0;
-  for (int tile = 128; tile >= 64; tile /= 2) {
-    const int64_t tiles = gemm_tiles((int)ceil_div(M, tile), (int)ceil_div(N, tile), lower);
-    const double t_row = 2.0 * tile * tile / (60e12 / (double)cus);  // s per k-row and tile
-    for (int s = 1; s <= MAX_SPLITS; s = s < 8 ? 8 : s + 8) {
-      if (s > 1 && ceil_div(K, s) < 4 * tile) break;
-      const double rounds = (double)ceil_div(tiles * s, cus);
-      double t = rounds * ((double)K / s) * t_row + (s > 1 ? s * (double)M * (double)N * 16.0 / bw : 0.0);
-      if (tile == 64) t *= 1.05;  // twice the operand traffic
-      if ((tile == 128 && s == 1) || t < best_t * (1.0 - 1e-9)) {
-        best = TilePlan{tile, s};
-        best_t = t;
-      }
-    }
-  }
-  return best;
-}
-
-// Plans the adjoint uses for blocks of `rows` rows.
-struct BwdSplits {
-  TilePlan h;  // Theta^T S (general) or H = G^T g G (fused, lower tiles)
-  TilePlan q;  // Abar^T X per orbital set
-};
-
-static BwdSplits bwd_splits(int64_t rows, int64_t n1, int n_mu, int n, bool fused, int slots) {
-  BwdSplits b;
-  b.h = splits_for(n1, n1, fused ? 1 : 0, rows, slots);
-  b.q = splits_for(2 * (int64_t)n_mu, 2 * (int64_t)n, 0, rows, slots);
-  return b;
 }
 
 // Planes of the adjoint's orbital products dX = Abar F (split precisions):
@@ -541,25 +470,17 @@ struct BwdPlan {
   ModWork mod1;  // of the real N1 x N1 ones around them (the same memory)
   ModWork modf;  // of the complex products with Phi_mu in FP64 (the same memory)
   int slots;     // workgroup slots the split factors were chosen for
+  SplitCaps caps;  // factors Ppart and Qpart hold
+  int64_t tcap;  // doubles of tpart
   size_t bytes;
 };
 
 static BwdPlan plan_bwd(void* ws, size_t cap, int64_t nr, int n_mu, int n_phi, int n_psi, bool aliased,
                         isdf_prec prec, int64_t rblock, int slots, bool saved = false) {
   const size_t tsize = tsize_of(prec);
-  // largest split factors over the block sizes that occur (both losses)
-  int sh = 1, sq = 1;
-  for (int64_t rows : {rblock, nr - (ceil_div(nr, rblock) - 1) * rblock})
-    for (bool fused : {false, true}) {
-      const int64_t n1b = aliased ? n_mu : 2 * (int64_t)n_mu;
-      const BwdSplits b1 = bwd_splits(rows, n1b, n_mu, n_phi, fused, slots);
-      const BwdSplits b2 = bwd_splits(rows, n1b, n_mu, n_psi, fused, slots);
-      sh = b1.h.splits > sh ? b1.h.splits : sh;
-      sq = b1.q.splits > sq ? b1.q.splits : sq;
-      sq = b2.q.splits > sq ? b2.q.splits : sq;
-    }
   Carver c(ws, cap);
   BwdPlan P{};
+  P.caps = bwd_split_caps(nr, rblock, aliased, n_mu, n_phi, n_psi, slots);
   const int nmu16 = (int)ceil_div(n_mu, 16) * 16;
   const int64_t n1 = aliased ? n_mu : 2 * (int64_t)n_mu;
   const int nmax = n_phi > n_psi ? n_phi : n_psi;
@@ -582,11 +503,11 @@ static BwdPlan plan_bwd(void* ws, size_t cap, int64_t nr, int n_mu, int n_phi, i
   }
   P.P = c.take<double>((size_t)n1 * n1);
   P.W2 = c.take<double>((size_t)n1 * n1);
-  P.Ppart = c.take<double>((size_t)sh * n1 * n1);
+  P.Ppart = c.take<double>((size_t)P.caps.h * n1 * n1);
   P.slots = slots;
   P.Qphi = c.take<double>((size_t)2 * n_mu * 2 * n_phi);
   if (!aliased) P.Qpsi = c.take<double>((size_t)2 * n_mu * 2 * n_psi);
-  P.Qpart = c.take<double>((size_t)sq * 2 * n_mu * 2 * nmax);
+  P.Qpart = c.take<double>((size_t)P.caps.q * 2 * n_mu * 2 * nmax);
   P.Amu = c.take<double>((size_t)n_mu * 2 * n_mu);
   if (!aliased) P.Bmu = c.take<double>((size_t)n_mu * 2 * n_mu);
   P.dA = c.take<double>((size_t)n_mu * 2 * n_mu);
@@ -621,20 +542,21 @@ static BwdPlan plan_bwd(void* ws, size_t cap, int64_t nr, int n_mu, int n_phi, i
     static_assert(SplitTile<SPLIT_BF16X6>::BM == bm && SplitTile<SPLIT_BF16X6>::BN == bn, "one tile");
     // (Abar^T X per orbital set: a set with fewer columns has fewer tiles and
     // may take a larger factor, so both sets are sized)
-    const int mode = prec == ISDF_P_BF16X6 ? SPLIT_BF16X6 : SPLIT_FP16X3;
+    const bool bf = prec == ISDF_P_BF16X6;
     const int64_t th = split_tiles((int)ceil_div(n1, bm), (int)ceil_div(n1, bn), bm / bn, 1);
     int64_t need = 0;
     for (int64_t rows : {rblock, nr - (ceil_div(nr, rblock) - 1) * rblock}) {
-      const int sh2 = split_k_for(th, kext_rows(rows), n1 * n1, slots, mode);
+      const int sh2 = split_k_for(th, kext_rows(rows), n1 * n1, slots, bf, MAX_SPLITS);
       if (sh2 > 1 && sh2 * n1 * n1 > need) need = sh2 * n1 * n1;
       for (int n : {n_phi, aliased ? n_phi : n_psi}) {
         const int64_t mn = 2 * (int64_t)n_mu * 2 * n;
         const int64_t tq = ceil_div(2 * (int64_t)n_mu, bm) * ceil_div(2 * (int64_t)n, bn);
-        const int sq2 = split_k_for(tq, kext_rows(rows), mn, slots, mode);
+        const int sq2 = split_k_for(tq, kext_rows(rows), mn, slots, bf, MAX_SPLITS);
         if (sq2 > 1 && sq2 * mn > need) need = sq2 * mn;
       }
     }
     if (need > 0) P.tpart = c.take<double>((size_t)need);
+    P.tcap = need;
   }
   P.bytes = c.used;
   return P;
@@ -681,7 +603,7 @@ static bool split_t_rows(const double* x, int64_t ld, int ncols, int rows, void*
 template <int SPLIT, class TY>
 static bool split_xty(const double* X, int64_t ldx, int mx, const double* rowscale, const TY* Y, int64_t ldy, int ny,
                       int rows, double* C, int64_t ldc, bool accumulate, int lower_only, void* tp, double* part,
-                      const double* sc, int slots, const int* ab, hipStream_t s, bool x_split = false) {
+                      int64_t part_cap, const double* sc, int slots, const int* ab, hipStream_t s, bool x_split = false) {
   typedef typename SplitT<SPLIT>::P P;
   constexpr int NP = SplitT<SPLIT>::NP;
   const int ldk = ldk_of(rows);
@@ -701,7 +623,7 @@ static bool split_xty(const double* X, int64_t ldx, int mx, const double* rowsca
   const int kx = kext_rows(rows);
   const int64_t tiles =
       split_tiles((int)ceil_div(mx, T::BM), (int)ceil_div(ny, T::BN), T::BM / T::BN, lower_only && mx == ny);
-  const int sp = part ? split_k_for(tiles, kx, (int64_t)mx * ny, slots, SPLIT) : 1;
+  const int sp = part ? split_k_for(tiles, kx, (int64_t)mx * ny, slots, SPLIT == SPLIT_BF16X6, part_cap / ((int64_t)mx * ldc)) : 1;
   const int64_t cn = (int64_t)mx * ldc;
   if (sp == 1) {
     EpiStore<double> epi{C, ldc, mx, ny, 1.0, accumulate ? 1.0 : 0.0, nullptr, 0, 0};
@@ -758,7 +680,7 @@ static bool orbital_block(const double* Abar, int n_mu, const typename Prec<PREC
                           const TS* X, int64_t ld_x, int n, TS* dX, int64_t ld_dx, int64_t r, int rows, double* Q,
                           double* Qpart, const double* scales, const double* scales_t, const AdjPlanes& ap,
                           const ModWork& modf, TilePlan sp,
-                          bool first, void* tp, double* tpart, int slots, const int* ab, hipStream_t s) {
+                          bool first, void* tp, double* tpart, int64_t tcap, int slots, const int* ab, hipStream_t s) {
   const int64_t two_mu = 2 * (int64_t)n_mu;
   constexpr int SPLIT = Prec<PREC>::SPLIT;
   if constexpr (SPLIT >= 0) {
@@ -772,13 +694,14 @@ static bool orbital_block(const double* Abar, int n_mu, const typename Prec<PREC
     if (!adj_rows<PREC, TS>(rows, Abar, n_mu, F, fplanes, n, dX + 2 * r * ld_dx, ld_dx, scales, ap, modf, ab, s, true))
       return false;
     return split_xty<SPLIT, TS>(Abar, two_mu, (int)two_mu, nullptr, X + 2 * r * ld_x, 2 * ld_x, 2 * n, rows, Q,
-                                2 * (int64_t)n, !first, 0, tp, tpart, h ? scales_t : nullptr, slots, ab, s, true);
+                                2 * (int64_t)n, !first, 0, tp, tpart, tcap, h ? scales_t : nullptr, slots, ab, s, true);
   } else {
     if (!adj_rows<PREC, TS>(rows, Abar, n_mu, F, fplanes, n, dX + 2 * r * ld_dx, ld_dx, scales, ap, modf, ab, s))
       return false;
     (void)scales_t;
     (void)tp;
     (void)tpart;
+    (void)tcap;
     (void)slots;
     const int64_t qn = two_mu * 2 * n;
     if (!tgemm<typename Prec<PREC>::Q, XC, XC>((int)two_mu, 2 * n, rows, Abar, two_mu, X + 2 * r * ld_x, 2 * ld_x,
@@ -886,8 +809,8 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
     if (!Gs && !gram<PREC, TS>(phi, ld_phi, n_phi, psi, ld_psi, n_psi, aliased, Ephi, Epsi, nmu16, n_mu, nullptr, nr,
                                r, rows, Gb, n1, aliased ? G_REAL : G_CPLX, ab, s, P.sc, &P.sw, Ab, Bb))
       return ISDF_E_HIP;
-    const BwdSplits sp_phi = bwd_splits(rows, n1, n_mu, n_phi, !tbar, P.slots);
-    const BwdSplits sp_psi = bwd_splits(rows, n1, n_mu, n_psi, !tbar, P.slots);
+    const BwdSplits sp_phi = bwd_splits(rows, n1, n_mu, n_phi, !tbar, P.slots, P.caps);
+    const BwdSplits sp_psi = bwd_splits(rows, n1, n_mu, n_psi, !tbar, P.slots, P.caps);
     constexpr int SPLIT = Prec<PREC>::SPLIT;
     if (!tbar) {
       // H += G^T diag(g) G (lower tiles, fixed-order reduction): FP64 split-K,
@@ -903,7 +826,7 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
           if (!launch_ok()) return ISDF_E_HIP;
           hsc = P.sc + 12;
         }
-        if (!split_xty<SPLIT, double>(Gb, n1, n1, g + r, Gb, n1, n1, rows, P.P, n1, !first, 1, P.tp, P.tpart, hsc,
+        if (!split_xty<SPLIT, double>(Gb, n1, n1, g + r, Gb, n1, n1, rows, P.P, n1, !first, 1, P.tp, P.tpart, P.tcap, hsc,
                                       P.slots, ab, s))
           return ISDF_E_HIP;
       } else {
@@ -978,11 +901,11 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
                          aliased ? 4 : 5, aliased ? 0 : 1);
     }
     if (!orbital_block<PREC, TS>(Abar, n_mu, Fphi, P.ap.f_phi, phi, ld_phi, n_phi, dphi, ld_dphi, r, rows, P.Qphi,
-                                 P.Qpart, P.sc + 4, P.sc + 8, P.ap, P.modf, sp_phi.q, first, P.tp, P.tpart, P.slots, ab, s))
+                                 P.Qpart, P.sc + 4, P.sc + 8, P.ap, P.modf, sp_phi.q, first, P.tp, P.tpart, P.tcap, P.slots, ab, s))
       return ISDF_E_HIP;
     if (!aliased && !orbital_block<PREC, TS>(Bbar, n_mu, Fpsi, P.ap.f_psi, psi, ld_psi, n_psi, dpsi, ld_dpsi, r, rows,
                                              P.Qpsi, P.Qpart, P.sc + 6, P.sc + 10, P.ap, P.modf, sp_psi.q, first, P.tp,
-                                             P.tpart, P.slots, ab, s))
+                                             P.tpart, P.tcap, P.slots, ab, s))
       return ISDF_E_HIP;
   }
   if (!(phases & BWD_END)) return ISDF_OK;

@@ -8,6 +8,7 @@
 
 #include "gemm_mod.h"
 #include "gemm_split.h"
+#include "splitk.h"
 
 namespace isdf {
 namespace {
@@ -529,11 +530,6 @@ static bool dgemm_batched(int M, int N, int64_t K, const double* A, int64_t lda,
   return launch_tiled<double, double, LA, double, LB>(tile_for(M, N, 0, batch), M, N, K, a, b, epi, 0, abort, st, 1,
                                                       batch, sa, sb, nullptr, nullptr, tri);
 }
-
-// Tile edge and split-K factor of a product.
-struct TilePlan {
-  int tile, splits;
-};
 
 // GEMM in compute type T with split-K slices written to C + z * zstride.
 // bscale: optional per-k factor of B; lower_only: skip tiles above the diagonal.

@@ -11,10 +11,10 @@
 // for callers that kept them from the forward (isdf_zc_ab), read from there
 // and overwritten in place; the r-block loop and every reduction order are
 // the same either way, so both give bitwise equal gradients.
-// General upstream Thetabar: per block the split-K partials of H = G^T Thetabar,
-// S = Thetabar M^-1 (FP64), Abar / Bbar in place; Theta^T S = M^-1 H M^-1 at the
-// end, so Theta is not formed again (two-set 36 x 40 x 48 gradient 27.8 -> 23.5
-// ms, the same error against 64 bits).
+// General upstream Thetabar: per block Theta = G M^-1 and S = Thetabar M^-1
+// (FP64 products), the split-K partials of Theta^T S, Abar / Bbar in place.
+// (M^-1 (G^T Thetabar) M^-1 is one product per block less, but its error is 1.5
+// to 4.5 times that of Theta^T S at condition numbers of 1e4 to 1e6.)
 // Fused loss L = sum_r g_r sum_mu |Theta_r,mu|^2 (Thetabar = 2 g Theta):
 // S = 2 g . (G M^-2) and Theta^T S = 2 M^-1 H M^-2 with H = G^T diag(g) G,
 // so Theta is never formed: per block one FP64 product G M^-2 whose epilogue
@@ -454,7 +454,7 @@ struct BwdPlan {
   FitState* st;
   int* marker;   // [N_r] occupancy of the interpolation rows (check_idx)
   void *Ephi, *Epsi, *Fphi, *Fpsi, *Xphi, *Xpsi;
-  double *G, *A, *B, *P, *Ppart, *Qphi, *Qpsi, *Qpart, *Amu, *Bmu, *dA, *dB, *T1, *lpart, *W2;
+  double *G, *Th, *A, *B, *P, *Ppart, *Qphi, *Qpsi, *Qpart, *Amu, *Bmu, *dA, *dB, *T1, *lpart, *W2;
   // binary16 split: operand maxima and power-of-two scales
   //  amax [8]: block rows of Phi, Psi; interpolation rows (E) of Phi, Psi; Abar, Bbar; g G, G
   //  sc [20]: Gram (rows Phi, E_phi, rows Psi, E_psi); Abar F (Abar, E_phi, Bbar, E_psi);
@@ -501,6 +501,7 @@ static BwdPlan plan_bwd(void* ws, size_t cap, int64_t nr, int n_mu, int n_phi, i
     P.A = c.take<double>((size_t)rblock * 2 * n_mu);
     if (!aliased) P.B = c.take<double>((size_t)rblock * 2 * n_mu);
   }
+  P.Th = c.take<double>((size_t)rblock * n1);
   P.P = c.take<double>((size_t)n1 * n1);
   P.W2 = c.take<double>((size_t)n1 * n1);
   P.Ppart = c.take<double>((size_t)P.caps.h * n1 * n1);
@@ -875,16 +876,19 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
       hipLaunchKernelGGL(add_loss, dim3(1), dim3(LOSS_THREADS), 0, s, P.st, (const double*)P.lpart, (int)ltiles);
       if (!launch_ok()) return ISDF_E_HIP;
     } else {
-      // H += G^T Thetabar, S = Thetabar M^-1 (over G), Abar / Bbar in place
+      // Theta = G M^-1, S = Thetabar M^-1 (over G), P += Theta^T S, Abar / Bbar in place
+      if (!nt_product<double>(rows, n1, n1, Gb, n1, minv, n1, MOD_DIAG_B, P.Th, n1, 1.0, P.mod, false, ab, s))
+        return ISDF_E_HIP;
       const int64_t ldt = aliased ? ld_tbar : 2 * ld_tbar;
-      const TT* tb = tbar + (r - gbase) * ldt;
+      if (!nt_product<double, TT>(rows, n1, n1, tbar + (r - gbase) * ldt, ldt, minv, n1, MOD_DIAG_B, Gb, n1, 1.0, P.mod,
+                                  true, ab, s))
+        return ISDF_E_HIP;
       const TilePlan sp = sp_phi.h;
       const int64_t pn = (int64_t)n1 * n1;
-      if (!tgemm<double, XC, XC>(n1, n1, rows, Gb, n1, tb, ldt, P.Ppart, n1, 1.0, 0.0, ab, s, sp, pn)) return ISDF_E_HIP;
-      hipLaunchKernelGGL(reduce_splits, dim3(blocks_for(pn)), dim3(256), 0, s, P.P, P.Ppart, pn, sp.splits,
-                         first ? 0 : 1, ab);
-      if (!nt_product<double, TT>(rows, n1, n1, tb, ldt, minv, n1, MOD_DIAG_B, Gb, n1, 1.0, P.mod, false, ab, s))
+      if (!tgemm<double, XC, XC>(n1, n1, rows, P.Th, n1, Gb, n1, P.Ppart, n1, 1.0, 0.0, ab, s, sp, pn))
         return ISDF_E_HIP;
+      hipLaunchKernelGGL(reduce_splits, dim3(blocks_for(pn)), dim3(256), 0, s, P.P, P.Ppart, pn, sp.splits, first ? 0 : 1,
+                         ab);
       hipLaunchKernelGGL(adj_hadamard, dim3(blocks_for((int64_t)rows * n_mu)), dim3(256), 0, s, (const double*)Gb,
                          Ab, Bb, (int64_t)rows, n_mu, aliased ? 1 : 0);
       if (!launch_ok()) return ISDF_E_HIP;
@@ -917,12 +921,6 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
       return ISDF_E_HIP;
     if (!nt_product<double>(n1, n1, n1, minv, n1, P.Ppart, n1, MOD_DIAG_A, P.P, n1, 2.0, P.mod1, false, ab, s))
       return ISDF_E_HIP;
-  }
-  if (tbar) {
-    // Theta^T S = M^-1 H M^-1 with H = G^T Thetabar (real forms, M^-1 symmetric)
-    if (!nt_product<double>(n1, n1, n1, P.P, n1, minv, n1, MOD_DIAG_B, P.Ppart, n1, 1.0, P.mod1, false, ab, s))
-      return ISDF_E_HIP;
-    if (!dgemm<KC, XC>(n1, n1, n1, minv, n1, P.Ppart, n1, P.P, n1, 1.0, 0.0, 0, ab, s)) return ISDF_E_HIP;
   }
   // Mbar terms at the interpolation rows
   if (!gram<PREC, TS>(phi, ld_phi, n_phi, psi, ld_psi, n_psi, aliased, Ephi, Epsi, nmu16, n_mu, idx, nr, 0, n_mu,

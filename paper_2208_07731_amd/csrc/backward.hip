@@ -666,7 +666,7 @@ static bool adj_rows(int rows, const double* Abar, int n_mu, const typename Prec
     // (F's even rows are the columns of conj(Phi_mu): a complex product with B^H)
     if constexpr (PREC == ISDF_P_FP64)
       if (modf.mp && mod_pays_c(rows, n, n_mu))
-        return nt_product<TS>(rows, 2 * n, (int)two_mu, Abar, two_mu, F, two_mu, MOD_PLAIN, dX, 2 * ld_dx, 1.0, modf,
+        return nt_product<TS>(rows, 2 * n, (int)two_mu, Abar, two_mu, F, two_mu, MOD_MEANS, dX, 2 * ld_dx, 1.0, modf,
                               false, ab, s);
     (void)modf;
     return tgemm<T, KC, KC>(rows, 2 * n, two_mu, Abar, two_mu, F, two_mu, dX, 2 * ld_dx, 1.0, 0.0, ab, s);
@@ -725,7 +725,7 @@ static bool orbital_fix(const double* dAbar, int n_mu, const typename Prec<PREC>
   if constexpr (sizeof(T) == 8)
     if (modf.mp && mod_pays_c(n_mu, n, n_mu)) {
       // 8192 x 1024 x 8192 complex: 9.4 ms on the FP64 matrix cores, 2.8 by residues
-      if (!nt_product<double>(n_mu, 2 * n, (int)two_mu, dAbar, two_mu, F, two_mu, MOD_PLAIN, T1, 2 * (int64_t)n, 1.0,
+      if (!nt_product<double>(n_mu, 2 * n, (int)two_mu, dAbar, two_mu, F, two_mu, MOD_MEANS, T1, 2 * (int64_t)n, 1.0,
                               modf, false, ab, s))
         return false;
       done = true;
@@ -853,7 +853,7 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
         const int64_t mp = w.mp, fp64 = ceil_div(rows, mp) * ceil_div(mp, 128) * ceil_div(n1, 128);
         if (!fill<double>(P.lpart, fp64, 0.0, s)) return ISDF_E_HIP;
         ltiles = fp64;
-        if (!mod_prepare(P.W2, n1, n1 / hc, n1 / hc, MOD_DIAG_B, P.W2, n1, w, ab, s)) return ISDF_E_HIP;
+        if (!mod_prepare<double>(Gb, n1, rows, P.W2, n1, n1 / hc, n1 / hc, MOD_DIAG_B, w, ab, s)) return ISDF_E_HIP;
         for (int64_t q = 0, p = 0; q < rows; q += mp, ++p) {
           const int pr = (int)(rows - q < mp ? rows - q : mp);
           double *Aq = Ab + q * 2 * n_mu, *Bq = aliased ? nullptr : Bb + q * 2 * n_mu, *Gq = Gb + q * n1;

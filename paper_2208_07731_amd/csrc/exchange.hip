@@ -134,7 +134,7 @@ static int exch_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const 
     // W rows = -(conj(V) .* A) Psi_mu; the even rows of the packed Psi_mu are the
     // columns of conj(Psi_mu), so by residues it is the product with B^H
     if (!nt_product<TS>(rows, 2 * n_psi, (int)two_mu, (const double*)P.A, two_mu, (const double*)P.Fpsi, two_mu,
-                        MOD_PLAIN, W + 2 * r * ld_w, 2 * ld_w, -1.0, P.mod, r > 0, P.ab, s))
+                        MOD_MEANS, W + 2 * r * ld_w, 2 * ld_w, -1.0, P.mod, r > 0, P.ab, s))
       return ISDF_E_HIP;
   }
   return ISDF_OK;

@@ -493,9 +493,9 @@ static bool dgemm(int M, int N, int64_t K, const TA* A, int64_t lda, const doubl
 }
 
 // C = alpha A B^T in FP64, by residues where that is faster (mod_pays) and the
-// work buffers are there, else on the FP64 matrix cores.  bal: the symmetric
-// operand (of order K) whose diagonal balances the two.  `prepared`: B's
-// residues are in the buffers from an earlier call.  With complex buffers B
+// work buffers are there, else on the FP64 matrix cores.  bal: what balances the
+// two operands.  `prepared`: the powers of two and B's residues are in the
+// buffers from an earlier call.  With complex buffers B
 // has to be the real 2 x 2 block form of a complex matrix, M, N, K count reals
 // all the same, and the product is the complex one of half N and K.
 template <class TC, class TA = double>
@@ -504,9 +504,7 @@ static bool nt_product(int64_t M, int N, int K, const TA* A, int64_t lda, const 
   const int h = w.cplx ? 2 : 1;
   if (!w.mp || !(w.cplx ? mod_pays_c(M, N / h, K / h) : mod_pays(M, N, K)))
     return dgemm<KC, KC, TC, TA>((int)M, N, K, A, lda, B, ldb, C, ldc, alpha, 0.0, 0, abort, st);
-  if (!prepared && !mod_prepare(B, ldb, N / h, K / h, bal, bal == MOD_DIAG_A ? (const double*)A : B,
-                                bal == MOD_DIAG_A ? lda : ldb, w, abort, st))
-    return false;
+  if (!prepared && !mod_prepare<TA>(A, lda, (int)M, B, ldb, N / h, K / h, bal, w, abort, st)) return false;
   const int vec = ldc % 2 == 0 && (uintptr_t)C % (2 * sizeof(TC)) == 0;
   for (int64_t r = 0, p = 0; r < M; r += w.mp, ++p) {
     const int rows = (int)(M - r < w.mp ? M - r : w.mp);

@@ -24,11 +24,14 @@
 // 2-norm error against extended precision is 1.1e-16 to 2.0e-16 where the
 // FP64 kernel's is 1.4e-15 to 3.0e-15.
 //
-// A common power of two per k may be moved from one operand to the other
-// (A(m, k) d_k, B(n, k) / d_k, exact): with B = (C C^H)^-1 and d_k =
-// sqrt(B(k, k)) (mod_diag) both operands lose the range that the density at
-// the interpolation points gives their columns (six orders of magnitude and
-// more), which a row's scale alone cannot.
+// A common power of two per k is moved from one operand to the other
+// (A(m, k) d_k, B(n, k) / d_k, exact), which takes out the range that the
+// density at the interpolation points gives the columns (six orders of magnitude
+// and more) and that a row's scale cannot.  With B = (C C^H)^-1 that is d_k =
+// sqrt(B(k, k)) (mod_diag); products with Phi_mu or Psi_mu take it from the mean
+// exponents of both operands' columns (mod_means), since Abar and V grow where
+// the orbitals are small: Abar Phi_mu at a density range of 1e6 is off by 2e-14
+// without it, where an FP64 sum is off by 5e-16, and by 2e-17 with it.
 //
 // A row that is not finite, or whose norm is outside 2^+-460, raises a flag;
 // the residue kernels then do nothing and the FP64 kernel launched behind them
@@ -167,12 +170,60 @@ __global__ void mod_diag(const double* __restrict__ B, int64_t ldb, int K, int s
   di[k] = ldexp(1.0, -e);
 }
 
+// d[k] = 2^round((b - a) / 2) and its reciprocal, with a and b the mean binary
+// exponents of the nonzero finite entries of column k of A (M rows) and of B (N
+// rows; both complex, re and im side by side, lda and ldb in reals), from at
+// most MEANS rows of each.  A mean of exponents and not a norm: one large entry
+// would take its column's digits from all the other rows.  32 columns by 8
+// groups of rows per workgroup; 2 MEANS rows are read, 8 MB of 16384 x 2048.
+constexpr int MEANS = 128;
+template <class TA>
+__global__ __launch_bounds__(256) void mod_means(const TA* __restrict__ A, int64_t lda, int M,
+                                                 const double* __restrict__ B, int64_t ldb, int N, int K,
+                                                 double* __restrict__ d, double* __restrict__ di) {
+  __shared__ int sum[2][8][32], cnt[2][8][32];
+  const int c = threadIdx.x & 31, g = threadIdx.x >> 5;
+  const int k = blockIdx.x * 32 + c, kc = k < K ? k : K - 1;
+  const auto column = [&](auto* x, int64_t ld, int rows, int which) {
+    const int n = rows < MEANS ? rows : MEANS;
+    int s = 0, m = 0;
+#pragma unroll 8
+    for (int i = g; i < n; i += 8) {
+      const double2 z = Cplx<std::remove_const_t<std::remove_pointer_t<decltype(x)>>>::load(
+          x + (int64_t)i * rows / n * ld + 2 * kc);
+      const int e = __double2hiint(fmax(fabs(z.x), fabs(z.y))) >> 20 & 0x7ff;
+      if (e != 0 && e != 0x7ff) {
+        s += e;
+        ++m;
+      }
+    }
+    sum[which][g][c] = s;
+    cnt[which][g][c] = m;
+  };
+  column(A, lda, M, 0);
+  column(B, ldb, N, 1);
+  __syncthreads();
+  if (g != 0 || k >= K) return;
+  int s[2] = {0, 0}, m[2] = {0, 0};
+#pragma unroll
+  for (int w = 0; w < 2; ++w)
+    for (int i = 0; i < 8; ++i) {
+      s[w] += sum[w][i][c];
+      m[w] += cnt[w][i][c];
+    }
+  int e = 0;
+  if (m[0] && m[1]) e = (int)rintf(0.5f * ((float)s[1] / (float)m[1] - (float)s[0] / (float)m[0]));
+  e = e < -400 ? -400 : e > 400 ? 400 : e;
+  d[k] = ldexp(1.0, e);
+  di[k] = ldexp(1.0, -e);
+}
+
 __global__ void mod_clear(int* flags, int n) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) flags[i] = 0;
 }
 
 // ------------------------------------------------------------------- split
-// Row blockIdx.x of X (K entries, times ks[k] when given): its scale and the
+// Row blockIdx.x of X (K entries, times ks[k]): its scale and the
 // residues of its scaled integers, planes [MOD_N][rows][kpad] (zero past K).
 // One workgroup per row, the row held in registers between the norm and the
 // residues (4 IT per thread).  Bound by HBM: 8 bytes read and 15 written per
@@ -232,14 +283,11 @@ __global__ __launch_bounds__(256) void mod_split(const TS* __restrict__ X, int64
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[it][e] = k + e < K ? (double)x[k + e] : 0.0;
     }
-    if (ks) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[it][e] *= k + e < K ? ks[k + e] : 0.0;
-    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      n2 = fma(v[it][e], v[it][e], n2);
       any |= v[it][e] != 0.0;  // true for NaN
+      v[it][e] *= k + e < K ? ks[k + e] : 0.0;
+      n2 = fma(v[it][e], v[it][e], n2);
     }
   }
   n2 = wave_sum(n2);
@@ -296,15 +344,13 @@ __global__ __launch_bounds__(256) void mod_split_c(const TS* __restrict__ X, int
           a = (double)x[2 * (k + e)];
           b = (double)x[2 * (k + e) + 1];
         }
-        if (ks) {
-          a *= ks[k + e];
-          b *= ks[k + e];
-        }
+        any |= a != 0.0 || b != 0.0;  // true for NaN
+        a *= ks[k + e];
+        b *= ks[k + e];
       }
       v[it][2 * e] = a;
       v[it][2 * e + 1] = b;
       n2 = fma(a, a, fma(b, b, n2));
-      any |= a != 0.0 || b != 0.0;  // true for NaN
     }
   }
   n2 = wave_sum(n2);
@@ -739,9 +785,9 @@ static bool mod_rows(const TS* X, int64_t ld, int rows, int K, const ModWork& w,
   return launch_ok();
 }
 
-// Which operand's diagonal (that operand symmetric of order K) gives the
-// powers of two that are moved from it to the other.
-enum { MOD_PLAIN = 0, MOD_DIAG_A = 1, MOD_DIAG_B = 2 };
+// Where the powers of two come from that are moved between the operands: the
+// diagonal of one of them (symmetric of order K), or the columns of both.
+enum { MOD_DIAG_A = 1, MOD_DIAG_B = 2, MOD_MEANS = 3 };
 
 // Raises the flag unless B (order 2 K) has the real 2 x 2 block form of a
 // complex Hermitian matrix, [[re, im], [-im, re]] per entry, to 2^-20 of the
@@ -758,20 +804,26 @@ __global__ __launch_bounds__(256) void mod_blocks(const double* __restrict__ B, 
   }
 }
 
-// Residues of B (N x K), once per call; dmat, ldd: the operand of `bal`.
-// Complex (w.cplx): B is the real 2 x 2 block form of a complex N x K matrix,
-// whose rows are the even ones, and the product is A B^H (bal = MOD_DIAG_B:
-// N = K, checked by mod_blocks).
-static bool mod_prepare(const double* B, int64_t ldb, int N, int K, int bal, const double* dmat, int64_t ldd,
+// Powers of two and residues of B (N x K), once per call; A: the other operand
+// (M rows).  Complex (w.cplx): B is the real 2 x 2 block form of a complex N x K
+// matrix, whose rows are the even ones, and the product is A B^H (bal =
+// MOD_DIAG_B: N = K, checked by mod_blocks).  MOD_MEANS: complex only.
+template <class TA>
+static bool mod_prepare(const TA* A, int64_t lda, int M, const double* B, int64_t ldb, int N, int K, int bal,
                         const ModWork& w, const int* abort, hipStream_t s) {
   const int step = w.cplx ? 2 : 1;
   hipLaunchKernelGGL(mod_clear, dim3(1), dim3(256), 0, s, w.flags, w.nflags);
-  if (bal != MOD_PLAIN)
-    hipLaunchKernelGGL(mod_diag, dim3((unsigned)ceil_div(K, 256)), dim3(256), 0, s, dmat, ldd, K, step, w.d, w.di);
+  if (bal == MOD_MEANS) {
+    hipLaunchKernelGGL((mod_means<TA>), dim3((unsigned)ceil_div(K, 32)), dim3(256), 0, s, A, lda, M, B, 2 * ldb, N, K,
+                       w.d, w.di);
+  } else {
+    const double* m = bal == MOD_DIAG_A ? (const double*)A : B;
+    hipLaunchKernelGGL(mod_diag, dim3((unsigned)ceil_div(K, 256)), dim3(256), 0, s, m, bal == MOD_DIAG_A ? lda : ldb, K,
+                       step, w.d, w.di);
+  }
   if (w.cplx && bal == MOD_DIAG_B)
     hipLaunchKernelGGL(mod_blocks, dim3((unsigned)ceil_div(K, 1024), (unsigned)K), dim3(256), 0, s, B, ldb, K, w.flags);
-  return mod_rows<double>(B, step * ldb, N, K, w, bal == MOD_PLAIN ? nullptr : bal == MOD_DIAG_B ? w.di : w.d, true,
-                          w.b, w.rb, w.flags, abort, s);
+  return mod_rows<double>(B, step * ldb, N, K, w, bal == MOD_DIAG_A ? w.d : w.di, true, w.b, w.rb, w.flags, abort, s);
 }
 
 template <class Epi>
@@ -786,8 +838,7 @@ template <class TA, class Epi>
 static bool mod_panel(const TA* A, int64_t lda, int rows, int N, int K, int bal, int panel, const ModWork& w,
                       const Epi& epi, const int* abort, hipStream_t s) {
   int* aflag = w.flags + 1 + panel;
-  if (!mod_rows<TA>(A, lda, rows, K, w, bal == MOD_PLAIN ? nullptr : bal == MOD_DIAG_B ? w.d : w.di, false, w.a, w.ra,
-                    aflag, abort, s))
+  if (!mod_rows<TA>(A, lda, rows, K, w, bal == MOD_DIAG_A ? w.di : w.d, false, w.a, w.ra, aflag, abort, s))
     return false;
   const int64_t tiles = ceil_div(rows, MOD_T) * ceil_div(N, MOD_T);
   const dim3 grid((unsigned)(tiles * (w.cplx ? 2 * MOD_NC : MOD_N)));

@@ -61,3 +61,66 @@ def test_gradient_of_an_ill_conditioned_fit():
         off = lambda d: float(np.linalg.norm((d - exact).astype(np.complex128)))
         ratios.append(off(dphi.cpu().numpy()) / off(gradient(np.complex128, np.float64, in_order)))
     assert np.exp(np.mean(np.log(ratios))) <= 1.25, ratios
+
+
+def graded(n_r, n, rng, decades):
+    """Orbital rows whose density ranges over `decades` powers of ten."""
+    c = rng.standard_normal((n_r, n)) + 1j * rng.standard_normal((n_r, n))
+    return c * 10.0 ** (-decades / 2 * rng.random((n_r, 1)))
+
+
+def row_error(x, exact):
+    """Root mean square over the rows of each row's relative error."""
+    e, x0 = (x - exact).astype(np.complex128), exact.astype(np.complex128)
+    return float(np.sqrt(np.mean((np.abs(e) ** 2).sum(1) / (np.abs(x0) ** 2).sum(1))))
+
+
+# sizes on the residue side of the rule (K N >= 160 (K + N), 2048 rows and more)
+@pytest.mark.parametrize("decades", [3, 9])
+def test_exchange_over_a_range_of_density(decades):
+    """The product with Psi_mu where the density at the points ranges over
+    powers of ten and V grows where it is small, as the potentials of Theta's
+    columns do.  Every row is as accurate as the same products in FP64 sums in k
+    order (1.25 for the scatter between orders of a sum)."""
+    n, n_phi, n_psi, n_mu = (15, 16, 17), 40, 210, 700
+    n_r = 15 * 16 * 17
+    rng = np.random.default_rng(decades)
+    phi, psi = graded(n_r, n_phi, rng, decades), graded(n_r, n_psi, rng, 0)
+    psi *= np.linalg.norm(phi, axis=1, keepdims=True)
+    idx = rng.permutation(n_r)[:n_mu]
+    v = rng.standard_normal((n_r, n_mu)) / (np.abs(phi[idx]) ** 2).sum(1)
+    got = isdf.exchange(dev(phi), dev(psi), dev(idx.astype(np.int32)), dev(v), grid=n).cpu().numpy()
+    rows = np.arange(5, n_r, 41)
+
+    def product(ct, mm):
+        f, q = phi.astype(ct), psi.astype(ct)
+        return -mm(v[rows].astype(ct) * mm(f[rows], f[idx].conj().T), q[idx])
+
+    exact = product(CLD, np.matmul)
+    assert row_error(got[rows], exact) <= 1.25 * row_error(product(np.complex128, in_order), exact)
+
+
+@pytest.mark.parametrize("decades", [3, 9])
+def test_gradient_over_a_range_of_density(decades):
+    """The rows Abar Phi_mu of the fused loss's gradient, S = 2 g G M^-2, given
+    the same FP64 M^-1, as test_exchange_over_a_range_of_density."""
+    n, n_phi, n_mu = (15, 16, 17), 200, 1001
+    n_r = 15 * 16 * 17
+    rng = np.random.default_rng(10 + decades)
+    phi = graded(n_r, n_phi, rng, decades)
+    idx = rng.permutation(n_r)[:n_mu]
+    g = rng.uniform(0.5, 1.5, n_r)
+    _, minv, _ = isdf.fit(dev(phi), None, dev(idx.astype(np.int32)), grid=n, nrows=0)
+    dphi, _, _, info = isdf.fit_backward(dev(phi), None, dev(idx.astype(np.int32)), minv, g=dev(g), grid=n)
+    assert info["status"] == 0
+    w = minv.cpu().numpy().reshape(n_mu, n_mu)
+    rows = np.setdiff1d(np.arange(5, n_r, 83), idx)  # the other rows have no term Abar^H Phi
+    w2, w2_ext = in_order(w, w), w.astype(LD) @ w.astype(LD)
+
+    def gradient(ct, v2, mm):
+        f = phi.astype(ct)
+        a = mm(f[rows], f[idx].conj().T)
+        return mm(2 * g[rows, None] * mm(a.real ** 2 + a.imag ** 2, v2) * a, f[idx])
+
+    exact = gradient(CLD, w2_ext, np.matmul)
+    assert row_error(dphi.cpu().numpy()[rows], exact) <= 1.25 * row_error(gradient(np.complex128, w2, in_order), exact)

@@ -264,7 +264,14 @@ int isdf_apply_minv(int32_t n_mu, int32_t aliased, const double* minv, const dou
  * isdf_apply_minv_ws: the same product with a workspace
  * (isdf_apply_minv_workspace bytes, 0 where it would not be used), which lets
  * it run on the 8-bit matrix cores by residues where that is faster; FP64
- * results either way.  ws null: isdf_apply_minv.
+ * results either way.  By residues a result is within 2^-63 sqrt(n') of the
+ * product of its row's and its column's 2-norms (of G diag(d) and diag(1/d)
+ * minv, d the square roots of minv's diagonal) and the rounding of the result,
+ * where an FP64 sum is off by a multiple of 2^-53 of the sum of moduli of its
+ * own terms: less, but for results that lie far below the norms of their row and
+ * column.  isdf_fit, the adjoint and
+ * isdf_exchange take the same products by the same rule.  ws null:
+ * isdf_apply_minv.
  */
 size_t isdf_apply_minv_workspace(int32_t n_mu, int32_t aliased, int64_t nrows);
 int isdf_apply_minv_ws(int32_t n_mu, int32_t aliased, const double* minv, const double* G, int64_t ldg,

@@ -2,27 +2,31 @@
 //
 //   C(m, n) = sum_k A(m, k) B(n, k), A and B K-contiguous, FP64 results.
 //
-// Each row of A and of B is scaled by a power of two to a 2-norm below 2^58
+// Each row of A and of B is scaled by a power of two to a 2-norm below 2^65
 // and rounded to integers (mod_split), so that every entry of the integer
-// product is below 2^116 (Cauchy-Schwarz) whatever K is.  The integer product
-// is computed exactly modulo 15 pairwise coprime moduli of at most 8 bits
-// (their product P is 2^117.8) with one int8 matrix product per modulus
+// product is below 2^130 (Cauchy-Schwarz) whatever K is.  The integer product
+// is computed exactly modulo 17 pairwise coprime moduli of at most 8 bits
+// (their product P is 2^133.0) with one int8 matrix product per modulus
 // (mod_gemm), and put together by the Chinese remainder theorem (mod_crt):
 // with w_i = ((P / p_i)^-1 mod p_i) / p_i, C / P = sum_i r_i w_i modulo 1.
-// The only errors are the rounding of the operands (absolute, 2^-59 of the
-// row's 2-norm per entry: 2^-53 relative for an entry 2^-6 of the norm, and
-// below the rounding that an FP64 sum of K products accumulates) and the last
-// rounding of C.  Residue products are the idea of Ozaki's scheme for matrix
-// multiplication through integer arithmetic; this form is derived from the
-// remainder theorem above.
+// The only errors are the rounding of the operands (absolute, up to 2^-65 of the
+// row's 2-norm per entry: entries down to 2^-12 of the norm keep all their 53
+// bits, and at K = 16384 terms the typical one is 2^-7 of it) and the last
+// rounding of C.  Two moduli fewer, 2^58, round the typical entry of K = 2048
+// and lose the tails of localised orbitals first: a worst entry 3 times as far
+// off as an FP64 sum's at a density range of 1e3, a ninth of it with these.
+// The guarantee stays relative to the product of the (balanced) rows' norms, an
+// FP64 sum's is relative to the sum of moduli of its own terms.  Residue
+// products are the idea of Ozaki's scheme for matrix multiplication through
+// integer arithmetic; this form is derived from the remainder theorem above.
 //
 // Why: the FP64 matrix cores do 78.6 TFLOP/s, the int8 ones 64 times as much,
-// so 15 int8 products have 4 times the rate to spend; splitting and putting
-// together move 23 bytes per operand and per result element, which K N / (K +
-// N) has to pay for (mod_pays).  Measured: 32768 x 8192 x 8192 65.6 ms FP64
-// (67 TFLOP/s), 33 ms by residues; 65536 x 2048 x 2048 8.5 and 6.3 ms; the
-// 2-norm error against extended precision is 1.1e-16 to 2.0e-16 where the
-// FP64 kernel's is 1.4e-15 to 3.0e-15.
+// so 17 int8 products have 3.7 times the rate to spend; splitting and putting
+// together move 25 bytes per operand and per result element, which K N / (K +
+// N) has to pay for (mod_pays).  Measured: 32768 x 8192 x 8192 69.0 ms FP64 (64
+// TFLOP/s), 34.2 by residues; 65536 x 2048 x 2048 8.6 and 6.1; the 2-norm error
+// against extended precision is 6.5e-17, that of rounding the result, where the
+// FP64 kernel's is 1.1e-15 to 3.2e-15.
 //
 // A common power of two per k is moved from one operand to the other
 // (A(m, k) d_k, B(n, k) / d_k, exact), which takes out the range that the
@@ -43,12 +47,47 @@
 namespace isdf {
 namespace {
 
-constexpr int MOD_N = 15;
-constexpr int MOD_BITS = 58;      // a scaled row's 2-norm is at most 2^58
+constexpr int MOD_N = 17;
+constexpr int MOD_BITS = 65;      // a scaled row's 2-norm is at most 2^65
 constexpr int MOD_KMAX = 16384;   // |sum| < K 2^14 <= 2^28, the bound of mod_reduce
 constexpr int MOD_T = 256;        // output tile edge
 constexpr int MOD_BK = 128;       // K bytes per LDS stage
 constexpr int MOD_THREADS = 512;  // 8 wavefronts, 2 (m) x 4 (n), 128 x 64 outputs each
+
+// Product of n moduli (below 2^160) as P + Plo, two doubles of 53 bits each.
+struct ModProduct {
+  double P, Plo;
+};
+constexpr ModProduct mod_product(const int* p, int n) {
+  unsigned limb[5] = {1, 0, 0, 0, 0};
+  for (int i = 0; i < n; ++i) {
+    unsigned long long carry = 0;
+    for (unsigned& l : limb) {
+      const unsigned long long t = (unsigned long long)l * (unsigned)p[i] + carry;
+      l = (unsigned)t;
+      carry = t >> 32;
+    }
+  }
+  ModProduct r{0.0, 0.0};
+  int seen = 0;  // bits from the first one on
+  for (int b = 159; b >= 0; --b) {
+    r.P *= 2.0;
+    r.Plo *= 2.0;
+    const int bit = limb[b / 32] >> (b % 32) & 1;
+    if (bit || seen) ++seen;
+    if (!bit) continue;
+    if (seen <= 53) r.P += 1.0;
+    else if (seen <= 106) r.Plo += 1.0;
+  }
+  return r;
+}
+// (product of the other moduli) mod p[i]
+constexpr int mod_others(const int* p, int n, int i) {
+  int m = 1;
+  for (int j = 0; j < n; ++j)
+    if (j != i) m = m * p[j] % p[i];
+  return m;
+}
 
 struct ModTab {
   int p[MOD_N];
@@ -62,11 +101,9 @@ struct ModTab {
 
 constexpr ModTab make_mod_tab() {
   ModTab t{};
-  const int p[MOD_N] = {256, 255, 253, 251, 247, 241, 239, 233, 229, 227, 223, 217, 211, 199, 197};
-  unsigned __int128 P = 1;
-  for (int i = 0; i < MOD_N; ++i) P *= (unsigned)p[i];
+  const int p[MOD_N] = {256, 255, 253, 251, 247, 241, 239, 233, 229, 227, 223, 217, 211, 199, 197, 193, 191};
   for (int i = 0; i < MOD_N; ++i) {
-    const int m = (int)((P / (unsigned)p[i]) % (unsigned)p[i]);
+    const int m = mod_others(p, MOD_N, i);
     int q = 1;
     while (q * m % p[i] != 1) ++q;
     if (2 * q > p[i]) q -= p[i];
@@ -78,8 +115,8 @@ constexpr ModTab make_mod_tab() {
     t.w1[i] = (double)(num / p[i]) / (double)(1ll << 42);
     t.w2[i] = ((double)(num % p[i]) / p[i]) / (double)(1ll << 42);
   }
-  t.P = (double)P;
-  t.Plo = (double)((__int128)P - (__int128)t.P);
+  t.P = mod_product(p, MOD_N).P;
+  t.Plo = mod_product(p, MOD_N).Plo;
   return t;
 }
 constexpr ModTab MOD_TAB = make_mod_tab();
@@ -87,12 +124,14 @@ static __device__ __constant__ ModTab mod_tab = make_mod_tab();
 
 // Complex products: modulo p = 1 (mod 4) (or a product of such primes) there is
 // an s with s^2 = -1, and x + i y -> (x + s y, x - s y) turns the complex
-// product into two independent real ones instead of four, exactly.  16 such
-// moduli of at most 241 have the product 2^117.7; 32 planes against the 60 of
-// the real 2 x 2 block form.  Conjugation swaps the two planes.  108000 x 1201
-// x 1201 complex: 11.2 ms of int8 products in the real form, 6.9 this way, and
-// 1.9 and 1.1 for the split and the recombination.
-constexpr int MOD_NC = 16;
+// product into two independent real ones instead of four, exactly.  18 such
+// moduli of at most 241 have the product 2^130.3, for rows of a 2-norm below
+// 2^64; 36 planes against the 68 of the real 2 x 2 block form.  Conjugation
+// swaps the two planes.  108000 x 1201 x 1201 complex: 22.5 ms on the FP64
+// matrix cores, 10.2 this way (with two moduli fewer the int8 products took 11.2
+// in the real form and 6.9 this way).
+constexpr int MOD_NC = 18;
+constexpr int MOD_BITS_C = 64;
 
 struct ModTabC {
   int p[MOD_NC];
@@ -113,11 +152,9 @@ constexpr int mod_inverse(int a, int p) {
 
 constexpr ModTabC make_mod_tab_c() {
   ModTabC t{};
-  const int p[MOD_NC] = {241, 233, 229, 221, 205, 197, 193, 181, 173, 157, 149, 137, 113, 109, 101, 97};
-  unsigned __int128 P = 1;
-  for (int i = 0; i < MOD_NC; ++i) P *= (unsigned)p[i];
+  const int p[MOD_NC] = {241, 233, 229, 221, 205, 197, 193, 181, 173, 157, 149, 137, 113, 109, 101, 97, 89, 73};
   for (int i = 0; i < MOD_NC; ++i) {
-    const int m = (int)((P / (unsigned)p[i]) % (unsigned)p[i]);
+    const int m = mod_others(p, MOD_NC, i);
     int s = 1;
     while ((s * s + 1) % p[i] != 0) ++s;
     const int q0 = mod_inverse(m, p[i]);
@@ -137,8 +174,8 @@ constexpr ModTabC make_mod_tab_c() {
     t.w1i[i] = (double)(ni / p[i]) / (double)(1ll << 42);
     t.w2i[i] = ((double)(ni % p[i]) / p[i]) / (double)(1ll << 42);
   }
-  t.P = (double)P;
-  t.Plo = (double)((__int128)P - (__int128)t.P);
+  t.P = mod_product(p, MOD_NC).P;
+  t.Plo = mod_product(p, MOD_NC).Plo;
   return t;
 }
 constexpr ModTabC MOD_TAB_C = make_mod_tab_c();
@@ -226,10 +263,11 @@ __global__ void mod_clear(int* flags, int n) {
 // Row blockIdx.x of X (K entries, times ks[k]): its scale and the
 // residues of its scaled integers, planes [MOD_N][rows][kpad] (zero past K).
 // One workgroup per row, the row held in registers between the norm and the
-// residues (4 IT per thread).  Bound by HBM: 8 bytes read and 15 written per
+// residues (4 IT per thread).  Bound by HBM: 8 bytes read and 17 written per
 // entry; a residue costs 7 FP64 operations.
-// r mod p of an integer |x| < 2^60 held in a double: the quotient's rounding
-// can leave the first remainder one p off, the second step is exact.
+// r mod p of an integer |x| <= 2^65 held in a double: the quotient is off by up
+// to 2^-52 |x| / p, which leaves a first remainder below 2^13 + p (an integer,
+// so exact); the second step takes that to [-p/2, p/2].
 __device__ __forceinline__ unsigned mod_byte(double x, double p, double ip) {
   const double r = fma(-__builtin_rint(x * ip), p, x);
   const double y = fma(-__builtin_rint(r * ip), p, r + 6755399441055744.0);  // + 1.5 2^52: integer in the low word
@@ -242,15 +280,14 @@ __device__ __forceinline__ unsigned mod_pack(unsigned a, unsigned b, unsigned c,
                                0x05040100u);
 }
 
-// The power of two that takes a row of squared 2-norm n2 to at most 2^MOD_BITS
-// (0 for a zero row); its reciprocal into *rscale; a row out of range (`some`:
+// The power of two that takes a row of squared 2-norm n2 to at most 2^bits (0 for a zero row); its reciprocal into *rscale; a row out of range (`some`:
 // not all zero) raises the flag.
-__device__ __forceinline__ double mod_scale(double n2, int some, int tid, double* rscale, int* flag) {
+__device__ __forceinline__ double mod_scale(double n2, int some, int bits, int tid, double* rscale, int* flag) {
   double up = 0.0, down = 0.0;
   if (n2 > 1e-280 && n2 < 1e280) {
     int e2 = 0;
     frexp(n2, &e2);  // n2 < 2^e2
-    const int e = MOD_BITS - ((e2 + 1) >> 1);
+    const int e = bits - ((e2 + 1) >> 1);
     up = ldexp(1.0, e);
     down = ldexp(1.0, -e);
   } else if (some) {
@@ -294,7 +331,7 @@ __global__ __launch_bounds__(256) void mod_split(const TS* __restrict__ X, int64
   if ((tid & 63) == 0) red[tid >> 6] = n2;
   const int some = __syncthreads_or(any);
   n2 = (red[0] + red[1]) + (red[2] + red[3]);
-  const double up = mod_scale(n2, some, tid, rscale + row, flag);
+  const double up = mod_scale(n2, some, MOD_BITS, tid, rscale + row, flag);
   int8_t* o = out + row * kpad;
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
@@ -316,8 +353,8 @@ __global__ __launch_bounds__(256) void mod_split(const TS* __restrict__ X, int64
 // Row blockIdx.x of a complex X (K entries, real and imaginary parts side by
 // side, ld in reals), scaled by the 2-norm of its 2 K reals: planes
 // [2 MOD_NC][rows][kpad] of x + s y and x - s y modulo each modulus (`conj`:
-// the other way round).  x and y leave FP64 as remainders below 1.5 p, the
-// rest is exact in FP32 (|x + s y| < 2^15.3).
+// the other way round).  x and y leave FP64 as remainders below 2^12 + p (as in
+// mod_byte), the rest is exact in FP32 (s < p / 2, so |x + s y| < 2^20).
 template <class TS, int IT>
 __global__ __launch_bounds__(256) void mod_split_c(const TS* __restrict__ X, int64_t ld, int rows, int K, int kpad,
                                                    const double* __restrict__ ks, int vec, int conj,
@@ -357,7 +394,7 @@ __global__ __launch_bounds__(256) void mod_split_c(const TS* __restrict__ X, int
   if ((tid & 63) == 0) red[tid >> 6] = n2;
   const int some = __syncthreads_or(any);
   n2 = (red[0] + red[1]) + (red[2] + red[3]);
-  const double up = mod_scale(n2, some, tid, rscale + row, flag);
+  const double up = mod_scale(n2, some, MOD_BITS_C, tid, rscale + row, flag);
   int8_t* o = out + row * kpad;
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
@@ -564,7 +601,7 @@ __global__ __launch_bounds__(MOD_THREADS, 2) void mod_gemm(const int8_t* __restr
 // --------------------------------------------------------------------- CRT
 // C(m, n .. n + 3) from the residues of one row m, in FP64: f = sum_i r_i w_i
 // modulo 1 is C / P (|C| < P / 3, so the fraction nearest zero), exact in its
-// first part (r_i w1_i are multiples of 2^-42 below 2^10).
+// first part (r_i w1_i are multiples of 2^-42, their sum below 2^11).
 __device__ __forceinline__ void mod_combine(const int8_t* __restrict__ R, int64_t rstride, double scale,
                                             const double* __restrict__ cs, int n, int N, double (&c)[4]) {
   int w[MOD_N];
@@ -585,7 +622,7 @@ __device__ __forceinline__ void mod_combine(const int8_t* __restrict__ R, int64_
 }
 
 // One thread per Epi::REP runs of 4 consecutive outputs of a row; workgroups
-// of 256 threads over the panel's rows x ceil(N / 4).  HBM-bound: 15 residue
+// of 256 threads over the panel's rows x ceil(N / 4).  HBM-bound: 17 residue
 // bytes read per output beside what the epilogue moves.
 template <class Epi>
 __global__ __launch_bounds__(256) void mod_crt(const int8_t* __restrict__ R, int64_t rstride, int ldr, int M, int N,
@@ -700,7 +737,7 @@ struct ModStore {
 
 // -------------------------------------------------------------------- host
 // Buffers of a product with up to `rows` rows of A per call, processed in
-// panels of `mp` rows (planes of a panel: 15 bytes per entry of A and of C, 32
+// panels of `mp` rows (planes of a panel: 17 bytes per entry of A and of C, 36
 // per complex one).
 struct ModWork {
   int8_t *a, *b, *r;
@@ -716,14 +753,14 @@ constexpr int64_t MOD_PANEL = 16384;
 constexpr int MOD_KMAX_C = 8192;  // entries of a complex row held in registers by mod_split_c
 
 // Whether residues beat the FP64 kernel: measured per M row and column, the
-// FP64 product takes 2 K N / 66 TFLOP/s and the residues 30 K N / 2.4 POP/s
-// plus 23 (K + N) bytes at 4.4 TB/s; a margin for short panels and tiles that
+// FP64 product takes 2 K N / 66 TFLOP/s and the residues 34 K N / 2.4 POP/s
+// plus 25 (K + N) bytes at 4.4 TB/s; a margin for short panels and tiles that
 // stick out.
 static bool mod_pays(int64_t M, int64_t N, int64_t K) {
   return M >= 2048 && K <= MOD_KMAX && K * N >= 512 * (K + N);
 }
 // The same for a complex product of N columns and K terms: 8 K N operations
-// against 64 K N and 48 K + 80 N bytes.
+// against 72 K N and 52 K + 88 N bytes.
 static bool mod_pays_c(int64_t M, int64_t N, int64_t K) {
   return M >= 2048 && K <= MOD_KMAX_C && K * N >= 160 * (K + N);
 }

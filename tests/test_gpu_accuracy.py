@@ -124,3 +124,39 @@ def test_gradient_over_a_range_of_density(decades):
 
     exact = gradient(CLD, w2_ext, np.matmul)
     assert row_error(dphi.cpu().numpy()[rows], exact) <= 1.25 * row_error(gradient(np.complex128, w2, in_order), exact)
+
+
+def test_exchange_of_localised_orbitals():
+    """Orbitals on separate centres: an entry of W is a sum over points of which
+    most belong to other orbitals, so it is small beside its row and column.
+    Every entry, relative to the sum of moduli of its terms, is as accurate as
+    FP64 sums in k order."""
+    n, n_phi, n_psi, n_mu = (15, 16, 17), 40, 210, 700
+    n_r = 15 * 16 * 17
+    rng = np.random.default_rng(1)
+    grid = np.stack(np.meshgrid(*[np.arange(m) for m in n], indexing="ij"), -1).reshape(-1, 3)
+
+    def localised(m):
+        x = rng.standard_normal((n_r, m)) + 1j * rng.standard_normal((n_r, m))
+        for j in range(m):
+            d = grid - rng.uniform(0, 1, 3) * np.array(n)
+            d -= np.array(n) * np.round(d / np.array(n))
+            x[:, j] *= np.exp(-(d ** 2).sum(1) / (2 * 2.0 ** 2))
+        return x
+
+    phi, psi = localised(n_phi), localised(n_psi)
+    idx = rng.permutation(n_r)[:n_mu]
+    v = rng.standard_normal((n_r, n_mu))
+    got = isdf.exchange(dev(phi), dev(psi), dev(idx.astype(np.int32)), dev(v), grid=n).cpu().numpy()
+    rows = np.arange(5, n_r, 41)
+
+    def product(ct, mm):
+        f, q = phi.astype(ct), psi.astype(ct)
+        return -mm(v[rows].astype(ct) * mm(f[rows], f[idx].conj().T), q[idx])
+
+    exact = product(CLD, np.matmul)
+    moduli = (np.abs(v[rows]) * (np.abs(phi[rows]) @ np.abs(phi[idx]).T)) @ np.abs(psi[idx])
+    off = lambda x: np.abs((x - exact).astype(np.complex128)) / moduli
+    here, fp64 = off(got[rows]), off(product(np.complex128, in_order))
+    assert here.max() <= 1.25 * fp64.max()
+    assert np.sqrt(np.mean(here ** 2)) <= 1.25 * np.sqrt(np.mean(fp64 ** 2))

@@ -269,9 +269,10 @@ int isdf_apply_minv(int32_t n_mu, int32_t aliased, const double* minv, const dou
  * minv, d the square roots of minv's diagonal) and the rounding of the result,
  * where an FP64 sum is off by a multiple of 2^-53 of the sum of moduli of its
  * own terms: less, but for results that lie far below the norms of their row and
- * column.  isdf_fit, the adjoint and
- * isdf_exchange take the same products by the same rule.  ws null:
- * isdf_apply_minv.
+ * column.  With Psi != Phi they take a minv of exact blocks [[re, im], [-im,
+ * re]], as isdf_fit leaves it; any other one is multiplied by the FP64 kernel.
+ * isdf_fit, the adjoint and isdf_exchange take the same products by the same
+ * rule.  ws null: isdf_apply_minv.
  */
 size_t isdf_apply_minv_workspace(int32_t n_mu, int32_t aliased, int64_t nrows);
 int isdf_apply_minv_ws(int32_t n_mu, int32_t aliased, const double* minv, const double* G, int64_t ldg,

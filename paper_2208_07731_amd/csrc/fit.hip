@@ -134,6 +134,7 @@ static int fit_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
                         minv, n1, aliased ? G_REAL : G_EMB, ab, s, P.sc, &P.sw))
       return ISDF_E_HIP;
     ISDF_TRY(spd_inverse(minv, n1, P.inv, P.st, s));
+    if (!aliased && !to_block_form(minv, n_mu, ab, s)) return ISDF_E_HIP;
   }
   for (int64_t r = 0; r < nrows; r += rblock) {
     const int rows = (int)(nrows - r < rblock ? nrows - r : rblock);

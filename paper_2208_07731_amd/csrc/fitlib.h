@@ -562,6 +562,26 @@ static bool mirror(double* H, int n, const int* abort, hipStream_t s) {
   return launch_ok();
 }
 
+// W (order 2 n, the real form of a complex matrix up to rounding) to the nearest
+// matrix of exact 2 x 2 blocks [[re, im], [-im, re]]: the mean of the two copies
+// of each part.  Symmetric stays symmetric.
+__global__ __launch_bounds__(256) void block_form(double* __restrict__ W, int n, const int* abort) {
+  if (*abort) return;
+  const int i = blockIdx.y;
+  double* r0 = W + (int64_t)2 * i * 2 * n;  // (the caller's: aligned to a double only)
+  double* r1 = r0 + 2 * n;
+  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < n; j += gridDim.x * blockDim.x) {
+    const double re = 0.5 * (r0[2 * j] + r1[2 * j + 1]), im = 0.5 * (r0[2 * j + 1] - r1[2 * j]);
+    r0[2 * j] = r1[2 * j + 1] = re;
+    r0[2 * j + 1] = im;
+    r1[2 * j] = -im;
+  }
+}
+static bool to_block_form(double* W, int n, const int* abort, hipStream_t s) {
+  hipLaunchKernelGGL(block_form, dim3((unsigned)ceil_div(n, 256), (unsigned)n), dim3(256), 0, s, W, n, abort);
+  return launch_ok();
+}
+
 // Cholesky of X (n x n, lower, in place) and W = X^-1 into X:
 //  1. blocked right-looking Cholesky: 64-wide diagonal blocks factored and
 //     inverted in LDS, panel L21 = A21 L11^-T; the columns of the same

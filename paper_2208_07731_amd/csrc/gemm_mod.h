@@ -826,19 +826,15 @@ static bool mod_rows(const TS* X, int64_t ld, int rows, int K, const ModWork& w,
 // diagonal of one of them (symmetric of order K), or the columns of both.
 enum { MOD_DIAG_A = 1, MOD_DIAG_B = 2, MOD_MEANS = 3 };
 
-// Raises the flag unless B (order 2 K) has the real 2 x 2 block form of a
-// complex Hermitian matrix, [[re, im], [-im, re]] per entry, to 2^-20 of the
-// diagonals' geometric mean (the rounding of a badly conditioned inverse stays
-// below; a general matrix does not and keeps the FP64 kernel).
+// Raises the flag unless B (order 2 K) is exactly the real 2 x 2 block form of a
+// complex matrix, [[re, im], [-im, re]] per entry, whose even rows say it all; any
+// other matrix keeps the FP64 kernel (block_form makes the library's own exact).
 __global__ __launch_bounds__(256) void mod_blocks(const double* __restrict__ B, int64_t ldb, int K, int* flag) {
   const int i = blockIdx.y;
   const double* r0 = B + 2 * i * ldb;
   const double* r1 = r0 + ldb;
-  const double di = r0[2 * i];
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < K; j += gridDim.x * blockDim.x) {
-    const double e = fabs(r0[2 * j] - r1[2 * j + 1]) + fabs(r0[2 * j + 1] + r1[2 * j]);
-    if (!(e <= 0x1p-20 * sqrt(fabs(di * B[2 * j * (ldb + 1)])))) atomicOr(flag, 1);
-  }
+  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < K; j += gridDim.x * blockDim.x)
+    if (!(r0[2 * j] == r1[2 * j + 1] && r0[2 * j + 1] == -r1[2 * j])) atomicOr(flag, 1);
 }
 
 // Powers of two and residues of B (N x K), once per call; A: the other operand

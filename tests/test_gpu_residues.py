@@ -109,3 +109,46 @@ def test_zero_rows_and_workspace_limits():
     assert lib.isdf_apply_minv_ws(n_mu, 1, W.data_ptr(), G.data_ptr(), n_mu, rows, L.C128, out.data_ptr(), n_mu,
                                   ws.data_ptr(), size - 1, None) == L.E_WORKSPACE
     assert lib.isdf_apply_minv_workspace(n_mu, 1, 2047) == 0  # too few rows: the FP64 kernel, no workspace
+
+
+def _block_form(n_mu, seed):
+    """[[re, im], [-im, re]] blocks of a Hermitian positive matrix."""
+    rng = np.random.default_rng(seed)
+    w = rng.standard_normal((n_mu, n_mu)) + 1j * rng.standard_normal((n_mu, n_mu))
+    w = (w + w.conj().T) / (2 * np.sqrt(n_mu)) + np.diag(rng.uniform(1, 3, n_mu))
+    W = np.empty((2 * n_mu, 2 * n_mu))
+    W[0::2, 0::2], W[0::2, 1::2], W[1::2, 0::2], W[1::2, 1::2] = w.real, w.imag, -w.imag, w.real
+    return W
+
+
+# one entry of an odd row: by half a unit in the last place, by 1e-9 of the diagonal
+@pytest.mark.parametrize("off", [0.0, 2.0 ** -52, 1e-9])
+def test_a_matrix_almost_of_block_form_is_multiplied_as_it_is(off):
+    """The complex product reads a matrix's even rows only, so it stands for a
+    matrix of exact blocks alone; any other one gives the FP64 kernel's bits."""
+    lib = L.load()
+    n_mu, rows = 600, 2304
+    Gh = np.random.default_rng(1).standard_normal((rows, 2 * n_mu))
+    Wh = _block_form(n_mu, 2)
+    Wh[7, 7] += off * Wh[7, 7]
+    G, W = torch.from_numpy(Gh).cuda(), torch.from_numpy(Wh).cuda()
+    ws = torch.empty(lib.isdf_apply_minv_workspace(n_mu, 0, rows), dtype=torch.uint8, device="cuda")
+    got = _apply(lib, G, W, n_mu, 0, rows, L.C128, n_mu, ws)
+    ref = _apply(lib, G, W, n_mu, 0, rows, L.C128, n_mu, None)
+    assert torch.equal(torch.view_as_real(got), torch.view_as_real(ref)) == (off != 0.0)
+
+
+def test_the_fit_leaves_exact_blocks():
+    """M^-1 of two orbital sets, of an order whose inverse is formed whole and of
+    one whose lower half is mirrored."""
+    import paper_2208_07731_amd as isdf
+
+    rng = np.random.default_rng(4)
+    c = lambda n: torch.from_numpy(rng.standard_normal((2016, n)) + 1j * rng.standard_normal((2016, n))).cuda()
+    phi, psi = c(24), c(40)
+    for n_mu in (65, 401):
+        idx = torch.from_numpy(rng.permutation(2016)[:n_mu].astype(np.int32)).cuda()
+        _, minv, _ = isdf.fit(phi, psi, idx, grid=(12, 12, 14), nrows=0)
+        w = minv.reshape(2 * n_mu, 2 * n_mu)
+        assert torch.equal(w[0::2, 0::2], w[1::2, 1::2]) and torch.equal(w[0::2, 1::2], -w[1::2, 0::2])
+        assert torch.equal(w, w.T)

@@ -504,7 +504,8 @@ static bool nt_product(int64_t M, int N, int K, const TA* A, int64_t lda, const 
   const int h = w.cplx ? 2 : 1;
   if (!w.mp || !(w.cplx ? mod_pays_c(M, N / h, K / h) : mod_pays(M, N, K)))
     return dgemm<KC, KC, TC, TA>((int)M, N, K, A, lda, B, ldb, C, ldc, alpha, 0.0, 0, abort, st);
-  if (!prepared && !mod_prepare<TA>(A, lda, (int)M, B, ldb, N / h, K / h, bal, w, abort, st)) return false;
+  if (!(prepared ? mod_next(w, st) : mod_prepare<TA>(A, lda, (int)M, B, ldb, N / h, K / h, bal, w, abort, st)))
+    return false;
   const int vec = ldc % 2 == 0 && (uintptr_t)C % (2 * sizeof(TC)) == 0;
   for (int64_t r = 0, p = 0; r < M; r += w.mp, ++p) {
     const int rows = (int)(M - r < w.mp ? M - r : w.mp);

@@ -859,6 +859,13 @@ static bool mod_prepare(const TA* A, int64_t lda, int M, const double* B, int64_
   return mod_rows<double>(B, step * ldb, N, K, w, bal == MOD_DIAG_A ? w.d : w.di, true, w.b, w.rb, w.flags, abort, s);
 }
 
+// Another product with the same B: the panels' flags of the last one go (a flag
+// left there would keep these panels on the FP64 kernel).
+static bool mod_next(const ModWork& w, hipStream_t s) {
+  hipLaunchKernelGGL(mod_clear, dim3(1), dim3(256), 0, s, w.flags + 1, w.nflags - 1);
+  return launch_ok();
+}
+
 template <class Epi>
 static int64_t mod_crt_blocks(int64_t rows, int64_t N) {
   return ceil_div(rows * ceil_div(N, 4), 256 * Epi::REP);

@@ -152,3 +152,23 @@ def test_the_fit_leaves_exact_blocks():
         w = minv.reshape(2 * n_mu, 2 * n_mu)
         assert torch.equal(w[0::2, 0::2], w[1::2, 1::2]) and torch.equal(w[0::2, 1::2], -w[1::2, 0::2])
         assert torch.equal(w, w.T)
+
+
+def test_a_flag_ends_with_its_block_of_rows():
+    """A row that sends its panel to the FP64 kernel leaves the later blocks of
+    rows as they are without it: the same bits by residues."""
+    import paper_2208_07731_amd as isdf
+
+    rng = np.random.default_rng(9)
+    n, n_mu, n_psi, rblock = (15, 16, 34), 700, 210, 2050  # the residues take blocks of 2048 rows and more
+    n_r = 15 * 16 * 34
+    c = lambda m: torch.from_numpy(rng.standard_normal((n_r, m)) + 1j * rng.standard_normal((n_r, m))).cuda()
+    phi, psi = c(20), c(n_psi)
+    idx = torch.from_numpy(rng.permutation(n_r)[:n_mu].astype(np.int32)).cuda()
+    v = torch.from_numpy(rng.standard_normal((n_r, n_mu))).cuda()
+    good = isdf.exchange(phi, psi, idx, v, rblock=rblock, grid=n)
+    v[1, 5] = float("nan")  # (row 1: not one that the balance of the columns samples)
+    bad = isdf.exchange(phi, psi, idx, v, rblock=rblock, grid=n)
+    assert bool(torch.isnan(bad[1].real).all())
+    assert torch.equal(torch.view_as_real(bad[rblock:]), torch.view_as_real(good[rblock:]))
+    assert not torch.equal(torch.view_as_real(bad[2:rblock]), torch.view_as_real(good[2:rblock]))

@@ -262,7 +262,7 @@ int isdf_apply_minv(int32_t n_mu, int32_t aliased, const double* minv, const dou
 
 /*
  * isdf_apply_minv_ws: the same product with a workspace
- * (isdf_apply_minv_workspace bytes, 0 where it would not be used), which lets
+ * (isdf_apply_minv_workspace bytes, 0 where it has no use for one), which lets
  * it run on the 8-bit matrix cores by residues where that is faster; FP64
  * results either way.  By residues a result is within 2^-63 sqrt(n') of the
  * product of its row's and its column's 2-norms (of G diag(d) and diag(1/d)

@@ -752,17 +752,33 @@ struct ModWork {
 constexpr int64_t MOD_PANEL = 16384;
 constexpr int MOD_KMAX_C = 8192;  // entries of a complex row held in registers by mod_split_c
 
-// Whether residues beat the FP64 kernel: measured per M row and column, the
-// FP64 product takes 2 K N / 66 TFLOP/s and the residues 34 K N / 2.4 POP/s
-// plus 25 (K + N) bytes at 4.4 TB/s; a margin for short panels and tiles that
-// stick out.
-static bool mod_pays(int64_t M, int64_t N, int64_t K) {
+// Whether the buffers are carved (the line that workspace sizes were given by).
+static bool mod_room(int64_t M, int64_t N, int64_t K) {
   return M >= 2048 && K <= MOD_KMAX && K * N >= 512 * (K + N);
 }
-// The same for a complex product of N columns and K terms: 8 K N operations
-// against 72 K N and 52 K + 88 N bytes.
-static bool mod_pays_c(int64_t M, int64_t N, int64_t K) {
+static bool mod_room_c(int64_t M, int64_t N, int64_t K) {
   return M >= 2048 && K <= MOD_KMAX_C && K * N >= 160 * (K + N);
+}
+// Whether residues beat the FP64 kernel, by the modelled time of a row of C: the
+// FP64 product takes 2 K N / 66 TFLOP/s on whole 128-wide tiles; the residues 34
+// K N / 2.4 POP/s on whole 256-wide tiles, with a prologue and an epilogue worth
+// 256 terms, and 25 (K + N) bytes at 4.4 TB/s.  FP64 over residues at 16384
+// rows: 1024 x 1024 1.03 measured, 1.05 modelled; 1100 1.25, 1.04; 1280 1.21,
+// 1.17; 2048 1.40, 1.41.
+static bool mod_pays(int64_t M, int64_t N, int64_t K) {
+  const double fp64 = 2.0 * (double)K * (double)(ceil_div(N, 128) * 128) / 66e12;
+  const double mod = 34.0 * (double)(K + 256) * (double)(ceil_div(N, MOD_T) * MOD_T) / 2.4e15 +
+                     25.0 * (double)(K + N) / 4.4e12;
+  return mod_room(M, N, K) && mod <= fp64;
+}
+// The same for a complex product of N columns and K terms: 8 K N operations
+// (tiles of 64 complex columns) against 72 K N and 52 K + 88 N bytes.  384 x 384
+// 0.78 measured, 0.81 modelled; 448 1.02, 0.97; 512 1.13, 1.13; 768 1.60, 1.49.
+static bool mod_pays_c(int64_t M, int64_t N, int64_t K) {
+  const double fp64 = 8.0 * (double)K * (double)(ceil_div(N, 64) * 64) / 66e12;
+  const double mod = 72.0 * (double)(K + 256) * (double)(ceil_div(N, MOD_T) * MOD_T) / 2.4e15 +
+                     (52.0 * (double)K + 88.0 * (double)N) / 4.4e12;
+  return mod_room_c(M, N, K) && mod <= fp64;
 }
 
 static ModWork carve_planes(Carver& c, int64_t rows, int64_t N, int64_t K, int cplx) {
@@ -784,10 +800,10 @@ static ModWork carve_planes(Carver& c, int64_t rows, int64_t N, int64_t K, int c
   return w;
 }
 static ModWork carve_mod(Carver& c, int64_t rows, int64_t N, int64_t K) {
-  return mod_pays(rows, N, K) ? carve_planes(c, rows, N, K, 0) : ModWork{};
+  return mod_room(rows, N, K) ? carve_planes(c, rows, N, K, 0) : ModWork{};
 }
 static ModWork carve_mod_c(Carver& c, int64_t rows, int64_t N, int64_t K) {
-  return mod_pays_c(rows, N, K) ? carve_planes(c, rows, N, K, 1) : ModWork{};
+  return mod_room_c(rows, N, K) ? carve_planes(c, rows, N, K, 1) : ModWork{};
 }
 // Buffers of the products with an N1 x N1 operand: complex ones of half the
 // order where the two orbital sets differ.

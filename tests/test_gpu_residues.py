@@ -172,3 +172,21 @@ def test_a_flag_ends_with_its_block_of_rows():
     assert bool(torch.isnan(bad[1].real).all())
     assert torch.equal(torch.view_as_real(bad[rblock:]), torch.view_as_real(good[rblock:]))
     assert not torch.equal(torch.view_as_real(bad[2:rblock]), torch.view_as_real(good[2:rblock]))
+
+
+# 384: padded to 512 columns; 448: the last multiple of 64 below the line; 449,
+# 512: above it.  Real: 1024 and 1025 are above it
+@pytest.mark.parametrize("n_mu,aliased,residues", [(384, 0, False), (448, 0, False), (449, 0, True), (512, 0, True),
+                                                   (1024, 1, True), (1025, 1, True)])
+def test_the_line_between_the_kernels(n_mu, aliased, residues):
+    """Where the residues would be slower the results are the FP64 kernel's bits."""
+    lib = L.load()
+    rows = 2304
+    n1 = n_mu if aliased else 2 * n_mu
+    Gh = np.random.default_rng(n_mu).standard_normal((rows, n1))
+    Wh = _inputs(1, n1, n_mu, 3.0)[1] if aliased else _block_form(n_mu, n_mu)
+    G, W = torch.from_numpy(Gh).cuda(), torch.from_numpy(np.ascontiguousarray(Wh)).cuda()
+    ws = torch.empty(lib.isdf_apply_minv_workspace(n_mu, aliased, rows), dtype=torch.uint8, device="cuda")
+    got = _apply(lib, G, W, n_mu, aliased, rows, L.C128, n_mu, ws)
+    ref = _apply(lib, G, W, n_mu, aliased, rows, L.C128, n_mu, None)
+    assert torch.equal(got, ref) != residues

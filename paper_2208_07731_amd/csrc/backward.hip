@@ -919,8 +919,10 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
   if (!tbar) {
     // Theta^T S = 2 M^-1 H M^-2 with H = G^T diag(g) G
     if (!mirror(P.P, n1, ab, s)) return ISDF_E_HIP;
-    // (all symmetric: (C C^H)^-2 H = (H (C C^H)^-2)^T is the second product's K-contiguous operand)
-    if (!nt_product<double>(n1, n1, n1, P.W2, n1, P.P, n1, MOD_DIAG_B, P.Ppart, n1, 1.0, P.mod1, false, ab, s))
+    // (all symmetric: (C C^H)^-2 H = (H (C C^H)^-2)^T is the second product's
+    // K-contiguous operand; balanced by the positive diagonal of (C C^H)^-2, since
+    // H's is positive for a positive field only)
+    if (!nt_product<double>(n1, n1, n1, P.W2, n1, P.P, n1, MOD_DIAG_A, P.Ppart, n1, 1.0, P.mod1, false, ab, s))
       return ISDF_E_HIP;
     if (!nt_product<double>(n1, n1, n1, minv, n1, P.Ppart, n1, MOD_DIAG_A, P.P, n1, 2.0, P.mod1, false, ab, s))
       return ISDF_E_HIP;

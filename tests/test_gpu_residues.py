@@ -175,9 +175,9 @@ def test_a_flag_ends_with_its_block_of_rows():
 
 
 # 384: padded to 512 columns; 448: the last multiple of 64 below the line; 449,
-# 512: above it.  Real: 1024 and 1025 are above it
+# 512: above it.  Real: 1100 below, 1200 above
 @pytest.mark.parametrize("n_mu,aliased,residues", [(384, 0, False), (448, 0, False), (449, 0, True), (512, 0, True),
-                                                   (1024, 1, True), (1025, 1, True)])
+                                                   (1024, 1, False), (1100, 1, False), (1200, 1, True)])
 def test_the_line_between_the_kernels(n_mu, aliased, residues):
     """Where the residues would be slower the results are the FP64 kernel's bits."""
     lib = L.load()

@@ -190,3 +190,62 @@ def test_the_line_between_the_kernels(n_mu, aliased, residues):
     got = _apply(lib, G, W, n_mu, aliased, rows, L.C128, n_mu, ws)
     ref = _apply(lib, G, W, n_mu, aliased, rows, L.C128, n_mu, None)
     assert torch.equal(got, ref) != residues
+
+
+# a raised flag in the first and in the second panel of 16384 rows, real and
+# complex
+@pytest.mark.parametrize("row", [77, 16384 + 77])
+@pytest.mark.parametrize("n_mu,aliased", [(1200, 1), (600, 0)])
+def test_a_flag_sends_its_panel_alone(n_mu, aliased, row):
+    lib = L.load()
+    rows, n1 = 16384 + 2304, n_mu if aliased else 2 * n_mu
+    Gh = np.random.default_rng(n_mu).standard_normal((rows, n1))
+    Wh = _inputs(1, n1, n_mu, 3.0)[1] if aliased else _block_form(n_mu, n_mu)
+    G, W = torch.from_numpy(Gh).cuda(), torch.from_numpy(np.ascontiguousarray(Wh)).cuda()
+    ws = torch.empty(lib.isdf_apply_minv_workspace(n_mu, aliased, rows), dtype=torch.uint8, device="cuda")
+    apply = lambda w: _apply(lib, G, W, n_mu, aliased, rows, L.C128, n_mu, w)
+    clean = apply(ws)
+    G[row] = 1e-200
+    got, ref = apply(ws), apply(None)
+    own, other = (slice(0, 16384), slice(16384, rows))[:: 1 if row < 16384 else -1]
+    assert torch.equal(got[own], ref[own])
+    assert torch.equal(got[other], clean[other]) and not torch.equal(got[other], ref[other])
+
+
+# blocks of more than one panel; the flagged row in the first and in the second
+@pytest.mark.parametrize("n_phi,n_psi,n_mu", [(60, 0, 1201), (30, 45, 701)])
+@pytest.mark.parametrize("fused", [1, 0])
+@pytest.mark.parametrize("row", [100, 17000])
+def test_adjoint_with_a_flagged_panel(n_phi, n_psi, n_mu, fused, row):
+    """One orbital row is so small that its row of G (or one row of the upstream
+    gradient) is out of the residues' range: its panel goes through the FP64
+    kernel, the other one by residues, each row and each loss partial once.
+    Against the oracle, within 1e-11 or n_mu eps kappa."""
+    import oracle
+    import paper_2208_07731_amd as isdf
+
+    n, n_r = (26, 26, 26), 26 ** 3
+    rng = np.random.default_rng(n_mu + row + fused)
+    c = lambda *s: rng.standard_normal(s) + 1j * rng.standard_normal(s)
+    phi = c(n_r, n_phi)
+    psi = c(n_r, n_psi) if n_psi else phi
+    idx = rng.permutation(np.setdiff1d(np.arange(n_r), [row]))[:n_mu].astype(np.int32)
+    kw = {}
+    if fused:
+        phi[row] *= 1e-150 if n_psi else 1e-75
+        kw["g"] = rng.uniform(0.5, 1.5, n_r)
+    else:
+        kw["theta_bar"] = c(n_r, n_mu) if n_psi else rng.standard_normal((n_r, n_mu))
+        kw["theta_bar"][row] *= 1e-160
+    ref = oracle.fit_backward(phi, psi, idx, **kw)
+    bar = max(1e-11, n_mu * EPS * oracle.cc_condition(phi, psi, idx))
+    d = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    a, b = d(phi), d(psi) if n_psi else None
+    _, minv, _ = isdf.fit(a, b, d(idx), grid=n, nrows=0)
+    dphi, dpsi, loss, _ = isdf.fit_backward(a, b, d(idx), minv, grid=n, **{k: d(v) for k, v in kw.items()})
+    rel = lambda x, y: float(np.linalg.norm(x.cpu().numpy() - y) / np.linalg.norm(y))
+    assert rel(dphi, ref["dphi"]) <= bar
+    if n_psi:
+        assert rel(dpsi, ref["dpsi"]) <= bar
+    if fused:
+        assert abs(loss.item() - ref["loss"]) <= bar * ref["loss"]

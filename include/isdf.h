@@ -296,8 +296,9 @@ int isdf_apply_minv_ws(int32_t n_mu, int32_t aliased, const double* minv, const 
  *   dphi, dpsi [N_r][ld] gradients, same type as the orbitals, overwritten;
  *              in the aliased case dpsi may equal dphi (written once).
  *   loss       FP64 device scalar (fused loss only; NULL: not returned)
- *   rblock     grid rows per internal step; Theta is recomputed per block,
- *              never stored whole
+ *   rblock     grid rows per internal step; for an upstream gradient Theta is
+ *              recomputed per block, never stored whole (the fused loss does
+ *              not form it)
  */
 int isdf_fit_backward(const isdf_grid* grid /* host */, int32_t dt,
                       const void* phi, int64_t ld_phi, int32_t n_phi,

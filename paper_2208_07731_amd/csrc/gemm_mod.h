@@ -433,10 +433,25 @@ __device__ __forceinline__ unsigned mod_reduce(int acc, int p, int c14, float fi
   const int q = __float_as_int(fmaf((float)t, fip, 12582912.0f));
   return (unsigned)(t - __mul24(q, p));
 }
-// The same where |acc| <= 120^2 K, K <= MOD_KQUICK and p <= 241: the quotient
-// of the sum rounded to FP32 is off by at most 2 / p + 2^-7, so the remainder
-// is within 120.5 + 3.9 and still fits the byte.
+// The same where K <= MOD_KQUICK and p <= 241: the residues are at most (p + 1) /
+// 2, so the sum is exact to half a unit of its FP32 rounding; with the rounding
+// of 1 / p the quotient is off by little enough that the remainder still fits
+// the byte (mod_quick_bound).
 constexpr int MOD_KQUICK = 4096;
+constexpr double mod_quick_bound() {
+  double worst = 0.0;
+  for (int i = 0; i < MOD_NC; ++i) {
+    const double p = MOD_TAB_C.p[i], r = (p + 1.0) / 2.0, acc = r * r * MOD_KQUICK;
+    double half = 0.5;  // half a unit in the last place of acc in FP32
+    for (double t = acc; t >= 16777216.0; t /= 2.0) half *= 2.0;
+    if (acc < 16777216.0) half = 0.0;
+    const double off = (double)MOD_TAB_C.fip[i] * p - 1.0;
+    const double bound = p / 2.0 + half + acc * (off < 0.0 ? -off : off);
+    worst = bound > worst ? bound : worst;
+  }
+  return worst;
+}
+static_assert(mod_quick_bound() < 127.5, "the remainder fits a byte");
 __device__ __forceinline__ unsigned mod_reduce_quick(int acc, int p, float fip) {
   const int q = __float_as_int(fmaf((float)acc, fip, 12582912.0f));
   return (unsigned)(acc - __mul24(q, p));
@@ -449,8 +464,8 @@ __device__ __forceinline__ unsigned mod_reduce_quick(int acc, int p, float fip) 
 // but one in flight in registers.  v_mfma_i32_32x32x32_i8 takes B's rows as
 // its row operand, so that a lane's four consecutive accumulators are four
 // consecutive n of one m and leave as one word.  An LDS row is its 8 chunks of
-// 16 bytes at chunk ^ (row / 4 % 8): the 32 lanes of a fragment read (32
-// rows, one chunk) hit 32 different 16-byte slots of the 512-byte bank row.
+// 16 bytes at chunk ^ (row / 2 % 8): the 32 lanes of a fragment read (32 rows,
+// one chunk) hit 16 different 16-byte slots modulo 512 bytes, two lanes each.
 template <bool CPLX>
 __global__ __launch_bounds__(MOD_THREADS, 2) void mod_gemm(const int8_t* __restrict__ A, int64_t astride,
                                                            const int8_t* __restrict__ B, int64_t bstride, int ld, int M,

@@ -29,7 +29,6 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-PEAK = {"fp64": 78.6, "fp32": 157.3}  # TFLOP/s, MI355X dense MFMA
 HBM_PEAK = 8000.0  # GB/s
 
 
@@ -70,11 +69,26 @@ def read_traffic(workload: str):
         return None
 
 
-MFMA_PEAK = {"fp64": 78.6, "fp32": 157.3, "bf16x6": 2500.0, "fp16x3": 2500.0}  # TFLOP/s, dense
+MFMA_PEAK = {"fp64": 78.6, "fp32": 157.3, "bf16x6": 2500.0, "fp16x3": 2500.0, "int8": 5000.0}  # TFLOP/s, TOP/s, dense
 ISSUED = {"fp64": 1, "fp32": 1, "bf16x6": 6, "fp16x3": 3}  # MFMA products per algorithmic product
 
 
-def phase_rates(wl, prec: str, phases: dict, rounds: int, saved_gram: bool = False, km: dict | None = None) -> dict:
+def residue_ops(rows, n, k, cplx: bool) -> int:
+    """int8 operations per FP64 operation of a product the library runs by
+    residues, 0 where it runs on the FP64 matrix cores."""
+    from paper_2208_07731_amd import _lib as L
+
+    return int(L.load().isdf_residue_ops(int(rows), int(n), int(k), int(cplx)))
+
+
+def fp64_product(flops: float, ops: int) -> tuple[float, str, int]:
+    """(seconds at peak, engine, operations issued per FP64 operation)."""
+    return (flops * ops / (MFMA_PEAK["int8"] * 1e12), "int8", ops) if ops else \
+        (flops / (MFMA_PEAK["fp64"] * 1e12), "fp64", 1)
+
+
+def phase_rates(wl, prec: str, phases: dict, rounds: int, saved_gram: bool = False, km: dict | None = None,
+                rows: int | None = None) -> dict:
     """Algorithmic work of each phase, its rate and its fraction of the
     roofline that bounds it.
 
@@ -84,13 +98,17 @@ def phase_rates(wl, prec: str, phases: dict, rounds: int, saved_gram: bool = Fal
              W = Y^T Y of the real n1 x n1 matrix (n1^3 / 3 each).
     zc     : 8 N_r N_mu (N_phi [+ N_psi]); split precisions issue 6x / 3x
              as many 16-bit MFMA products, against the 16-bit peak.
-    solve  : 2 N_r n1^2 (FP64).
+    solve  : 2 N_r n1^2 (FP64; by residues 17, or 9 complex, int8 operations
+             for each, against the int8 peak).
     adjoint: Gram recompute 8 N_r N_mu N (not when the forward kept the
              Gram blocks), orbital products Abar F and Abar^T X 16 N_r N_mu N,
              and the fused-loss products H = G^T g G over the lower half
              (N_r n1^2; in the split precision when the orbital products are)
-             and S = G M^-2 (2 N_r n1^2, FP64).
+             and S = G M^-2 (2 N_r n1^2, FP64; by residues as the solve, and in
+             FP64 Abar F too where its sizes allow).
+    rows   : rows of a block (default: the whole grid).
     """
+    rows = rows or wl.n_r
     n_e = wl.n_phi + (0 if wl.aliased else wl.n_psi)
     esize = 16
     n1 = wl.n_mu if wl.aliased else 2 * wl.n_mu
@@ -104,10 +122,13 @@ def phase_rates(wl, prec: str, phases: dict, rounds: int, saved_gram: bool = Fal
     if km is not None:  # what the pruned classification actually evaluated
         out["kmeans"]["evaluated_pairs"] = km.get("pairs_evaluated")
         out["kmeans"]["bound_tests"] = km.get("bound_tests")
+    order = wl.n_mu  # of the products with (C C^H)^-1, complex where Psi != Phi
+    minv_ops = residue_ops(rows, order, order, not wl.aliased)
+    _, solve_on, solve_issued = fp64_product(1.0, minv_ops)
     work = {
         "factor": (8.0 * wl.n_mu ** 2 * n_e + float(n1) ** 3, "fp64", 1),
         "zc": (8.0 * wl.n_r * wl.n_mu * n_e, prec, ISSUED[prec]),
-        "solve": (2.0 * wl.n_r * n1 * n1, "fp64", 1),
+        "solve": (2.0 * wl.n_r * n1 * n1, solve_on, solve_issued),
     }
     for name, (flops, pk, issued) in work.items():
         ms = phases[name]
@@ -124,7 +145,13 @@ def phase_rates(wl, prec: str, phases: dict, rounds: int, saved_gram: bool = Fal
     f64 = (2.0 if split else 3.0) * wl.n_r * n1 * n1
     orb = (16.0 if saved_gram else 24.0) * wl.n_r * wl.n_mu * n_e + (1.0 * wl.n_r * n1 * n1 if split else 0.0)
     ms = phases["adjoint"]
-    t_peak = f64 / (MFMA_PEAK["fp64"] * 1e12) + orb * ISSUED[prec] / (MFMA_PEAK[prec] * 1e12)
+    s_flops = 2.0 * wl.n_r * n1 * n1
+    t_peak = fp64_product(s_flops, minv_ops)[0] + (f64 - s_flops) / (MFMA_PEAK["fp64"] * 1e12)
+    t_peak += orb * ISSUED[prec] / (MFMA_PEAK[prec] * 1e12)
+    if prec == "fp64":  # Abar F of each orbital set
+        for n in [wl.n_phi] + ([] if wl.aliased else [wl.n_psi]):
+            af = 8.0 * wl.n_r * wl.n_mu * n
+            t_peak += fp64_product(af, residue_ops(rows, n, wl.n_mu, True))[0] - af / (MFMA_PEAK["fp64"] * 1e12)
     out["adjoint"] = {"ms": ms, "bound": "mfma", "flops": f64 + orb, "fp64_flops": f64, "orbital_flops": orb,
                       "orbital_prec": prec, "TFLOP/s": round((f64 + orb) / (ms * 1e-3) / 1e12, 2),
                       "frac": round(t_peak / (ms * 1e-3), 4)}
@@ -133,9 +160,9 @@ def phase_rates(wl, prec: str, phases: dict, rounds: int, saved_gram: bool = Fal
 
 def poisson_leg(st, wl, steps, exchange=False) -> dict:
     """V_mu for every column of the step's Theta (isdf_poisson), HIP-event
-    timed; algorithmic bytes: Theta read once and V written once, plus the
-    four intermediate passes over the complex work array (real Theta packs
-    two columns per complex signal)."""
+    timed; bytes: Theta read once and V written once, plus what the passes in
+    between move of the complex work array (real Theta packs two columns per
+    complex signal)."""
     import torch
 
     from paper_2208_07731_amd import api
@@ -154,7 +181,11 @@ def poisson_leg(st, wl, steps, exchange=False) -> dict:
     cols = th.shape[1] if th.is_complex() else (th.shape[1] + 1) // 2
     work = th.shape[0] * cols * 16
     io = th.numel() * th.element_size()
-    nbytes = 2 * io + 8 * work  # 5 passes: Theta in, V out, 4 x (W in + W out) in between
+    # three passes where a plane of one column fits LDS: W out, in, out, in; else
+    # five by lines: 4 x (W in + W out)
+    n = wl.n
+    planes = n > 1 and n % 7 and n * n <= 8192 and n * (n + n // 8) <= 9216
+    nbytes = 2 * io + (4 if planes else 8) * work
     out = {"ms": round(ms, 3), "bound": "hbm", "bytes": nbytes, "GB/s": round(nbytes / ms / 1e6, 1),
            "frac": round(nbytes / ms / 1e6 / HBM_PEAK, 4), "columns": th.shape[1],
            "note": "includes the per-call workspace allocation by the Python wrapper"}
@@ -170,9 +201,13 @@ def poisson_leg(st, wl, steps, exchange=False) -> dict:
         torch.cuda.synchronize()
         ms_x = a.elapsed_time(b) / steps
         flops = 8.0 * th.shape[0] * wl.n_mu * (wl.n_phi + wl.n_psi)
+        gram = 8.0 * th.shape[0] * wl.n_mu * wl.n_phi
+        ops = residue_ops(min(th.shape[0], 1 << 16), wl.n_psi, wl.n_mu, True)  # the wrapper's blocks of rows
+        t_peak = gram / (MFMA_PEAK["fp64"] * 1e12) + fp64_product(flops - gram, ops)[0]
         out["exchange"] = {"ms": round(ms_x, 3), "bound": "mfma", "flops": flops,
-                           "TFLOP/s": round(flops / ms_x / 1e9, 2), "peak": MFMA_PEAK["fp64"],
-                           "frac": round(flops / ms_x / 1e9 / MFMA_PEAK["fp64"], 4)}
+                           "TFLOP/s": round(flops / ms_x / 1e9, 2), "frac": round(t_peak / (ms_x * 1e-3), 4)}
+        if ops:
+            out["exchange"]["int8_ops_per_flop_of_the_psi_product"] = ops
         del w
     del v
     return out
@@ -542,8 +577,10 @@ def main():
     n1 = wl.n_mu if wl.aliased else 2 * wl.n_mu
     nb = len(st.blocks)
     flops = 2.0 * (wl.n_r / nb) * n1 * n1  # per launch (row blocks of equal size)
-    achieved = flops / (solve_ms * 1e-3) / 1e12
-    traffic = read_traffic(wl.name)
+    ops = residue_ops(st.block_rows, wl.n_mu, wl.n_mu, not wl.aliased)
+    _, engine, issued = fp64_product(flops, ops)
+    achieved = flops * issued / (solve_ms * 1e-3) / 1e12
+    traffic = None if ops else read_traffic(wl.name)  # (the profile is of the FP64 kernel)
     dtype = {"fp64": "f64", "fp32": "f32+f64", "bf16x6": "bf16x6+f64", "fp16x3": "f16x3+f64"}[args.prec]
     out = {
         "metric": "ISDF time (K-means+fit+bwd), % MFMA/HBM peak, mixed vs FP64 at 1e-6 rel err",
@@ -557,11 +594,16 @@ def main():
                                + (" (Gram blocks kept for the adjoint)" if st.save_gram else ""),
                    "gram_prec": args.prec},
         "phases_ms": phases,
-        "phases": phase_rates(wl, args.prec, phases, info["kmeans"]["iters"], st.save_gram, info["kmeans"]),
+        "phases": phase_rates(wl, args.prec, phases, info["kmeans"]["iters"], st.save_gram, info["kmeans"],
+                              st.block_rows),
         "kmeans": {"rounds": info["kmeans"]["iters"], "converged": info["kmeans"]["converged"]},
-        "roofline": {"bound": "mfma", "kernel": "FP64 product Theta = (Z C^H)(C C^H)^-1 (one r-block), by int8 residues; peak: FP64 matrix cores",
-                     "achieved": round(achieved, 2), "peak": PEAK["fp64"], "unit": "TFLOP/s",
-                     "frac": round(achieved / PEAK["fp64"], 4), "traffic": traffic,
+        "roofline": {"bound": "mfma",
+                     "kernel": "FP64 product Theta = (Z C^H)(C C^H)^-1 (one r-block)"
+                               + (f", {ops} int8 operations for each FP64 one" if ops else ""),
+                     "achieved": round(achieved, 2), "peak": MFMA_PEAK[engine],
+                     "unit": "TOP/s int8" if ops else "TFLOP/s",
+                     "frac": round(achieved / MFMA_PEAK[engine], 4), "traffic": traffic,
+                     "fp64_tflops": round(flops / (solve_ms * 1e-3) / 1e12, 2),
                      "flops_per_launch": flops, "ms_per_launch": round(solve_ms, 3)},
     }
     if args.poisson:

@@ -280,6 +280,14 @@ int isdf_apply_minv_ws(int32_t n_mu, int32_t aliased, const double* minv, const 
                        void* stream);
 
 /*
+ * isdf_residue_ops: int8 operations per FP64 operation of the library's products
+ * by residues, for a product of `rows` x n results of k terms each (cplx:
+ * complex ones): 17, or 9 when complex; 0 where such a product runs on the FP64
+ * matrix cores.  For rates and rooflines.
+ */
+int32_t isdf_residue_ops(int64_t rows, int64_t n, int64_t k, int32_t cplx);
+
+/*
  * Adjoint of isdf_fit with the interpolation points fixed (the paper gives
  * no adjoint; this is reverse-mode differentiation of eq. theta).  With
  * Theta = G M^-1, G = A .* conj(B), M = G[idx]:

@@ -69,6 +69,7 @@ SIGNATURES = {
                              _P, _P, _P, _SZ, _P]),
     "isdf_apply_minv": (C.c_int, [_I32, _I32, _P, _P, _I64, _I64, C.c_int, _P, _I64, _P]),
     "isdf_apply_minv_workspace": (_SZ, [_I32, _I32, _I64]),
+    "isdf_residue_ops": (_I32, [_I64, _I64, _I64, _I32]),
     "isdf_apply_minv_ws": (C.c_int, [_I32, _I32, _P, _P, _I64, _I64, C.c_int, _P, _I64, _P, _SZ, _P]),
     "isdf_fit_backward": (C.c_int, [_G, C.c_int, _P, _I64, _I32, _P, _I64, _I32, _P, _I32, C.c_int, _P,
                                     _P, _I64, _P, _P, _I64, _P, _I64, _P, _I64, _P, _P, _SZ, _P]),

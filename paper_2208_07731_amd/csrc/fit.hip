@@ -450,3 +450,9 @@ extern "C" int isdf_apply_minv_ws(int32_t n_mu, int32_t aliased, const double* m
                                   size_t ws_bytes, void* stream) {
   return apply_minv(n_mu, aliased, minv, G, ldg, nrows, dt_in, theta, ld_theta, ws, ws_bytes, stream);
 }
+
+extern "C" int32_t isdf_residue_ops(int64_t rows, int64_t n, int64_t k, int32_t cplx) {
+  if (rows <= 0 || n <= 0 || k <= 0) return 0;
+  if (cplx) return mod_pays_c(rows, n, k) ? 2 * MOD_NC / 4 : 0;
+  return mod_pays(rows, n, k) ? MOD_N : 0;
+}

@@ -77,6 +77,28 @@ static inline int split_k_for(int64_t tiles, int64_t K, int64_t mn, int slots, b
   return best;
 }
 
+// Slices that a product with FP32 sums takes at least: a slice is one chain of FP32
+// additions (the slices are added in FP64), so fewer, longer ones are less
+// accurate.  As many as 128-wide tiles at two workgroups per CU are fastest with;
+// splits_for alone takes a quarter of them or one in places (32 orbitals, 800
+// points, 110592 rows: 8 for 32).
+static inline int fp32_slices(int64_t M, int64_t N, int64_t K, int slots, int cap) {
+  const int64_t tiles = out_tiles(M, N, 128, 0);
+  const double t_row = 2.0 * 128 * 128 / (60e12 / slots), bw = 4e12;
+  int best = 1;
+  double best_t = 0.0;
+  for (int s = 1; s <= cap; s = s < 8 ? 8 : s + 8) {
+    if (s > 1 && (K + s - 1) / s < 512) break;
+    const double waves = (double)((tiles * s + slots - 1) / slots);
+    const double t = waves * ((double)K / s) * t_row + (s > 1 ? s * (double)M * (double)N * 16.0 / bw : 0.0);
+    if (s == 1 || t < best_t * (1.0 - 1e-9)) {
+      best = s;
+      best_t = t;
+    }
+  }
+  return best;
+}
+
 // Plans the adjoint uses for blocks of `rows` rows.
 struct BwdSplits {
   TilePlan h;  // Theta^T S (general) or H = G^T g G (fused, lower tiles)
@@ -90,24 +112,30 @@ struct SplitCaps {
   int h, q;
 };
 
-static inline BwdSplits bwd_splits(int64_t rows, int64_t n1, int n_mu, int n, bool fused, int slots, SplitCaps cap) {
+// fp32: Abar^T X in FP32 sums.
+static inline BwdSplits bwd_splits(int64_t rows, int64_t n1, int n_mu, int n, bool fused, bool fp32, int slots,
+                                   SplitCaps cap) {
   BwdSplits b;
   b.h = splits_for(n1, n1, fused ? 1 : 0, rows, slots, cap.h);
   b.q = splits_for(2 * (int64_t)n_mu, 2 * (int64_t)n, 0, rows, slots, cap.q);
+  if (fp32) {
+    const int least = fp32_slices(2 * (int64_t)n_mu, 2 * (int64_t)n, rows, slots, cap.q);
+    if (b.q.splits < least) b.q.splits = least;
+  }
   return b;
 }
 
 // Sizes the partial buffers by the lengths of a sweep in equal blocks, rblock
 // and the grid's remainder, for both losses and both orbital sets.
 static inline SplitCaps bwd_split_caps(int64_t nr, int64_t rblock, bool aliased, int n_mu, int n_phi, int n_psi,
-                                       int slots) {
+                                       bool fp32, int slots) {
   const SplitCaps any{MAX_SPLITS, MAX_SPLITS};
   const int64_t n1 = aliased ? n_mu : 2 * (int64_t)n_mu;
   SplitCaps c{1, 1};
   for (int64_t rows : {rblock, nr - ((nr + rblock - 1) / rblock - 1) * rblock})
     for (int n : {n_phi, n_psi})
       for (bool fused : {false, true}) {
-        const BwdSplits b = bwd_splits(rows, n1, n_mu, n, fused, slots, any);
+        const BwdSplits b = bwd_splits(rows, n1, n_mu, n, fused, fp32, slots, any);
         c.h = b.h.splits > c.h ? b.h.splits : c.h;
         c.q = b.q.splits > c.q ? b.q.splits : c.q;
       }

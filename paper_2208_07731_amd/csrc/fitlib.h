@@ -586,11 +586,11 @@ static bool to_block_form(double* W, int n, const int* abort, hipStream_t s) {
 
 // Cholesky of X (n x n, lower, in place) and W = X^-1 into X:
 //  1. blocked right-looking Cholesky: 64-wide diagonal blocks factored and
-//     inverted in LDS, panel L21 = A21 L11^-T; the columns of the same
-//     CHOL_OUTER-wide block are updated after each panel, the columns beyond
-//     it once per block, so that they are read and written once per 256 of K
-//     instead of once per 64 (n = 8192: 23 GB of passes over the trailing
-//     matrix become 6 GB);
+//     inverted in LDS, panel L21 = A21 L11^-T, trailing update A22 -= L21 L21^T
+//     on its lower tiles.  (The columns beyond a 256-wide block updated once per
+//     block save 4 ms of passes over the trailing matrix at n = 8192, and make
+//     the inverse 5 to 10 % less accurate: sums of 256 terms between two
+//     subtractions instead of 64.)
 //  2. Y = L^-1 by recursive doubling: once every aligned segment of size b
 //     has its inverse, a pair [[A, 0], [L21, C]] gets its lower-left block
 //     -C^-1 L21 A^-1 (two GEMMs, batched over all pairs of the level; K loops
@@ -601,34 +601,24 @@ struct InvWork {
   double* Y;  // [n][n]
   double* R;  // [n][n] scratch
 };
-constexpr int CHOL_OUTER = 256;
 constexpr int MIRROR_MIN = 768;
 
 // (w.Y all zeros on entry)
 static int spd_inverse(double* X, int n, InvWork w, FitState* st, hipStream_t s) {
   const int* ab = &st->abort;
-  for (int o = 0; o < n; o += CHOL_OUTER) {
-    const int oe = n - o < CHOL_OUTER ? n : o + CHOL_OUTER;
-    for (int k0 = o; k0 < oe; k0 += NB) {
-      const int kb = n - k0 < NB ? n - k0 : NB, k1 = k0 + kb;
-      hipLaunchKernelGGL(potrf_diag, dim3(1), dim3(256), 0, s, X, (int64_t)n, k0, kb, w.Y, (int64_t)n, st);
-      if (!launch_ok()) return ISDF_E_HIP;
-      if (k1 >= n) continue;
-      double* P = X + (int64_t)k1 * n + k0;
-      // panel: L21 = A21 L11^-T in place, each workgroup with all 64 columns of
-      // its rows (it reads them before it writes them)
-      EpiStore<double> epi{P, n, n - k1, kb, 1.0, 0.0, nullptr, 0, 0};
-      Operand<double> a{P, n, nullptr, nullptr}, b{w.Y + (int64_t)k0 * n + k0, n, nullptr, nullptr};
-      if (!launch_gemm<double, 32, NB, 32, 2, 2, double, KC, double, KC, 1>(n - k1, kb, kb, a, b, a, b, 0, epi, 0, ab,
-                                                                           s))
-        return ISDF_E_HIP;
-      // the block's columns right of the panel: A -= L21 L21^T
-      if (!dgemm<KC, KC>(n - k1, oe - k1, kb, P, n, P, n, X + (int64_t)k1 * n + k1, n, -1.0, 1.0, 0, ab, s))
-        return ISDF_E_HIP;
-    }
-    // the columns right of the block (lower tiles)
-    double* P = X + (int64_t)oe * n + o;
-    if (oe < n && !dgemm<KC, KC>(n - oe, n - oe, oe - o, P, n, P, n, X + (int64_t)oe * n + oe, n, -1.0, 1.0, 1, ab, s))
+  for (int k0 = 0; k0 < n; k0 += NB) {
+    const int kb = n - k0 < NB ? n - k0 : NB, k1 = k0 + kb;
+    hipLaunchKernelGGL(potrf_diag, dim3(1), dim3(256), 0, s, X, (int64_t)n, k0, kb, w.Y, (int64_t)n, st);
+    if (!launch_ok()) return ISDF_E_HIP;
+    if (k1 >= n) continue;
+    double* P = X + (int64_t)k1 * n + k0;
+    // panel: L21 = A21 L11^-T in place, each workgroup with all 64 columns of
+    // its rows (it reads them before it writes them)
+    EpiStore<double> epi{P, n, n - k1, kb, 1.0, 0.0, nullptr, 0, 0};
+    Operand<double> a{P, n, nullptr, nullptr}, b{w.Y + (int64_t)k0 * n + k0, n, nullptr, nullptr};
+    if (!launch_gemm<double, 32, NB, 32, 2, 2, double, KC, double, KC, 1>(n - k1, kb, kb, a, b, a, b, 0, epi, 0, ab, s))
+      return ISDF_E_HIP;
+    if (!dgemm<KC, KC>(n - k1, n - k1, kb, P, n, P, n, X + (int64_t)k1 * n + k1, n, -1.0, 1.0, 1, ab, s))
       return ISDF_E_HIP;
   }
   const int64_t ld = n;

@@ -192,3 +192,80 @@ def test_gradient_of_a_loss_field_of_either_sign(sign):
     ref_psi[idx] += bbar.conj().T @ psi
     assert row_error(dphi.cpu().numpy()[idx], ref_phi[idx]) <= 1e-11
     assert row_error(dpsi.cpu().numpy()[idx], ref_psi[idx]) <= 1e-11
+
+
+def fma(a, b, c):
+    return (a.astype(LD) * b + c).astype(np.float64)
+
+
+def chain(a, b):
+    """a @ b by fused multiply-adds in k order."""
+    c = np.zeros((a.shape[0], b.shape[1]))
+    for k in range(a.shape[1]):
+        c = fma(a[:, k, None], b[None, k], c)
+    return c
+
+
+def blocked_inverse(m):
+    """m^-1 by the right-looking Cholesky of 64-wide blocks, the doubling of the
+    blocks' inverses and Y^T Y, in FP64."""
+    n = len(m)
+    x, y = m.copy(), np.zeros((n, n))
+    for k0 in range(0, n, 64):
+        k1 = min(n, k0 + 64)
+        a, r = np.tril(x[k0:k1, k0:k1]), np.eye(k1 - k0)
+        for j in range(k1 - k0):
+            u = a[j + 1:, j] * (1 / a[j, j])
+            a[j + 1:, j + 1:] = fma(-u[:, None], a[j + 1:, j][None], a[j + 1:, j + 1:])
+            a[j, j] = np.sqrt(a[j, j])
+            a[j + 1:, j] /= a[j, j]
+        for j in range(k1 - k0):
+            r[j] /= a[j, j]
+            r[j + 1:] = fma(-a[j + 1:, j][:, None], r[j][None], r[j + 1:])
+        y[k0:k1, k0:k1] = np.tril(r)
+        p = x[k1:, k0:k1] = chain(x[k1:, k0:k1], y[k0:k1, k0:k1].T)
+        x[k0:k1, k0:k1] = np.tril(a)
+        x[k1:, k1:] -= chain(p, p.T)
+    b = 64
+    while b < n:
+        for o in range(0, n - b, 2 * b):
+            h, e = o + b, min(n, o + 2 * b)
+            y[h:e, o:h] = -chain(y[h:e, h:e], chain(x[h:e, o:h], y[o:h, o:h]))
+        b *= 2
+    return chain(np.ascontiguousarray(y.T), y)
+
+
+def test_inverse_is_as_accurate_as_64_wide_steps():
+    """M^-1 of order 520 against extended precision: the geometric mean over two
+    seeds of its error over that of the same steps in FP64 is 1 within the scatter
+    of single matrices (2 %); sums of 256 terms between two subtractions are at
+    1.08."""
+    ratios = []
+    for seed in range(2):
+        n, n_phi, n_mu = (16, 18, 20), 30, 520
+        n_r = 16 * 18 * 20
+        rng = np.random.default_rng(seed)
+        phi = rng.standard_normal((*n, n_phi)) + 1j * rng.standard_normal((*n, n_phi))
+        for axis in range(3):
+            phi = 0.5 * phi + 0.25 * (np.roll(phi, 1, axis) + np.roll(phi, -1, axis))
+        phi = phi.reshape(n_r, n_phi) * 10.0 ** (-rng.random((n_r, 1)))
+        idx = rng.permutation(n_r)[:n_mu]
+        p = phi[idx]
+        a = p.astype(CLD) @ p.conj().T.astype(CLD)
+        l, y = (a.real ** 2 + a.imag ** 2).astype(LD), np.eye(n_mu, dtype=LD)
+        for k in range(n_mu):  # the exact inverse, by elimination
+            f = l[k + 1:, k] / l[k, k]
+            l[k + 1:, k + 1:] -= f[:, None] * l[k, k + 1:][None]
+            y[k + 1:, : k + 1] -= f[:, None] * y[k, : k + 1][None]
+        exact = y.T @ (y / np.diag(l)[:, None])
+        re, im = np.zeros((n_mu, n_mu)), np.zeros((n_mu, n_mu))
+        for k in range(n_phi):  # the Gram product in k order
+            s, t = p[:, k].real, p[:, k].imag
+            re = fma(t[:, None], t[None], fma(s[:, None], s[None], re))
+            im = fma(-s[:, None], t[None], fma(t[:, None], s[None], im))
+        _, minv, info = isdf.fit(dev(phi), None, dev(idx.astype(np.int32)), grid=n, nrows=0)
+        assert info["status"] == 0
+        scale = np.sqrt(np.outer(np.diag(exact), np.diag(exact)))
+        off = lambda w: float(np.linalg.norm(((w - exact) / scale).astype(np.float64)))
+        ratios.append(off(minv.cpu().numpy().reshape(n_mu, n_mu)) / off(blocked_inverse(re * re + im * im)))
+    assert np.exp(np.mean(np.log(ratios))) <= 1.04, ratios

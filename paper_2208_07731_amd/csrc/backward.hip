@@ -856,7 +856,7 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
         const int64_t mp = w.mp, fp64 = ceil_div(rows, mp) * ceil_div(mp, 128) * ceil_div(n1, 128);
         if (!fill<double>(P.lpart, fp64, 0.0, s)) return ISDF_E_HIP;
         ltiles = fp64;
-        if (!mod_prepare<double>(Gb, n1, rows, P.W2, n1, n1 / hc, n1 / hc, MOD_DIAG_B, w, ab, s)) return ISDF_E_HIP;
+        if (!mod_prepare<double>(Gb, n1, rows, P.W2, n1, n1 / hc, n1 / hc, MOD_DIAG_B, 0.0, w, ab, s)) return ISDF_E_HIP;
         for (int64_t q = 0, p = 0; q < rows; q += mp, ++p) {
           const int pr = (int)(rows - q < mp ? rows - q : mp);
           double *Aq = Ab + q * 2 * n_mu, *Bq = aliased ? nullptr : Bb + q * 2 * n_mu, *Gq = Gb + q * n1;
@@ -880,7 +880,8 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
       if (!launch_ok()) return ISDF_E_HIP;
     } else {
       // Theta = G M^-1, S = Thetabar M^-1 (over G), P += Theta^T S, Abar / Bbar in place
-      if (!nt_product<double>(rows, n1, n1, Gb, n1, minv, n1, MOD_DIAG_B, P.Th, n1, 1.0, P.mod, false, ab, s))
+      if (!nt_product<double>(rows, n1, n1, Gb, n1, minv, n1, MOD_DIAG_B, P.Th, n1, 1.0, P.mod, false, ab, s,
+                              sizeof(TT) == 4 ? MOD_TOL_SINGLE : 0.0))
         return ISDF_E_HIP;
       const int64_t ldt = aliased ? ld_tbar : 2 * ld_tbar;
       if (!nt_product<double, TT>(rows, n1, n1, tbar + (r - gbase) * ldt, ldt, minv, n1, MOD_DIAG_B, Gb, n1, 1.0, P.mod,

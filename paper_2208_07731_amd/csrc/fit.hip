@@ -134,7 +134,9 @@ static int fit_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
                         minv, n1, aliased ? G_REAL : G_EMB, ab, s, P.sc, &P.sw))
       return ISDF_E_HIP;
     ISDF_TRY(spd_inverse(minv, n1, P.inv, P.st, s));
-    if (!aliased && !to_block_form(minv, n_mu, ab, s)) return ISDF_E_HIP;
+    // (the copies differ by the contractions' error, 2^-33 in BF16x6; in FP32 by
+    // 2^-25, more than a result in double should move)
+    if (!aliased && PREC != ISDF_P_FP32 && !to_block_form(minv, n_mu, ab, s)) return ISDF_E_HIP;
   }
   for (int64_t r = 0; r < nrows; r += rblock) {
     const int rows = (int)(nrows - r < rblock ? nrows - r : rblock);
@@ -174,7 +176,8 @@ static int resid_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const
     if (!gram<PREC, TS>(phi, ld_phi, n_phi, psi, ld_psi, n_psi, aliased, Ephi, Epsi, nmu16, n_mu, nullptr, nr, r, rows,
                         P.G, n1, aliased ? G_REAL : G_CPLX, ab, s, P.sc, &P.sw))
       return ISDF_E_HIP;
-    if (!nt_product<double>(rows, n1, n1, P.G, n1, minv, n1, MOD_DIAG_B, P.Th, n1, 1.0, P.mod, r > 0, ab, s))
+    if (!nt_product<double>(rows, n1, n1, P.G, n1, minv, n1, MOD_DIAG_B, P.Th, n1, 1.0, P.mod, r > 0, ab, s,
+                            sizeof(TS) == 4 ? MOD_TOL_SINGLE : 0.0))
       return ISDF_E_HIP;
     hipLaunchKernelGGL((fit_resid_rows<TS>), dim3(RESID_BLOCKS), dim3(PAIR_THREADS), 0, s, (const double*)P.G,
                        (const double*)P.Th, rows, n1, phi, ld_phi, n_phi, psi, ld_psi, n_psi, aliased ? 1 : 0, r,

@@ -498,14 +498,16 @@ static bool dgemm(int M, int N, int64_t K, const TA* A, int64_t lda, const doubl
 // two operands.  `prepared`: the powers of two and B's residues are in the
 // buffers from an earlier call.  With complex buffers B
 // has to be the real 2 x 2 block form of a complex matrix, M, N, K count reals
-// all the same, and the product is the complex one of half N and K.
+// all the same, and the product is the complex one of half N and K (tol: how far
+// B may be from that form, mod_blocks).
 template <class TC, class TA = double>
 static bool nt_product(int64_t M, int N, int K, const TA* A, int64_t lda, const double* B, int64_t ldb, int bal, TC* C,
-                       int64_t ldc, double alpha, const ModWork& w, bool prepared, const int* abort, hipStream_t st) {
+                       int64_t ldc, double alpha, const ModWork& w, bool prepared, const int* abort, hipStream_t st,
+                       double tol = sizeof(TC) == 4 ? MOD_TOL_SINGLE : 0.0) {
   const int h = w.cplx ? 2 : 1;
   if (!w.mp || !(w.cplx ? mod_pays_c(M, N / h, K / h) : mod_pays(M, N, K)))
     return dgemm<KC, KC, TC, TA>((int)M, N, K, A, lda, B, ldb, C, ldc, alpha, 0.0, 0, abort, st);
-  if (!(prepared ? mod_next(w, st) : mod_prepare<TA>(A, lda, (int)M, B, ldb, N / h, K / h, bal, w, abort, st)))
+  if (!(prepared ? mod_next(w, st) : mod_prepare<TA>(A, lda, (int)M, B, ldb, N / h, K / h, bal, tol, w, abort, st)))
     return false;
   const int vec = ldc % 2 == 0 && (uintptr_t)C % (2 * sizeof(TC)) == 0;
   for (int64_t r = 0, p = 0; r < M; r += w.mp, ++p) {

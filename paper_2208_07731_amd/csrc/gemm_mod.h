@@ -860,24 +860,31 @@ static bool mod_rows(const TS* X, int64_t ld, int rows, int K, const ModWork& w,
 // diagonal of one of them (symmetric of order K), or the columns of both.
 enum { MOD_DIAG_A = 1, MOD_DIAG_B = 2, MOD_MEANS = 3 };
 
-// Raises the flag unless B (order 2 K) is exactly the real 2 x 2 block form of a
-// complex matrix, [[re, im], [-im, re]] per entry, whose even rows say it all; any
-// other matrix keeps the FP64 kernel (block_form makes the library's own exact).
-__global__ __launch_bounds__(256) void mod_blocks(const double* __restrict__ B, int64_t ldb, int K, int* flag) {
+// Raises the flag unless B (order 2 K) is the real 2 x 2 block form of a complex
+// matrix, [[re, im], [-im, re]] per entry, whose even rows say it all: exactly
+// for results in double (block_form makes the library's own matrices exact), to
+// `tol` of the diagonals' geometric mean for results stored in single.  Any other
+// matrix keeps the FP64 kernel.
+constexpr double MOD_TOL_SINGLE = 0x1p-24;
+__global__ __launch_bounds__(256) void mod_blocks(const double* __restrict__ B, int64_t ldb, int K, double tol,
+                                                  int* flag) {
   const int i = blockIdx.y;
   const double* r0 = B + 2 * i * ldb;
   const double* r1 = r0 + ldb;
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < K; j += gridDim.x * blockDim.x)
-    if (!(r0[2 * j] == r1[2 * j + 1] && r0[2 * j + 1] == -r1[2 * j])) atomicOr(flag, 1);
+  const double di = r0[2 * i];
+  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < K; j += gridDim.x * blockDim.x) {
+    const double e = fabs(r0[2 * j] - r1[2 * j + 1]) + fabs(r0[2 * j + 1] + r1[2 * j]);
+    if (!(e <= tol * sqrt(fabs(di * B[2 * j * (ldb + 1)])))) atomicOr(flag, 1);
+  }
 }
 
 // Powers of two and residues of B (N x K), once per call; A: the other operand
 // (M rows).  Complex (w.cplx): B is the real 2 x 2 block form of a complex N x K
 // matrix, whose rows are the even ones, and the product is A B^H (bal =
-// MOD_DIAG_B: N = K, checked by mod_blocks).  MOD_MEANS: complex only.
+// MOD_DIAG_B: N = K, checked by mod_blocks to `tol`).  MOD_MEANS: complex only.
 template <class TA>
 static bool mod_prepare(const TA* A, int64_t lda, int M, const double* B, int64_t ldb, int N, int K, int bal,
-                        const ModWork& w, const int* abort, hipStream_t s) {
+                        double tol, const ModWork& w, const int* abort, hipStream_t s) {
   const int step = w.cplx ? 2 : 1;
   hipLaunchKernelGGL(mod_clear, dim3(1), dim3(256), 0, s, w.flags, w.nflags);
   if (bal == MOD_MEANS) {
@@ -889,7 +896,8 @@ static bool mod_prepare(const TA* A, int64_t lda, int M, const double* B, int64_
                        step, w.d, w.di);
   }
   if (w.cplx && bal == MOD_DIAG_B)
-    hipLaunchKernelGGL(mod_blocks, dim3((unsigned)ceil_div(K, 1024), (unsigned)K), dim3(256), 0, s, B, ldb, K, w.flags);
+    hipLaunchKernelGGL(mod_blocks, dim3((unsigned)ceil_div(K, 1024), (unsigned)K), dim3(256), 0, s, B, ldb, K, tol,
+                       w.flags);
   return mod_rows<double>(B, step * ldb, N, K, w, bal == MOD_DIAG_A ? w.d : w.di, true, w.b, w.rb, w.flags, abort, s);
 }
 

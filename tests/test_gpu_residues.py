@@ -122,10 +122,11 @@ def _block_form(n_mu, seed):
 
 
 # one entry of an odd row: by half a unit in the last place, by 1e-9 of the diagonal
-@pytest.mark.parametrize("off", [0.0, 2.0 ** -52, 1e-9])
-def test_a_matrix_almost_of_block_form_is_multiplied_as_it_is(off):
-    """The complex product reads a matrix's even rows only, so it stands for a
-    matrix of exact blocks alone; any other one gives the FP64 kernel's bits."""
+@pytest.mark.parametrize("dt,off", [(L.C128, 0.0), (L.C128, 2.0 ** -52), (L.C128, 1e-9), (L.C64, 2.0 ** -20)])
+def test_a_matrix_almost_of_block_form_is_multiplied_as_it_is(dt, off):
+    """The complex product reads a matrix's even rows only, so for results in
+    double it stands for a matrix of exact blocks alone, and in single for one
+    within 2^-24; any other one gives the FP64 kernel's bits."""
     lib = L.load()
     n_mu, rows = 600, 2304
     Gh = np.random.default_rng(1).standard_normal((rows, 2 * n_mu))
@@ -133,12 +134,13 @@ def test_a_matrix_almost_of_block_form_is_multiplied_as_it_is(off):
     Wh[7, 7] += off * Wh[7, 7]
     G, W = torch.from_numpy(Gh).cuda(), torch.from_numpy(Wh).cuda()
     ws = torch.empty(lib.isdf_apply_minv_workspace(n_mu, 0, rows), dtype=torch.uint8, device="cuda")
-    got = _apply(lib, G, W, n_mu, 0, rows, L.C128, n_mu, ws)
-    ref = _apply(lib, G, W, n_mu, 0, rows, L.C128, n_mu, None)
+    got = _apply(lib, G, W, n_mu, 0, rows, dt, n_mu, ws)
+    ref = _apply(lib, G, W, n_mu, 0, rows, dt, n_mu, None)
     assert torch.equal(torch.view_as_real(got), torch.view_as_real(ref)) == (off != 0.0)
 
 
-def test_the_fit_leaves_exact_blocks():
+@pytest.mark.parametrize("prec", ["fp64", "bf16x6", "fp16x3"])
+def test_the_fit_leaves_exact_blocks(prec):
     """M^-1 of two orbital sets, of an order whose inverse is formed whole and of
     one whose lower half is mirrored."""
     import paper_2208_07731_amd as isdf
@@ -148,7 +150,7 @@ def test_the_fit_leaves_exact_blocks():
     phi, psi = c(24), c(40)
     for n_mu in (65, 401):
         idx = torch.from_numpy(rng.permutation(2016)[:n_mu].astype(np.int32)).cuda()
-        _, minv, _ = isdf.fit(phi, psi, idx, grid=(12, 12, 14), nrows=0)
+        _, minv, _ = isdf.fit(phi, psi, idx, grid=(12, 12, 14), nrows=0, prec=prec)
         w = minv.reshape(2 * n_mu, 2 * n_mu)
         assert torch.equal(w[0::2, 0::2], w[1::2, 1::2]) and torch.equal(w[0::2, 1::2], -w[1::2, 0::2])
         assert torch.equal(w, w.T)

@@ -180,7 +180,8 @@ struct EpiSAdj {
 // EpiSAdj for the residue form of the product: the same arithmetic on the 4
 // consecutive outputs of a thread (two whole columns nu in the complex case),
 // loss and maxima summed per workgroup.  G and A are read while the residues are
-// put together (64-water blocks 524 -> 429 us per 16384 rows, 1.85 GB).
+// put together (64-water blocks 524 -> 429 us per 16384 rows with 15 residues;
+// 455 with 17, 1.9 GB).
 struct ModSAdj {
   static constexpr int REP = 8;
   struct Sum {
@@ -724,7 +725,7 @@ static bool orbital_fix(const double* dAbar, int n_mu, const typename Prec<PREC>
   bool done = false;
   if constexpr (sizeof(T) == 8)
     if (modf.mp && mod_pays_c(n_mu, n, n_mu)) {
-      // 8192 x 1024 x 8192 complex: 9.4 ms on the FP64 matrix cores, 2.8 by residues
+      // 8192 x 1024 x 8192 complex: 9.4 ms on the FP64 matrix cores, 3.3 by residues
       if (!nt_product<double>(n_mu, 2 * n, (int)two_mu, dAbar, two_mu, F, two_mu, MOD_MEANS, T1, 2 * (int64_t)n, 1.0,
                               modf, false, ab, s))
         return false;

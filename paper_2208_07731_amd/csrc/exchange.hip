@@ -17,7 +17,7 @@ namespace {
 // never stored.  64^3, 2048 points, 256 orbitals: a pass of its own over A (24
 // bytes read and 16 written per entry) took 4.5 ms of 38.7 and the FP64 product
 // behind it 17.2; this epilogue costs nothing that can be told from the clock's
-// drift, and the residue product takes 12 (split 5.9, int8 products 5.3).
+// drift, and the residue product takes 14 (split 7.3, int8 products 5.8).
 // Multiplying by V as the rows are split instead: 8.0 for the split, 34.5 in all
 // against 32.8.
 template <class TS>

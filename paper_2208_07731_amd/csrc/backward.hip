@@ -481,7 +481,7 @@ static BwdPlan plan_bwd(void* ws, size_t cap, int64_t nr, int n_mu, int n_phi, i
   const size_t tsize = tsize_of(prec);
   Carver c(ws, cap);
   BwdPlan P{};
-  P.caps = bwd_split_caps(nr, rblock, aliased, n_mu, n_phi, n_psi, prec == ISDF_P_FP32, slots);
+  P.caps = bwd_split_caps(nr, rblock, aliased, n_mu, n_phi, n_psi, slots);
   const int nmu16 = (int)ceil_div(n_mu, 16) * 16;
   const int64_t n1 = aliased ? n_mu : 2 * (int64_t)n_mu;
   const int nmax = n_phi > n_psi ? n_phi : n_psi;
@@ -814,8 +814,8 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
     if (!Gs && !gram<PREC, TS>(phi, ld_phi, n_phi, psi, ld_psi, n_psi, aliased, Ephi, Epsi, nmu16, n_mu, nullptr, nr,
                                r, rows, Gb, n1, aliased ? G_REAL : G_CPLX, ab, s, P.sc, &P.sw, Ab, Bb))
       return ISDF_E_HIP;
-    const BwdSplits sp_phi = bwd_splits(rows, n1, n_mu, n_phi, !tbar, PREC == ISDF_P_FP32, P.slots, P.caps);
-    const BwdSplits sp_psi = bwd_splits(rows, n1, n_mu, n_psi, !tbar, PREC == ISDF_P_FP32, P.slots, P.caps);
+    const BwdSplits sp_phi = bwd_splits(rows, n1, n_mu, n_phi, !tbar, P.slots, P.caps);
+    const BwdSplits sp_psi = bwd_splits(rows, n1, n_mu, n_psi, !tbar, P.slots, P.caps);
     constexpr int SPLIT = Prec<PREC>::SPLIT;
     if (!tbar) {
       // H += G^T diag(g) G (lower tiles, fixed-order reduction): FP64 split-K,

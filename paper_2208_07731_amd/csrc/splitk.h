@@ -20,29 +20,52 @@ static inline int64_t out_tiles(int64_t M, int64_t N, int64_t tile, int lower) {
   return lower ? tm * (tm + 1) / 2 : tm * tn;
 }
 
-// Tile and split-K factor of an M x N product of K-deep sums (its lower tiles
-// only when `lower`): 1 or a multiple of 8 (one K slice per XCD at a time) up
-// to `cap`, slices of at least 4 tile edges of rows, chosen to minimise the
-// modelled time ceil(tiles s / CUs) (K / s) t_row + s M N 16 B / bw, i.e. whole
-// rounds of workgroups against the partial sums' write and read.  A round of
-// one workgroup per CU runs at about the rate of two (the matrix cores bound
-// both), hence CUs and not resident workgroups.  Small outputs get 64-tiles:
-// 256 x 256 lower tiles over 13824 rows 96 us on 128-tiles, 39 on these; 512 x
-// 64 over 13824 rows 98 and 29.
+// Slices that an M x N product of K-deep sums (its lower tiles only when `lower`)
+// takes at least: a slice is one chain of additions, and fewer, longer chains are
+// less accurate.  As many as 128-wide tiles at two workgroups per CU are fastest
+// with; by time alone splits_for takes a quarter of them in places, which put FP32
+// gradients of 40^3 points, 256 orbitals off by 6.5e-7 instead of 4.8e-7 and FP64
+// ones of 24^3, 200 points by 1.6e-15 instead of 1.1e-15.
+static inline int least_splits(int64_t M, int64_t N, int lower, int64_t K, int slots, int cap) {
+  const int64_t tiles = out_tiles(M, N, 128, lower);
+  const double t_row = 2.0 * 128 * 128 / (60e12 / slots), bw = 4e12;
+  int best = 1;
+  double best_t = 0.0;
+  for (int s = 1; s <= cap; s = s < 8 ? 8 : s + 8) {
+    if (s > 1 && (K + s - 1) / s < 512) break;
+    const double waves = (double)((tiles * s + slots - 1) / slots);
+    const double t = waves * ((double)K / s) * t_row + (s > 1 ? s * (double)M * (double)N * 16.0 / bw : 0.0);
+    if (s == 1 || t < best_t * (1.0 - 1e-9)) {
+      best = s;
+      best_t = t;
+    }
+  }
+  return best;
+}
+
+// Tile and split-K factor of such a product: 1 or a multiple of 8 (one K slice per
+// XCD at a time) from least_splits up to `cap`, slices of at least 4 tile edges of
+// rows, chosen to minimise the modelled time ceil(tiles s / CUs) (K / s) t_row +
+// s M N 16 B / bw, i.e. whole rounds of workgroups against the partial sums' write
+// and read.  A round of one workgroup per CU runs at about the rate of two (the
+// matrix cores bound both), hence CUs and not resident workgroups.  Small outputs
+// get 64-tiles: 256 x 256 lower tiles over 13824 rows 96 us on 128-tiles, 39 on
+// these; 512 x 64 over 13824 rows 98 and 29.
 static inline TilePlan splits_for(int64_t M, int64_t N, int lower, int64_t K, int slots, int cap) {
   const int64_t cus = slots / 2 > 0 ? slots / 2 : 1;
   const double bw = 4e12;  // B/s for the partials
-  TilePlan best{128, 1};
-  double best_t = 0.0;
+  const int least = least_splits(M, N, lower, K, slots, cap);
+  TilePlan best{128, least};
+  double best_t = -1.0;
   for (int tile = 128; tile >= 64; tile /= 2) {
     const int64_t tiles = out_tiles(M, N, tile, lower);
     const double t_row = 2.0 * tile * tile / (60e12 / (double)cus);  // s per k-row and tile
-    for (int s = 1; s <= cap; s = s < 8 ? 8 : s + 8) {
+    for (int s = least; s <= cap; s = s < 8 ? 8 : s + 8) {
       if (s > 1 && (K + s - 1) / s < 4 * tile) break;
       const double rounds = (double)((tiles * s + cus - 1) / cus);
       double t = rounds * ((double)K / s) * t_row + (s > 1 ? s * (double)M * (double)N * 16.0 / bw : 0.0);
       if (tile == 64) t *= 1.05;  // twice the operand traffic
-      if ((tile == 128 && s == 1) || t < best_t * (1.0 - 1e-9)) {
+      if (best_t < 0.0 || t < best_t * (1.0 - 1e-9)) {
         best = TilePlan{tile, s};
         best_t = t;
       }
@@ -77,65 +100,37 @@ static inline int split_k_for(int64_t tiles, int64_t K, int64_t mn, int slots, b
   return best;
 }
 
-// Slices that a product with FP32 sums takes at least: a slice is one chain of FP32
-// additions (the slices are added in FP64), so fewer, longer ones are less
-// accurate.  As many as 128-wide tiles at two workgroups per CU are fastest with;
-// splits_for alone takes a quarter of them or one in places (32 orbitals, 800
-// points, 110592 rows: 8 for 32).
-static inline int fp32_slices(int64_t M, int64_t N, int64_t K, int slots, int cap) {
-  const int64_t tiles = out_tiles(M, N, 128, 0);
-  const double t_row = 2.0 * 128 * 128 / (60e12 / slots), bw = 4e12;
-  int best = 1;
-  double best_t = 0.0;
-  for (int s = 1; s <= cap; s = s < 8 ? 8 : s + 8) {
-    if (s > 1 && (K + s - 1) / s < 512) break;
-    const double waves = (double)((tiles * s + slots - 1) / slots);
-    const double t = waves * ((double)K / s) * t_row + (s > 1 ? s * (double)M * (double)N * 16.0 / bw : 0.0);
-    if (s == 1 || t < best_t * (1.0 - 1e-9)) {
-      best = s;
-      best_t = t;
-    }
-  }
-  return best;
-}
-
 // Plans the adjoint uses for blocks of `rows` rows.
 struct BwdSplits {
   TilePlan h;  // Theta^T S (general) or H = G^T g G (fused, lower tiles)
   TilePlan q;  // Abar^T X per orbital set
 };
 
-// Factors the adjoint's partial buffers hold.  The factor chosen for a length
-// is not monotone in it (a shorter block may take 64-tiles and more, shorter
-// slices), so each block's plan is capped by what the buffers were sized for.
+// Factors the adjoint's partial buffers hold: the most that the lengths they are
+// sized for take.  Nothing makes a shorter block take fewer (by time alone it may
+// take 64-tiles and more, shorter slices), so each block's plan is capped by them.
 struct SplitCaps {
   int h, q;
 };
 
-// fp32: Abar^T X in FP32 sums.
-static inline BwdSplits bwd_splits(int64_t rows, int64_t n1, int n_mu, int n, bool fused, bool fp32, int slots,
-                                   SplitCaps cap) {
+static inline BwdSplits bwd_splits(int64_t rows, int64_t n1, int n_mu, int n, bool fused, int slots, SplitCaps cap) {
   BwdSplits b;
   b.h = splits_for(n1, n1, fused ? 1 : 0, rows, slots, cap.h);
   b.q = splits_for(2 * (int64_t)n_mu, 2 * (int64_t)n, 0, rows, slots, cap.q);
-  if (fp32) {
-    const int least = fp32_slices(2 * (int64_t)n_mu, 2 * (int64_t)n, rows, slots, cap.q);
-    if (b.q.splits < least) b.q.splits = least;
-  }
   return b;
 }
 
 // Sizes the partial buffers by the lengths of a sweep in equal blocks, rblock
 // and the grid's remainder, for both losses and both orbital sets.
 static inline SplitCaps bwd_split_caps(int64_t nr, int64_t rblock, bool aliased, int n_mu, int n_phi, int n_psi,
-                                       bool fp32, int slots) {
+                                       int slots) {
   const SplitCaps any{MAX_SPLITS, MAX_SPLITS};
   const int64_t n1 = aliased ? n_mu : 2 * (int64_t)n_mu;
   SplitCaps c{1, 1};
   for (int64_t rows : {rblock, nr - ((nr + rblock - 1) / rblock - 1) * rblock})
     for (int n : {n_phi, n_psi})
       for (bool fused : {false, true}) {
-        const BwdSplits b = bwd_splits(rows, n1, n_mu, n, fused, fp32, slots, any);
+        const BwdSplits b = bwd_splits(rows, n1, n_mu, n, fused, slots, any);
         c.h = b.h.splits > c.h ? b.h.splits : c.h;
         c.q = b.q.splits > c.q ? b.q.splits : c.q;
       }

@@ -19,10 +19,10 @@ def dev(x):
     return torch.as_tensor(np.ascontiguousarray(x)).cuda()
 
 
-# blocks whose own best split-K plan has more slices than the plans of rblock
-# and of the grid's remainder: 32 against 24 of G^T Thetabar (or Theta^T S) for
-# 9984 to 12032 rows of 168 points, two sets; 32 against 24 of Abar^T Phi for
-# 12032 rows of 519 points and 64 orbitals
+# blocks that by time alone take more split-K slices than rblock and the grid's
+# remainder do: 32 against 24 of Theta^T S for 9984 to 12032 rows of 168 points,
+# two sets; 32 against 24 of Abar^T Phi for 12032 rows of 519 points and 64
+# orbitals
 @pytest.mark.parametrize("n_phi,n_psi,n_mu,fused,blocks", [
     (16, 16, 168, 0, (11008, 11008, 14848)),
     (16, 16, 168, 1, (14848, 11008, 11008)),

@@ -251,3 +251,27 @@ def test_adjoint_with_a_flagged_panel(n_phi, n_psi, n_mu, fused, row):
         assert rel(dpsi, ref["dpsi"]) <= bar
     if fused:
         assert abs(loss.item() - ref["loss"]) <= bar * ref["loss"]
+
+
+def test_rows_at_the_points_by_residues():
+    """dAbar Phi_mu at 2049 interpolation rows and Abar Phi_mu of blocks of 2100
+    rows (the last one shorter, on the FP64 kernel), 256 orbitals: both products
+    are on the residues' side of the rule.  Against the oracle, within 1e-11 or
+    n_mu eps kappa."""
+    import oracle
+    import paper_2208_07731_amd as isdf
+
+    n, n_r, n_phi, n_mu = (16, 17, 16), 16 * 17 * 16, 256, 2049
+    assert L.load().isdf_residue_ops(n_mu, n_phi, n_mu, 1) == 9
+    rng = np.random.default_rng(12)
+    phi = rng.standard_normal((n_r, n_phi)) + 1j * rng.standard_normal((n_r, n_phi))
+    idx = rng.permutation(n_r)[:n_mu].astype(np.int32)
+    g = rng.uniform(0.5, 1.5, n_r)
+    ref = oracle.fit_backward(phi, phi, idx, g=g)
+    d = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    a = d(phi)
+    _, minv, _ = isdf.fit(a, None, d(idx), grid=n, nrows=0)
+    dphi, _, loss, _ = isdf.fit_backward(a, None, d(idx), minv, g=d(g), grid=n, rblock=2100)
+    bar = max(1e-11, n_mu * EPS * oracle.cc_condition(phi, phi, idx))
+    assert float(np.linalg.norm(dphi.cpu().numpy() - ref["dphi"]) / np.linalg.norm(ref["dphi"])) <= bar
+    assert abs(loss.item() - ref["loss"]) <= bar * ref["loss"]

@@ -270,11 +270,11 @@ int isdf_apply_minv(int32_t n_mu, int32_t aliased, const double* minv, const dou
  * where an FP64 sum is off by a multiple of 2^-53 of the sum of moduli of its
  * own terms: less, but for results that lie far below the norms of their row and
  * column.  With Psi != Phi they take a minv of exact blocks [[re, im], [-im,
- * re]], as isdf_fit leaves it (FP32 contractions: to 2^-25 of the diagonals'
- * mean), and for single-precision results one that is within 2^-24 of them; any
- * other one is multiplied by the FP64 kernel.
- * isdf_fit, the adjoint and isdf_exchange take the same products by the same
- * rule.  ws null: isdf_apply_minv.
+ * re]], as isdf_fit leaves it where they are used (FP32 contractions: to 2^-25 of
+ * the diagonals' mean), and for single-precision results one that is within 2^-24
+ * of them; any other one is multiplied by the FP64 kernel.  isdf_fit, the adjoint
+ * and isdf_exchange take the same products by the same rule.  ws null:
+ * isdf_apply_minv.
  */
 size_t isdf_apply_minv_workspace(int32_t n_mu, int32_t aliased, int64_t nrows);
 int isdf_apply_minv_ws(int32_t n_mu, int32_t aliased, const double* minv, const double* G, int64_t ldg,

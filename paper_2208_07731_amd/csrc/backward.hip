@@ -794,7 +794,7 @@ static int bwd_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
     if (!tbar) {  // (C C^H)^-2
       if (!nt_product<double>(n1, n1, n1, minv, n1, minv, n1, MOD_DIAG_B, P.W2, n1, 1.0, P.mod1, false, ab, s))
         return ISDF_E_HIP;
-      if (!aliased && !to_block_form(P.W2, n_mu, ab, s)) return ISDF_E_HIP;
+      if (!aliased && P.mod.mp && !to_block_form(P.W2, n_mu, ab, s)) return ISDF_E_HIP;
     }
   }  // BWD_BEGIN
   for (int64_t r = row_lo; r < row_hi; r += rblock) {

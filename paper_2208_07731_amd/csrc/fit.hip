@@ -134,9 +134,11 @@ static int fit_run(int64_t nr, const TS* phi, int64_t ld_phi, int n_phi, const T
                         minv, n1, aliased ? G_REAL : G_EMB, ab, s, P.sc, &P.sw))
       return ISDF_E_HIP;
     ISDF_TRY(spd_inverse(minv, n1, P.inv, P.st, s));
-    // (the copies differ by the contractions' error, 2^-33 in BF16x6; in FP32 by
-    // 2^-25, more than a result in double should move)
-    if (!aliased && PREC != ISDF_P_FP32 && !to_block_form(minv, n_mu, ab, s)) return ISDF_E_HIP;
+    // exact blocks where products with the inverse may go by residues.  (The copies
+    // differ by the contractions' error, 2^-33 in BF16x6; in FP32 by 2^-25, more than
+    // a result in double should move)
+    if (!aliased && PREC != ISDF_P_FP32 && mod_pays_c(INT32_MAX, n_mu, n_mu) && !to_block_form(minv, n_mu, ab, s))
+      return ISDF_E_HIP;
   }
   for (int64_t r = 0; r < nrows; r += rblock) {
     const int rows = (int)(nrows - r < rblock ? nrows - r : rblock);

@@ -141,14 +141,13 @@ def test_a_matrix_almost_of_block_form_is_multiplied_as_it_is(dt, off):
 
 @pytest.mark.parametrize("prec", ["fp64", "bf16x6", "fp16x3"])
 def test_the_fit_leaves_exact_blocks(prec):
-    """M^-1 of two orbital sets, of an order whose inverse is formed whole and of
-    one whose lower half is mirrored."""
+    """M^-1 of two orbital sets, of the orders whose products go by residues."""
     import paper_2208_07731_amd as isdf
 
     rng = np.random.default_rng(4)
     c = lambda n: torch.from_numpy(rng.standard_normal((2016, n)) + 1j * rng.standard_normal((2016, n))).cuda()
     phi, psi = c(24), c(40)
-    for n_mu in (65, 401):
+    for n_mu in (449, 601):
         idx = torch.from_numpy(rng.permutation(2016)[:n_mu].astype(np.int32)).cuda()
         _, minv, _ = isdf.fit(phi, psi, idx, grid=(12, 12, 14), nrows=0, prec=prec)
         w = minv.reshape(2 * n_mu, 2 * n_mu)
